@@ -502,25 +502,43 @@ __global__ void __launch_bounds__(256 * (WAVES > 1 ? WAVES / 4 : 1)) threshold_s
   }
 }
 // ========================================================================
-// Filtered path for k <= 64.
+// Filtered path.
 //
-// Ring core: a workgroup multiplies 256 history rows by 256 queries per
-// step; wave w = 2*wh + wq owns the 128 x 128 block of rows wh and queries
-// wq (4 x 4 MFMA 32x32x16 tiles, 256 accumulators). The d axis is walked in
-// 32-wide slices held in a ring of four LDS stages (512 rows x 64 bytes
-// each). Stages are filled by direct global->LDS loads (16 bytes per lane,
-// no registers): waves 0-1 move history rows, waves 2-3 query rows, three
-// slices ahead of the MFMAs and straight across step boundaries, so the
-// pipeline never drains between steps. One barrier per slice.
+// Ring core: a workgroup multiplies 256 history rows by kBQ = 64 WQ queries
+// per step with 2 WQ waves; wave w = wh * WQ + wq owns the 128 x 64 block of
+// rows wh and queries wq (4 x 2 MFMA 32x32x16 tiles, 128 accumulators). The d
+// axis is walked in 32-wide slices held in a ring of LDS stages (256 + kBQ
+// rows x 64 bytes each). Stages are filled by direct global->LDS loads (16
+// bytes per lane, no registers), kStages - 1 slices ahead of the MFMAs and
+// straight across step boundaries, so the pipeline never drains between
+// steps. One barrier per slice.
+//
+// Two waves per SIMD: the epilogue (one subtraction and one funnel shift per
+// score, and the picking of survivors) is bound by VALU issue, and one wave
+// alone issues only every 7 to 7.5 cycles where the SIMD takes one every 4;
+// with 256 registers a wave the accumulators are also plain VGPRs, so that the
+// epilogue reads them in place instead of copying each from an AGPR. Against
+// four waves of 128 x 128 blocks in AGPRs (same tile, 1.5x fewer LDS operand
+// reads), same box: 30.43 -> 29.55 ms at 16,384 x 1M x 1024 (fed by the
+// last-level cache), 1.590 -> 1.449 ms at 4,096 x 262,144 x 768, 174 -> 149 us
+// at 1,001 x 100,003 x 384 (whole decisions).
 // ========================================================================
 namespace ring {
 
 constexpr int kKT = 32;                          // bf16 columns per slice
-constexpr int kStages = 4;                       // a power of two (stage = g & (kStages - 1))
-constexpr int kStageBytes = 512 * kKT * 2;       // 32 KiB
-constexpr int kBQ = 256;                         // queries per tile
-constexpr int kLoads = 8;                        // 16-byte loads per lane per slice
-constexpr int kAhead = kStages - 1;              // slices in flight
+constexpr int kRows = 256;                       // history rows per step
+template <int WQ>
+struct Shape {
+  static constexpr int kWaves = 2 * WQ;
+  static constexpr int kThreads = kWave * kWaves;
+  static constexpr int kBQ = 64 * WQ;            // queries per tile
+  static constexpr int kStages = 4;              // a power of two (stage = g & (kStages - 1))
+  static constexpr int kStageBytes = (kRows + kBQ) * kKT * 2;
+  static constexpr int kHL = kRows / 16 / kWaves;   // history loads per wave and slice
+  static constexpr int kQL = kBQ / 16 / kWaves;     // query loads per wave and slice
+  static constexpr int kLoads = kHL + kQL;
+  static constexpr int kAhead = kStages - 1;     // slices in flight
+};
 
 // 16-byte chunk c (0..3) of LDS row r (64 bytes) is stored at position
 // c ^ swz(r). An MFMA operand read has 16 lanes reading one chunk of 16
@@ -547,12 +565,18 @@ __device__ __forceinline__ void load_to_lds_if(const void* base, uint32_t off, u
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-// Waits until at most n slices (n * kLoads loads) of this wave are in flight.
-__device__ __forceinline__ void wait_slices(int n) {
-  if (n <= 0) wait_loads<0>();
-  else if (n == 1) wait_loads<kLoads>();
-  else if (n == 2) wait_loads<2 * kLoads>();
-  else wait_loads<3 * kLoads>();
+// Waits until at most n slices and, with `half`, half a slice of this wave's
+// loads are in flight (n < kAhead - 1 + 1).
+template <int kLoads>
+__device__ __forceinline__ void wait_slices(int n, bool half) {
+  if (half) {
+    if (n <= 0) wait_loads<kLoads / 2>();
+    else wait_loads<kLoads + kLoads / 2>();
+  } else {
+    if (n <= 0) wait_loads<0>();
+    else if (n == 1) wait_loads<kLoads>();
+    else wait_loads<2 * kLoads>();
+  }
 }
 // Workgroup barrier that first retires this wave's LDS reads. The wait is the
 // compiler's own instruction (lgkmcnt(0), other counters untouched), so its
@@ -563,177 +587,158 @@ __device__ __forceinline__ void barrier() {
 }
 
 struct Frags {
-  bf16x8 a[4], b[4];
+  bf16x8 a[4], b[2];
 };
-
-// Keeps a tile in accumulator registers up to this point of the program, so
-// that epilogues copy tiles out one at a time (bounded register use).
-__device__ __forceinline__ void pin(floatx16& x) { asm volatile("" : "+a"(x)); }
 
 // Runs steps h0 = h_first + j * h_stride (j < n_steps) of query tile q0 and
 // calls epi(acc, h0, step_end) after each, step_end = min(h_limit, h0 + 256),
 // with acc[u][t][v] = S[h][q] for
-//   h = h0 + 128 wh + 32 u + 8 (v / 4) + 4 half + v % 4,  q = q0 + 128 wq + 32 t + l32.
+//   h = h0 + 128 wh + 32 u + 8 (v / 4) + 4 half + v % 4,  q = q0 + 64 wq + 32 t + l32.
 // Rows past N - 1 and queries past Q - 1 are read clamped (their scores are
 // meaningless and must be masked by the caller). Requires d % 32 == 0.
-template <class Epi>
+template <int WQ, class Epi>
 __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, int h_stride, int n_steps,
                                       int h_limit, const EmbView& queries, int Q, int q0, int d, char* lds,
                                       Epi& epi) {
+  using S = Shape<WQ>;
+  constexpr int kLoads = S::kLoads, kHL = S::kHL, kQL = S::kQL, kAhead = S::kAhead;
+  constexpr int kStageMask = S::kStages - 1, kStageBytes = S::kStageBytes;
+  static_assert(kLoads % 2 == 0 && kAhead == 3, "the waits below count half slices, at most two whole ones");
   const int lane = (int)lane_id();
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int wh = w >> 1, wq = w & 1;
+  const int wh = w / WQ, wq = w % WQ;
   const int l32 = lane & 31, half = lane >> 5;
   const int nk = d / kKT;
   const int total = n_steps * nk;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
-  // Loader: slot (8w + i) * 64 + lane of a stage holds chunk (lane & 3) ^ swz
-  // of LDS row 16 (8w + i) + lane / 4, i.e. row r0 + 16 i (r0 = 128 (w & 1) +
-  // lane / 4) of this wave's operand: the history step for w < 2, the query
-  // tile otherwise. swz of that row depends on lane and on i only via i % 2.
-  // swz of those rows is (lane / 16) % 4 for every i.
-  const bool hist_side = w < 2;
-  const int r0 = 128 * (w & 1) + (lane >> 2);
+  // Loader: every wave moves kHL pieces of 16 history rows and kQL pieces of
+  // 16 query rows per slice; lane l carries chunk (l & 3) ^ swz of row l / 4
+  // of a piece (swz of those rows is (l / 16) % 4 for every piece).
+  const int rh = 16 * kHL * w + (lane >> 2), rq = 16 * kQL * w + (lane >> 2);
   const uint32_t cb = (uint32_t)(((lane & 3) ^ swz(lane >> 2)) * 16);
-  // Bytes between rows of this wave's operand and between its 32-column slices.
-  const uint32_t row_bytes = (uint32_t)((hist_side ? hist.row : queries.row) * 2);
-  const long long slice_bytes = (hist_side ? hist.panel : queries.panel) * 2;
+  const uint32_t h_row_bytes = (uint32_t)(hist.row * 2), q_row_bytes = (uint32_t)(queries.row * 2);
+  const long long h_slice_bytes = hist.panel * 2, q_slice_bytes = queries.panel * 2;
   int ld_step = 0, ld_kt = 0;
-  const char* src = nullptr;                  // source of slice ld_kt of step ld_step
-  uint32_t off[kLoads];                       // per-lane byte offsets within a slice
-  auto next_source = [&]() {                  // at the first slice of step ld_step
-    int last;
-    if (hist_side) {
-      const int base_row = h_first + ld_step * h_stride;
-      src = reinterpret_cast<const char*>(emb_at(hist, base_row, 0));
-      last = N - 1 - base_row;
-    } else {
-      src = reinterpret_cast<const char*>(emb_at(queries, q0, 0));
-      last = Q - 1 - q0;
-    }
+  const char* hsrc = nullptr;                 // sources of slice ld_kt of step ld_step
+  const char* const qsrc0 = reinterpret_cast<const char*>(emb_at(queries, q0, 0));
+  const char* qsrc = qsrc0;
+  uint32_t hoff[kHL], qoff[kQL];              // per-lane byte offsets within a slice
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) off[i] = (uint32_t)min(r0 + 16 * i, last) * row_bytes + cb;
+  for (int i = 0; i < kQL; ++i) qoff[i] = (uint32_t)min(rq + 16 * i, Q - 1 - q0) * q_row_bytes + cb;
+  auto next_source = [&]() {                  // at the first slice of step ld_step
+    const int base_row = h_first + ld_step * h_stride;
+    hsrc = reinterpret_cast<const char*>(emb_at(hist, base_row, 0));
+    qsrc = qsrc0;
+    const int last = N - 1 - base_row;
+#pragma unroll
+    for (int i = 0; i < kHL; ++i) hoff[i] = (uint32_t)min(rh + 16 * i, last) * h_row_bytes + cb;
   };
-  // Load i (0..7) of slice g into its stage; then advance to the next slice.
-  auto issue_one = [&](int g, int i, int enabled) {
-    const uint32_t m0 = lds0 + (uint32_t)((g & (kStages - 1)) * kStageBytes + (w * kLoads + i) * 1024);
-    load_to_lds_if(src, off[i], __builtin_amdgcn_readfirstlane(m0), __builtin_amdgcn_readfirstlane(enabled));
-  };
-  auto issue_always = [&](int g, int i) {
-    const uint32_t m0 = lds0 + (uint32_t)((g & (kStages - 1)) * kStageBytes + (w * kLoads + i) * 1024);
-    load_to_lds(src, off[i], __builtin_amdgcn_readfirstlane(m0));
+  // Load i of slice g into its stage: history pieces first, then queries.
+  const uint32_t h_lds = lds0 + (uint32_t)(w * kHL * 1024);
+  const uint32_t q_lds = lds0 + (uint32_t)((kRows / 16 + w * kQL) * 1024);
+  auto issue_one = [&](int g, int i, bool always, int enabled) {
+    const uint32_t stage = (uint32_t)((g & kStageMask) * kStageBytes);
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane(
+        stage + (i < kHL ? h_lds + (uint32_t)i * 1024u : q_lds + (uint32_t)(i - kHL) * 1024u));
+    const char* src = i < kHL ? hsrc : qsrc;
+    const uint32_t off = i < kHL ? hoff[i < kHL ? i : 0] : qoff[i < kHL ? 0 : i - kHL];
+    if (always) load_to_lds(src, off, m0);
+    else load_to_lds_if(src, off, m0, __builtin_amdgcn_readfirstlane(enabled));
   };
   auto advance = [&]() {
-    src += slice_bytes;
+    hsrc += h_slice_bytes;
+    qsrc += q_slice_bytes;
     if (++ld_kt == nk) {
       ld_kt = 0;
       ++ld_step;
       if (ld_step < n_steps) next_source();
     }
   };
-  auto issue = [&](int g) {
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) issue_one(g, i, 1);
-    advance();
-  };
   next_source();
 
   // Operand reads: A = history rows 128 wh + 32 u + l32, B = query rows
-  // 256 + 128 wq + 32 t + l32; k chunk 2 kk + half of the slice.
+  // 256 + 64 wq + 32 t + l32; k chunk 2 kk + half of the slice.
   uint32_t a_off[2], b_off[2];
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk) {
     const uint32_t pos = (uint32_t)(((2 * kk + half) ^ swz(l32)) * 16);
     a_off[kk] = (uint32_t)((128 * wh + l32) * 64) + pos;
-    b_off[kk] = (uint32_t)((256 + 128 * wq + l32) * 64) + pos;
+    b_off[kk] = (uint32_t)((kRows + 64 * wq + l32) * 64) + pos;
   }
-  auto read = [&](int g, int kk, Frags& f) {
-    const char* stage = lds + (g & (kStages - 1)) * kStageBytes;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) f.a[u] = *reinterpret_cast<const bf16x8*>(stage + a_off[kk] + u * 2048);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) f.b[t] = *reinterpret_cast<const bf16x8*>(stage + b_off[kk] + t * 2048);
-  };
-  // Piece p of the fragments: A tile p (p < 4) or B tile p - 4.
+  // Piece p of the fragments in the order of use: B0, A0, B1, A1, A2, A3.
   auto read_piece = [&](int g, int kk, int p, Frags& f) {
-    const char* stage = lds + (g & (kStages - 1)) * kStageBytes;
-    if (p < 4) f.a[p] = *reinterpret_cast<const bf16x8*>(stage + a_off[kk] + p * 2048);
-    else f.b[p - 4] = *reinterpret_cast<const bf16x8*>(stage + b_off[kk] + (p - 4) * 2048);
+    const char* stage = lds + (g & kStageMask) * kStageBytes;
+    if (p == 0) f.b[0] = *reinterpret_cast<const bf16x8*>(stage + b_off[kk]);
+    else if (p == 2) f.b[1] = *reinterpret_cast<const bf16x8*>(stage + b_off[kk] + 2048);
+    else {
+      const int u = p == 1 ? 0 : p - 2;
+      f.a[u] = *reinterpret_cast<const bf16x8*>(stage + a_off[kk] + u * 2048);
+    }
   };
 
   __syncthreads();                              // earlier users of the LDS are done
   const int pre = min(kAhead, total);
-  for (int g = 0; g < pre; ++g) issue(g);
-  wait_slices(pre - 1);                         // slice 0 has landed
+  for (int g = 0; g < pre; ++g) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) issue_one(g, i, true, 1);
+    advance();
+  }
+  wait_slices<kLoads>(pre - 1, false);          // slice 0 has landed
   barrier();
   Frags f0, f1;
-  read(0, 0, f0);
+#pragma unroll
+  for (int p = 0; p < 6; ++p) read_piece(0, 0, p, f0);
   int g = 0;
   for (int step = 0; step < n_steps; ++step) {
-    floatx16 acc[4][4];
+    floatx16 acc[4][2];
     // One slice: f0 holds its first 16 columns on entry; on exit f0 holds the
     // first 16 columns of slice g + 1 (past the last slice those reads fetch
     // a stale stage, which is never used).
     //  * The fragment reads are spread over the MFMAs, one after each of the
-    //    first eight of a half, pinned there with scheduling groups: issued
-    //    as one burst next to their consumers, the compiler waits on them and
-    //    the matrix pipe drains (measured: 1.4 PF/s for a burst schedule
-    //    against 2.0 PF/s interleaved, MFMA + LDS only). A read never
-    //    overwrites a fragment that an MFMA still in the pipe reads: the
-    //    previous users of f1 (f0) were issued a half-slice earlier.
-    //  * The eight loads of slice g + kAhead (whose stage was last read in
-    //    slice g - 1) go out four in each half, which keeps the address unit
+    //    first six of a half, pinned there with scheduling groups: issued as
+    //    one burst next to their consumers, the compiler waits on them and
+    //    the matrix pipe drains.
+    //  * The loads of slice g + kAhead (whose stage was last read in slice
+    //    g - 1) go out half of them in each half, which keeps the address unit
     //    evenly busy.
     auto slice = [&](bool first, bool steady) {
       const int more = steady ? 1 : (g + kAhead < total);
       const floatx16 zero = {};
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int u = j >> 2, t = j & 3;
+      for (int j = 0; j < 8; ++j) {
+        const int u = j >> 1, t = j & 1;
         acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0.a[u], f0.b[t], first ? zero : acc[u][t], 0, 0, 0);
-        if (j < 8) read_piece(g, 1, j, f1);
-        if (t == 3) {
-          if (steady) issue_always(g + kAhead, u);
-          else issue_one(g + kAhead, u, more);
-        }
+        if (j < 6) read_piece(g, 1, j, f1);
+        if ((j + 1) % (16 / kLoads) == 0 && (j + 1) / (16 / kLoads) <= kLoads / 2)
+          issue_one(g + kAhead, (j + 1) / (16 / kLoads) - 1, steady, more);
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < 6; ++j) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-      // The half's last eight MFMAs stay before the barrier (left alone, the
-      // compiler sinks seven of them past it), so the matrix pipe has work
-      // queued while the wave waits for its reads and for the other waves.
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      // The half's last MFMAs stay before the barrier, so the matrix pipe has
+      // work queued while the wave waits for its reads and for the other waves.
       __builtin_amdgcn_sched_barrier(0);
-      if (steady) {
-        wait_loads<kLoads + kLoads / 2>();
-      } else {
-        const int after = (g + 2 < total ? kLoads : 0) + (more ? kLoads / 2 : 0);
-        if (after == 0) wait_loads<0>();
-        else if (after == kLoads / 2) wait_loads<kLoads / 2>();
-        else if (after == kLoads) wait_loads<kLoads>();
-        else wait_loads<kLoads + kLoads / 2>();
-      }
+      if (steady) wait_loads<kLoads + kLoads / 2>();
+      else wait_slices<kLoads>(g + 2 < total ? 1 : 0, more != 0);
       barrier();
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int u = j >> 2, t = j & 3;
+      for (int j = 0; j < 8; ++j) {
+        const int u = j >> 1, t = j & 1;
         acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1.a[u], f1.b[t], acc[u][t], 0, 0, 0);
-        if (j < 8) read_piece(g + 1, 0, j, f0);
-        if (t == 3) {
-          if (steady) issue_always(g + kAhead, kLoads / 2 + u);
-          else issue_one(g + kAhead, kLoads / 2 + u, more);
-        }
+        if (j < 6) read_piece(g + 1, 0, j, f0);
+        if ((j + 1) % (16 / kLoads) == 0 && (j + 1) / (16 / kLoads) <= kLoads / 2)
+          issue_one(g + kAhead, kLoads / 2 + (j + 1) / (16 / kLoads) - 1, steady, more);
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < 6; ++j) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
       if (more) advance();
       ++g;
     };
@@ -747,7 +752,7 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
       for (int kt = 1; kt < nk; ++kt) slice(false, false);
     }
     const int h0 = h_first + step * h_stride;
-    epi(acc, h0, min(h_limit, h0 + 256));
+    epi(acc, h0, min(h_limit, h0 + kRows));
   }
 }
 
@@ -756,27 +761,28 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
 // Sampled group maxima with the ring core (the same scores as the filter
 // kernel): block (tile, y) runs samples y * spb .. of the sample list,
 // sample s being step s * sample_every; every sampled step is whole.
-__global__ void __launch_bounds__(kThreads, 1) threshold_sample_ring_kernel(
+template <int WQ>
+__global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) threshold_sample_ring_kernel(
     EmbView queries, int Q, EmbView hist, int N, int d,
     int sample_every, int n_samples, int spb, float* __restrict__ gm) {
-  __shared__ __align__(16) char lds[ring::kStages * ring::kStageBytes];
-  const int q0 = blockIdx.x * ring::kBQ;
+  using S = ring::Shape<WQ>;
+  __shared__ __align__(16) char lds[S::kStages * S::kStageBytes];
+  const int q0 = blockIdx.x * S::kBQ;
   const int s0 = blockIdx.y * spb;
   const int n_steps = min(spb, n_samples - s0);
   const int lane = (int)lane_id();
   const int w = threadIdx.x / kWave;
-  const int wh = w >> 1, wq = w & 1;
+  const int wh = w / WQ, wq = w % WQ;
   const int l32 = lane & 31, half = lane >> 5;
   const int stride = sample_every * kStepRows;
   // Sampled steps are whole (256 rows inside the store): no row masking.
-  auto epi = [&](floatx16 (&acc)[4][4], int h0, int) {
+  auto epi = [&](floatx16 (&acc)[4][2], int h0, int) {
     const int s = h0 / stride;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int q = q0 + 128 * wq + 32 * t + l32;
+    for (int t = 0; t < 2; ++t) {
+      const int q = q0 + 64 * wq + 32 * t + l32;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        ring::pin(acc[u][t]);
         float m = acc[u][t][0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) m = fmaxf(m, acc[u][t][v]);
@@ -784,23 +790,21 @@ __global__ void __launch_bounds__(kThreads, 1) threshold_sample_ring_kernel(
       }
     }
   };
-  ring::sweep(hist, N, s0 * stride, stride, n_steps, N, queries, Q, q0, d, lds, epi);
+  ring::sweep<WQ>(hist, N, s0 * stride, stride, n_steps, N, queries, Q, q0, d, lds, epi);
 }
 
 // Filter kernel: every score >= theta0[q] is written as a key to the
 // segment [q][chunk][0..seg_cap) (position from an LDS counter); the true
 // count goes to seg_count[q][chunk] even when the segment overflows.
-__global__ void __launch_bounds__(kThreads, 1) sim_filter_kernel(
+template <int WQ>
+__global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kernel(
     EmbView queries, int Q, EmbView hist, int N, int d,
     int chunk_rows, int n_chunks, int q_tiles, int q_groups, const float* __restrict__ theta0,
     int seg_cap, uint64_t* __restrict__ seg, int* __restrict__ seg_count, uint32_t* __restrict__ flag_word) {
-  __shared__ __align__(16) char lds[ring::kStages * ring::kStageBytes];
+  using S = ring::Shape<WQ>;
+  __shared__ __align__(16) char lds[S::kStages * S::kStageBytes];
   if (blockIdx.x == 0 && threadIdx.x == 0) *flag_word = 0u;     // set again by the select if it flags a query
-  __shared__ int cnt[ring::kBQ];
-  // Per-lane rows for reading survivors back by a lane-varying index (16
-  // scores each, padded to 80 bytes so that the 16-byte writes of 16 lanes
-  // fall on distinct banks).
-  __shared__ __align__(16) float stage_rows[4][kWave][20];
+  __shared__ int cnt[S::kBQ];
   int qt, chunk;
   const int b = blockIdx.x;
   if (q_groups > 0) {
@@ -823,22 +827,21 @@ __global__ void __launch_bounds__(kThreads, 1) sim_filter_kernel(
   const int tid = threadIdx.x;
   const int lane = (int)lane_id();
   const int w = tid / kWave;
-  const int wh = w >> 1, wq = w & 1;
+  const int wh = w / WQ, wq = w % WQ;
   const int l32 = lane & 31, half = lane >> 5;
-  const int q0 = qt * ring::kBQ;
+  const int q0 = qt * S::kBQ;
   const int h_begin = chunk * chunk_rows;
   const int h_end = min(N, h_begin + chunk_rows);
-  cnt[tid] = 0;
-  float thr[4];
+  if (tid < S::kBQ) cnt[tid] = 0;
+  float thr[2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int q = q0 + 128 * wq + 32 * t + l32;
+  for (int t = 0; t < 2; ++t) {
+    const int q = q0 + 64 * wq + 32 * t + l32;
     thr[t] = q < Q ? float_below(theta0 ? theta0[q] : -__builtin_inff()) : __builtin_inff();
   }
   // Score acc[u][t][v] of this lane is row h0 + 128 wh + 4 half + r(i) for
   // bit i = 16 u + v, r(i) = 32 (i / 16) + 8 ((i / 4) % 4) + i % 4.
-  float* row = &stage_rows[w][lane][0];
-  auto epi = [&](floatx16 (&acc)[4][4], int h0, int step_end) {
+  auto epi = [&](floatx16 (&acc)[4][2], int h0, int step_end) {
     const int lim = step_end - h0 - 128 * wh - 4 * half;     // r(i) < lim: row inside the step
     const int hl = h0 + 128 * wh + 4 * half;
     // Rows inside the step: all of them but in a sweep's last, partial step,
@@ -850,17 +853,38 @@ __global__ void __launch_bounds__(kThreads, 1) sim_filter_kernel(
       const int n_in = 4 * (c >> 3) + min(c & 7, 4);
       in_step = n_in >= 64 ? ~0ull : (1ull << n_in) - 1ull;
     }
+    // The value of bit f (0..15) of a tile: a select tree on the bits of f, as
+    // bitwise selects under all-ones / all-zeros masks (one v_bfi each). The
+    // masks are opaque to the compiler, which would otherwise fold the tree
+    // into a dynamically indexed array and send it through memory.
+    auto pick = [](const floatx16& tv, int f) {
+      uint32_t sel[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        sel[k] = 0u - (uint32_t)((f >> k) & 1);
+        asm volatile("" : "+v"(sel[k]));
+      }
+      auto bfi = [](uint32_t mask, uint32_t hi, uint32_t lo) { return (hi & mask) | (lo & ~mask); };
+      uint32_t a[8], b4[4], c[2];
+#pragma unroll
+      for (int v = 0; v < 8; ++v) a[v] = bfi(sel[0], __float_as_uint(tv[2 * v + 1]), __float_as_uint(tv[2 * v]));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) b4[v] = bfi(sel[1], a[2 * v + 1], a[2 * v]);
+#pragma unroll
+      for (int v = 0; v < 2; ++v) c[v] = bfi(sel[2], b4[2 * v + 1], b4[2 * v]);
+      return __uint_as_float(bfi(sel[3], c[1], c[0]));
+    };
     // Column t's survivors are written one column later, so that its LDS
     // atomic (the segment position) is in flight during the next column's
-    // compare. Per tile, the lane's first survivor is picked from the
-    // registers by a select tree on its index; a lane with two or more
-    // survivors in one tile (rare) takes the rest through its LDS row.
+    // compare. Per tile, a lane's first survivor is picked from the registers;
+    // a lane with two or more survivors in one tile (rare) picks the rest one
+    // by one.
     uint64_t m_prev = 0;
     int base_prev = 0;
     uint32_t f_prev = 0;
     float fv_prev[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     auto write_column = [&](int t, uint64_t m, int base, uint32_t fidx, const float (&fv)[4]) {
-      const int ql = 128 * wq + 32 * t + l32;
+      const int ql = 64 * wq + 32 * t + l32;
       uint64_t* dst = seg + ((size_t)(q0 + ql) * n_chunks + chunk) * seg_cap;
       uint64_t rest = 0;
 #pragma unroll
@@ -878,24 +902,20 @@ __global__ void __launch_bounds__(kThreads, 1) sim_filter_kernel(
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         uint32_t bits = (uint32_t)(rest >> (16 * u)) & 0xffffu;
-        if (!__any(bits != 0)) continue;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          *reinterpret_cast<float4*>(row + 4 * c) =
-              make_float4(acc[u][t][4 * c], acc[u][t][4 * c + 1], acc[u][t][4 * c + 2], acc[u][t][4 * c + 3]);
-        while (bits) {
-          const int v = __ffs(bits) - 1;
-          bits &= bits - 1;
-          const int i = 16 * u + v;
-          const int j = base + __popcll(m & ((1ull << i) - 1ull));
-          if (j < seg_cap) dst[j] = make_key(row[v], (uint32_t)(hl + 32 * u + 8 * (v >> 2) + (v & 3)));
+        while (__any(bits != 0)) {
+          const int v = (__ffs(bits) - 1) & 15;
+          const float sv = pick(acc[u][t], v);
+          if (bits != 0) {
+            const int i = 16 * u + v;
+            const int j = base + __popcll(m & ((1ull << i) - 1ull));
+            if (j < seg_cap) dst[j] = make_key(sv, (uint32_t)(hl + 32 * u + 8 * (v >> 2) + (v & 3)));
+            bits &= bits - 1u;
+          }
         }
       }
     };
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) ring::pin(acc[u][t]);
+    for (int t = 0; t < 2; ++t) {
       // Bit v of mk[u] = [acc[u][t][v] > thr]: the sign of thr - s, shifted
       // in with one funnel shift (no compare, so no serialisation on VCC).
       // For finite scores the sign of the rounded difference is exact: -0
@@ -905,44 +925,21 @@ __global__ void __launch_bounds__(kThreads, 1) sim_filter_kernel(
       uint32_t fidx = 0;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        // The tile is copied out whole before use, so the 16 register reads
-        // and differences are independent rather than one chain through a
-        // single temporary.
-        floatx16 tv = acc[u][t];
-        asm volatile("" : "+v"(tv));
         uint32_t sg[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sg[v] = __float_as_uint(thr[t] - tv[v]);
+        for (int v = 0; v < 16; ++v) sg[v] = __float_as_uint(thr[t] - acc[u][t][v]);
 #pragma unroll
         for (int v = 15; v >= 0; --v) mk[u] = __builtin_amdgcn_alignbit(mk[u], sg[v], 31);
         mk[u] &= (uint32_t)(in_step >> (16 * u)) & 0xffffu;
         if (__any(mk[u] != 0)) {
-          // Select tree on the bits of f, as bitwise selects under all-ones
-          // / all-zeros masks (one v_bfi each). The masks are opaque to the
-          // compiler, which would otherwise fold the tree into a dynamically
-          // indexed array and send it through memory.
           const int f = (__ffs(mk[u]) - 1) & 15;
-          uint32_t sel[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            sel[k] = 0u - (uint32_t)((f >> k) & 1);
-            asm volatile("" : "+v"(sel[k]));
-          }
-          auto pick = [](uint32_t mask, uint32_t hi, uint32_t lo) { return (hi & mask) | (lo & ~mask); };
-          uint32_t a[8], b[4], c[2];
-#pragma unroll
-          for (int v = 0; v < 8; ++v) a[v] = pick(sel[0], __float_as_uint(tv[2 * v + 1]), __float_as_uint(tv[2 * v]));
-#pragma unroll
-          for (int v = 0; v < 4; ++v) b[v] = pick(sel[1], a[2 * v + 1], a[2 * v]);
-#pragma unroll
-          for (int v = 0; v < 2; ++v) c[v] = pick(sel[2], b[2 * v + 1], b[2 * v]);
-          fv[u] = __uint_as_float(pick(sel[3], c[1], c[0]));
+          fv[u] = pick(acc[u][t], f);
           fidx |= (uint32_t)f << (4 * u);
         }
       }
       const uint32_t lo = mk[0] | (mk[1] << 16), hi = mk[2] | (mk[3] << 16);
       const uint64_t m = ((uint64_t)hi << 32) | lo;
-      const int ql = 128 * wq + 32 * t + l32;
+      const int ql = 64 * wq + 32 * t + l32;
       const int base = m != 0 ? atomicAdd(&cnt[ql], __popcll(m)) : 0;
       if (t > 0 && __any(m_prev != 0)) write_column(t - 1, m_prev, base_prev, f_prev, fv_prev);
       m_prev = m;
@@ -951,12 +948,12 @@ __global__ void __launch_bounds__(kThreads, 1) sim_filter_kernel(
 #pragma unroll
       for (int u = 0; u < 4; ++u) fv_prev[u] = fv[u];
     }
-    if (__any(m_prev != 0)) write_column(3, m_prev, base_prev, f_prev, fv_prev);
+    if (__any(m_prev != 0)) write_column(1, m_prev, base_prev, f_prev, fv_prev);
   };
   const int n_steps = (h_end - h_begin + kStepRows - 1) / kStepRows;
-  ring::sweep(hist, N, h_begin, kStepRows, n_steps, h_end, queries, Q, q0, d, lds, epi);
+  ring::sweep<WQ>(hist, N, h_begin, kStepRows, n_steps, h_end, queries, Q, q0, d, lds, epi);
   __syncthreads();
-  if (q0 + tid < Q) seg_count[(size_t)(q0 + tid) * n_chunks + chunk] = cnt[tid];
+  if (tid < S::kBQ && q0 + tid < Q) seg_count[(size_t)(q0 + tid) * n_chunks + chunk] = cnt[tid];
 }
 
 // Select kernel: one wavefront per query, four queries per workgroup. The
@@ -1093,8 +1090,8 @@ hipError_t launch_theta(EmbView queries, int Q, EmbView hist, int N, int d, int 
     } else if (sampler == Sampler::ring) {
       const int spb = p.f_spb;
       const dim3 rgrid(q_tiles, (p.n_samples + spb - 1) / spb);
-      hipLaunchKernelGGL(threshold_sample_ring_kernel, rgrid, dim3(kThreads), 0, stream, queries, Q,
-                         hist, N, d, p.sample_every, p.n_samples, spb, gm);
+      hipLaunchKernelGGL(threshold_sample_ring_kernel<4>, rgrid, dim3(ring::Shape<4>::kThreads), 0, stream,
+                         queries, Q, hist, N, d, p.sample_every, p.n_samples, spb, gm);
     } else if (p.list_len == 128) {              // the same core as sim_topk_kernel<2, 128>
       hipLaunchKernelGGL((threshold_sample_kernel<2>), grid, dim3(kThreads), 0, stream, queries, Q,
                          hist, N, d, p.sample_every, p.n_samples, gm);
@@ -1178,7 +1175,7 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
   // Filtered path (k <= 64): 256-query tiles, segments of 8192 keys per query in all.
   p.fast = L == 64;
   if (p.fast) {
-    p.f_q_tiles = (Q + ring::kBQ - 1) / ring::kBQ;
+    p.f_q_tiles = (Q + ring::Shape<4>::kBQ - 1) / ring::Shape<4>::kBQ;
     // samples per sampling block: about one block per CU
     p.f_spb = 1;
     while (p.n_samples > 0 && (long)p.f_q_tiles * ((p.n_samples + 2 * p.f_spb - 1) / (2 * p.f_spb)) >= 256)
@@ -1192,7 +1189,7 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     p.f_q_groups = 0;
     for (int a = 1; a <= 8; a *= 2) {
       if (p.f_q_tiles % a != 0 || p.f_n_chunks % (8 / a) != 0) continue;
-      if ((size_t)(p.f_q_tiles / a) * ring::kBQ * d * 2 <= ((size_t)3 << 20)) { p.f_q_groups = a; break; }
+      if ((size_t)(p.f_q_tiles / a) * ring::Shape<4>::kBQ * d * 2 <= ((size_t)3 << 20)) { p.f_q_groups = a; break; }
     }
     p.seg_cap = 1;                                   // power of two, n_chunks * cap <= 8192
     while (p.seg_cap * 2 * p.f_n_chunks <= 8192) p.seg_cap *= 2;
@@ -1251,7 +1248,7 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     const Flagged fl{reinterpret_cast<int*>(ws + p.off_flags), reinterpret_cast<uint32_t*>(ws + p.off_flag_word)};
     {
       LaunchScope scope("sim_topk", stream);
-      hipLaunchKernelGGL(sim_filter_kernel, dim3(p.f_q_tiles * p.f_n_chunks), dim3(kThreads), 0, stream,
+      hipLaunchKernelGGL(sim_filter_kernel<4>, dim3(p.f_q_tiles * p.f_n_chunks), dim3(ring::Shape<4>::kThreads), 0, stream,
                          queries, Q, hist, N, d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_groups,
                          p.n_samples > 0 ? theta0 : nullptr, p.seg_cap, seg, segcnt, fl.word);
     }
