@@ -222,127 +222,6 @@ __global__ void __launch_bounds__(kThreads) sim_stream_kernel(
   }
 }
 
-// The list of a wave's S * 64 best keys, descending over positions
-// p = 64 s + lane (register s, lane). Half-cleaners sort a bitonic list.
-template <int S>
-__device__ __forceinline__ void list_clean(uint64_t (&lv)[S]) {
-#pragma unroll
-  for (int st = S / 2; st >= 1; st >>= 1)
-#pragma unroll
-    for (int s = 0; s < S; ++s)
-      if ((s & st) == 0) {
-        const uint64_t x = lv[s], y = lv[s + st];
-        lv[s] = x > y ? x : y;
-        lv[s + st] = x > y ? y : x;
-      }
-#pragma unroll
-  for (int s = 0; s < S; ++s)
-#pragma unroll
-    for (int stride = 32; stride > 0; stride >>= 1) lv[s] = cx_lanes(lv[s], stride, true);
-}
-// Fold 64 keys (one per lane, any order) into the list: sorted ascending
-// they are the reversed tail of a descending list, so max(A_p, B_(KL-1-p))
-// touches the last register only and leaves a bitonic list.
-template <int S>
-__device__ __forceinline__ void list_fold(uint64_t (&lv)[S], uint64_t key) {
-  const uint64_t asc = wave_sort64(key, false);
-  lv[S - 1] = lv[S - 1] > asc ? lv[S - 1] : asc;
-  list_clean<S>(lv);
-}
-
-// One workgroup of 16 waves per query; a query with more candidates than the
-// array holds, or fewer than min(k, N), is flagged for the exact path and
-// left untouched. Wave w takes candidates
-// 64 w + lane + 1024 i; keys that beat its list's last key are gathered in
-// LDS and folded 64 at a time. The 16 lists are then merged pairwise in a
-// tree, and wave 0 writes the first k.
-template <int S>
-__global__ void __launch_bounds__(1024) select_few_kernel(const uint64_t* __restrict__ cand,
-                                                          const int* __restrict__ cand_count, int cap, int k,
-                                                          int need, int* __restrict__ flags,
-                                                          uint32_t* __restrict__ flag_word,
-                                                          int32_t* __restrict__ ids, float* __restrict__ sims) {
-  constexpr int KL = 64 * S;
-  constexpr int W = 16;
-  __shared__ uint64_t lists[W][KL];
-  __shared__ uint64_t pend[W][2 * kWave];
-  const int q = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int lane = (int)lane_id();
-  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int n = cand_count[q];
-  if (n > cap || n < need) {                         // need = min(k, N)
-    if (tid == 0) {
-      flags[q] = 1;
-      *flag_word = 1u;
-    }
-    return;
-  }
-  if (tid == 0) flags[q] = 0;
-  const uint64_t* src = cand + (size_t)q * cap;
-  uint64_t lv[S];
-#pragma unroll
-  for (int s = 0; s < S; ++s) lv[s] = kPadKey;
-  uint64_t* buf = pend[w];
-  int n_buf = 0;
-  auto take = [&](uint64_t cur) {
-    const bool keep = cur > lane_value_u64(lv[S - 1], kWave - 1);
-    const uint64_t mask = __ballot(keep);
-    if (mask == 0) return;
-    const int pos = n_buf + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-    if (keep) buf[pos] = cur;
-    n_buf += __popcll(mask);
-    __builtin_amdgcn_wave_barrier();
-    if (n_buf >= kWave) {
-      list_fold<S>(lv, buf[lane]);
-      n_buf -= kWave;
-      const uint64_t rest = lane < n_buf ? buf[kWave + lane] : kPadKey;
-      __builtin_amdgcn_wave_barrier();
-      if (lane < n_buf) buf[lane] = rest;
-      __builtin_amdgcn_wave_barrier();
-    }
-  };
-  constexpr int kPre = 4;                            // loads in flight per wave
-  for (int b0 = w * kWave; b0 < n; b0 += kPre * W * kWave) {
-    uint64_t cur[kPre];
-#pragma unroll
-    for (int j = 0; j < kPre; ++j) {
-      const int e = b0 + j * W * kWave + lane;
-      cur[j] = e < n ? src[e] : kPadKey;
-    }
-#pragma unroll
-    for (int j = 0; j < kPre; ++j) take(cur[j]);
-  }
-  if (n_buf > 0) list_fold<S>(lv, lane < n_buf ? buf[lane] : kPadKey);
-#pragma unroll
-  for (int s = 0; s < S; ++s) lists[w][64 * s + lane] = lv[s];
-  __syncthreads();
-  for (int h = 1; h < W; h <<= 1) {
-    if ((w & (2 * h - 1)) == 0) {
-      // C_p = max(A_p, B_(KL-1-p)) is bitonic and holds the KL best of both.
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const uint64_t o = lists[w + h][64 * (S - 1 - s) + (kWave - 1 - lane)];
-        lv[s] = lv[s] > o ? lv[s] : o;
-      }
-      list_clean<S>(lv);
-#pragma unroll
-      for (int s = 0; s < S; ++s) lists[w][64 * s + lane] = lv[s];
-    }
-    __syncthreads();
-  }
-  if (w != 0) return;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const int p = 64 * s + lane;
-    if (p < k) {
-      ids[(size_t)q * k + p] = lv[s] == kPadKey ? -1 : key_id(lv[s]);
-      sims[(size_t)q * k + p] = lv[s] == kPadKey ? -__builtin_inff() : key_sim(lv[s]);
-    }
-  }
-}
-
 }  // namespace
 
 hipError_t launch_stream_sample(EmbView queries, int Q, EmbView hist, int N, int d, int sample_every,
@@ -357,28 +236,16 @@ hipError_t launch_stream_sample(EmbView queries, int Q, EmbView hist, int N, int
   return hipGetLastError();
 }
 
-hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int k, int chunk_rows,
-                                const float* theta0, int cap, uint64_t* cand, int* cand_count, Flagged fl,
-                                int32_t* ids, float* sims, hipStream_t stream) {
-  if (Q <= 0 || Q > kStreamMaxQ || d % 32 != 0 || d > kStreamMaxD || k > 256 || N <= 0 || chunk_rows <= 0)
+hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int chunk_rows,
+                                const float* theta0, int cap, uint64_t* cand, int* cand_count, uint32_t* flag_word,
+                                hipStream_t stream) {
+  if (Q <= 0 || Q > kStreamMaxQ || d % 32 != 0 || d > kStreamMaxD || N <= 0 || chunk_rows <= 0)
     return hipErrorInvalidValue;
-  {
-    LaunchScope scope("sim_topk", stream);
-    const int blocks = (N + chunk_rows - 1) / chunk_rows;
-    const size_t lds = (size_t)(d / 32) * kWave * sizeof(uint4);   // sized to d: more workgroups per CU
-    hipLaunchKernelGGL(sim_stream_kernel, dim3(blocks), dim3(kThreads), lds, stream, queries, Q, hist, N, d,
-                       chunk_rows, theta0, cap, cand, cand_count, fl.word);
-  }
-  LaunchScope scope("topk_select", stream);
-  if (k <= 64)
-    hipLaunchKernelGGL((select_few_kernel<1>), dim3(Q), dim3(1024), 0, stream, cand, cand_count, cap, k,
-                       min(k, N), fl.flags, fl.word, ids, sims);
-  else if (k <= 128)
-    hipLaunchKernelGGL((select_few_kernel<2>), dim3(Q), dim3(1024), 0, stream, cand, cand_count, cap, k,
-                       min(k, N), fl.flags, fl.word, ids, sims);
-  else
-    hipLaunchKernelGGL((select_few_kernel<4>), dim3(Q), dim3(1024), 0, stream, cand, cand_count, cap, k,
-                       min(k, N), fl.flags, fl.word, ids, sims);
+  LaunchScope scope("sim_topk", stream);
+  const int blocks = (N + chunk_rows - 1) / chunk_rows;
+  const size_t lds = (size_t)(d / 32) * kWave * sizeof(uint4);   // sized to d: more workgroups per CU
+  hipLaunchKernelGGL(sim_stream_kernel, dim3(blocks), dim3(kThreads), lds, stream, queries, Q, hist, N, d,
+                     chunk_rows, theta0, cap, cand, cand_count, flag_word);
   return hipGetLastError();
 }
 

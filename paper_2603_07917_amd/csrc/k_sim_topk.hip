@@ -26,6 +26,7 @@
 //   between when a step brings more), and the wave owning the query folds
 //   full buffers into the query's descending list with a bitonic merge. The
 //   lists end in the partial buffer [Q][chunks][KL].
+#include <algorithm>
 #include <atomic>
 
 #include "sage_device.hpp"
@@ -421,22 +422,6 @@ __global__ void __launch_bounds__(kThreads, 1) sim_topk_kernel(
 
 
 
-// Descending order of a bitonic sequence held one key per lane (half-cleaners).
-__device__ __forceinline__ uint64_t wave_bitonic_clean_desc64(uint64_t v) {
-#pragma unroll
-  for (int stride = 32; stride > 0; stride >>= 1) v = cx_lanes(v, stride, true);
-  return v;
-}
-
-// Folds 64 keys (one per lane, any order) into the wave's descending list of
-// its 64 largest keys: skipped when no key beats the list's last one,
-// otherwise a wave bitonic sort, C_i = max(A_i, B_{63-i}) and half-cleaners.
-__device__ __forceinline__ uint64_t fold_group(uint64_t list, uint64_t key) {
-  if (!__any(key > lane_value_u64(list, kWave - 1))) return list;
-  const uint64_t asc = wave_sort64(key, false);       // B_{63-i} of the descending order
-  return wave_bitonic_clean_desc64(list > asc ? list : asc);
-}
-
 // theta0: the k-th largest of a query's m (<= 512 * 16) group maxima, held
 // in registers as monotone key bits (VPL per lane; past m: key 0, below every
 // real score). theta0 is the largest key T with at least k keys >= T, built
@@ -532,7 +517,9 @@ struct Shape {
   static constexpr int kWaves = 2 * WQ;
   static constexpr int kThreads = kWave * kWaves;
   static constexpr int kBQ = 64 * WQ;            // queries per tile
-  static constexpr int kStages = 4;              // a power of two (stage = g & (kStages - 1))
+  // 256 queries: four stages (128 KiB), one workgroup of eight waves per CU.
+  // 128 queries: three stages (72 KiB), two workgroups of four waves per CU.
+  static constexpr int kStages = WQ == 4 ? 4 : 3;
   static constexpr int kStageBytes = (kRows + kBQ) * kKT * 2;
   static constexpr int kHL = kRows / 16 / kWaves;   // history loads per wave and slice
   static constexpr int kQL = kBQ / 16 / kWaves;     // query loads per wave and slice
@@ -565,8 +552,8 @@ __device__ __forceinline__ void load_to_lds_if(const void* base, uint32_t off, u
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-// Waits until at most n slices and, with `half`, half a slice of this wave's
-// loads are in flight (n < kAhead - 1 + 1).
+// Waits until at most n (0 to 2) slices of this wave's loads are in flight,
+// and with `half` half a slice more (then n is 0 or 1).
 template <int kLoads>
 __device__ __forceinline__ void wait_slices(int n, bool half) {
   if (half) {
@@ -602,8 +589,9 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
                                       Epi& epi) {
   using S = Shape<WQ>;
   constexpr int kLoads = S::kLoads, kHL = S::kHL, kQL = S::kQL, kAhead = S::kAhead;
-  constexpr int kStageMask = S::kStages - 1, kStageBytes = S::kStageBytes;
-  static_assert(kLoads % 2 == 0 && kAhead == 3, "the waits below count half slices, at most two whole ones");
+  constexpr int kGap = 16 / kLoads;             // MFMAs between two loads of a half slice
+  constexpr int kStages = S::kStages, kStageBytes = S::kStageBytes;
+  static_assert(kLoads % 2 == 0 && (kAhead == 2 || kAhead == 3), "the waits below: half slices, at most two whole ones");
   const int lane = (int)lane_id();
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int wh = w / WQ, wq = w % WQ;
@@ -634,13 +622,12 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
 #pragma unroll
     for (int i = 0; i < kHL; ++i) hoff[i] = (uint32_t)min(rh + 16 * i, last) * h_row_bytes + cb;
   };
-  // Load i of slice g into its stage: history pieces first, then queries.
+  // Load i of the next slice into a stage: history pieces first, then queries.
   const uint32_t h_lds = lds0 + (uint32_t)(w * kHL * 1024);
   const uint32_t q_lds = lds0 + (uint32_t)((kRows / 16 + w * kQL) * 1024);
-  auto issue_one = [&](int g, int i, bool always, int enabled) {
-    const uint32_t stage = (uint32_t)((g & kStageMask) * kStageBytes);
+  auto issue_one = [&](int stage, int i, bool always, int enabled) {
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-        stage + (i < kHL ? h_lds + (uint32_t)i * 1024u : q_lds + (uint32_t)(i - kHL) * 1024u));
+        (uint32_t)(stage * kStageBytes) + (i < kHL ? h_lds + (uint32_t)i * 1024u : q_lds + (uint32_t)(i - kHL) * 1024u));
     const char* src = i < kHL ? hsrc : qsrc;
     const uint32_t off = i < kHL ? hoff[i < kHL ? i : 0] : qoff[i < kHL ? 0 : i - kHL];
     if (always) load_to_lds(src, off, m0);
@@ -667,8 +654,8 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
     b_off[kk] = (uint32_t)((kRows + 64 * wq + l32) * 64) + pos;
   }
   // Piece p of the fragments in the order of use: B0, A0, B1, A1, A2, A3.
-  auto read_piece = [&](int g, int kk, int p, Frags& f) {
-    const char* stage = lds + (g & kStageMask) * kStageBytes;
+  auto read_piece = [&](int st, int kk, int p, Frags& f) {
+    const char* stage = lds + st * kStageBytes;
     if (p == 0) f.b[0] = *reinterpret_cast<const bf16x8*>(stage + b_off[kk]);
     else if (p == 2) f.b[1] = *reinterpret_cast<const bf16x8*>(stage + b_off[kk] + 2048);
     else {
@@ -689,7 +676,7 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
   Frags f0, f1;
 #pragma unroll
   for (int p = 0; p < 6; ++p) read_piece(0, 0, p, f0);
-  int g = 0;
+  int g = 0, st = 0;                            // slice and its stage (g % kStages)
   for (int step = 0; step < n_steps; ++step) {
     floatx16 acc[4][2];
     // One slice: f0 holds its first 16 columns on entry; on exit f0 holds the
@@ -704,14 +691,15 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
     //    evenly busy.
     auto slice = [&](bool first, bool steady) {
       const int more = steady ? 1 : (g + kAhead < total);
+      const int st_load = st == 0 ? kStages - 1 : st - 1;         // stage of slice g + kAhead
+      const int st_next = st == kStages - 1 ? 0 : st + 1;         // stage of slice g + 1
       const floatx16 zero = {};
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int u = j >> 1, t = j & 1;
         acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0.a[u], f0.b[t], first ? zero : acc[u][t], 0, 0, 0);
-        if (j < 6) read_piece(g, 1, j, f1);
-        if ((j + 1) % (16 / kLoads) == 0 && (j + 1) / (16 / kLoads) <= kLoads / 2)
-          issue_one(g + kAhead, (j + 1) / (16 / kLoads) - 1, steady, more);
+        if (j < 6) read_piece(st, 1, j, f1);
+        if ((j + 1) % kGap == 0 && (j + 1) / kGap <= kLoads / 2) issue_one(st_load, (j + 1) / kGap - 1, steady, more);
       }
 #pragma unroll
       for (int j = 0; j < 6; ++j) {
@@ -722,16 +710,16 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
       // The half's last MFMAs stay before the barrier, so the matrix pipe has
       // work queued while the wave waits for its reads and for the other waves.
       __builtin_amdgcn_sched_barrier(0);
-      if (steady) wait_loads<kLoads + kLoads / 2>();
-      else wait_slices<kLoads>(g + 2 < total ? 1 : 0, more != 0);
+      if (steady) wait_loads<(kAhead - 2) * kLoads + kLoads / 2>();
+      else wait_slices<kLoads>(min(kAhead - 2, max(0, total - 2 - g)), more != 0);
       barrier();
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int u = j >> 1, t = j & 1;
         acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1.a[u], f1.b[t], acc[u][t], 0, 0, 0);
-        if (j < 6) read_piece(g + 1, 0, j, f0);
-        if ((j + 1) % (16 / kLoads) == 0 && (j + 1) / (16 / kLoads) <= kLoads / 2)
-          issue_one(g + kAhead, kLoads / 2 + (j + 1) / (16 / kLoads) - 1, steady, more);
+        if (j < 6) read_piece(st_next, 0, j, f0);
+        if ((j + 1) % kGap == 0 && (j + 1) / kGap <= kLoads / 2)
+          issue_one(st_load, kLoads / 2 + (j + 1) / kGap - 1, steady, more);
       }
 #pragma unroll
       for (int j = 0; j < 6; ++j) {
@@ -741,6 +729,7 @@ __device__ __forceinline__ void sweep(const EmbView& hist, int N, int h_first, i
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
       if (more) advance();
       ++g;
+      st = st_next;
     };
     // Every slice of a step before the last has its look-ahead slice inside
     // the sweep (when a step has at least kAhead slices): no conditions.
@@ -795,35 +784,30 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) threshold_sample
 
 // Filter kernel: every score >= theta0[q] is written as a key to the
 // segment [q][chunk][0..seg_cap) (position from an LDS counter); the true
-// count goes to seg_count[q][chunk] even when the segment overflows.
+// count goes to seg_count[q][chunk] even when the segment overflows. With a
+// spill array (many small segments) the keys past a full segment go to the
+// query's spill[q][0..spill_cap), one device atomic each: a chunk whose rows
+// are alike fills its segment without sending the query to the exact path.
 template <int WQ>
 __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kernel(
     EmbView queries, int Q, EmbView hist, int N, int d,
-    int chunk_rows, int n_chunks, int q_tiles, int q_groups, const float* __restrict__ theta0,
-    int seg_cap, uint64_t* __restrict__ seg, int* __restrict__ seg_count, uint32_t* __restrict__ flag_word) {
+    int chunk_rows, int n_chunks, int q_tiles, int q_sub, const float* __restrict__ theta0,
+    int seg_cap, uint64_t* __restrict__ seg, int* __restrict__ seg_count, int spill_cap,
+    uint64_t* __restrict__ spill, int* __restrict__ spill_count, uint32_t* __restrict__ flag_word) {
   using S = ring::Shape<WQ>;
   __shared__ __align__(16) char lds[S::kStages * S::kStageBytes];
   if (blockIdx.x == 0 && threadIdx.x == 0) *flag_word = 0u;     // set again by the select if it flags a query
   __shared__ int cnt[S::kBQ];
-  int qt, chunk;
-  const int b = blockIdx.x;
-  if (q_groups > 0) {
-    // Workgroup b runs on XCD b % 8. XCD x owns query-tile group x % q_groups
-    // and chunk group x / q_groups: its L2 keeps that group's query tiles
-    // resident while the chunks stream through.
-    const int x = b & 7, slot = b >> 3;
-    const int per_group = q_tiles / q_groups;
-    const int chunks_per_group = n_chunks / (8 / q_groups);
-    qt = (x % q_groups) * per_group + slot % per_group;
-    chunk = (x / q_groups) * chunks_per_group + slot / per_group;
-  } else if (n_chunks % 8 == 0) {
-    const int x = b & 7, slot = b >> 3;
-    chunk = x + 8 * (slot / q_tiles);
-    qt = slot % q_tiles;
-  } else {
-    chunk = b / q_tiles;
-    qt = b % q_tiles;
-  }
+  // Workgroup b runs on XCD b % 8. The (query tile, chunk) pairs are listed in
+  // blocks of q_sub tiles, chunk by chunk within a block, and XCD x takes the
+  // x-th eighth of the list: the tiles that it works on at a time stay in its
+  // L2 while the chunks stream through.
+  const int n_pairs = q_tiles * n_chunks;
+  const int pair = (int)(blockIdx.x & 7) * ((n_pairs + 7) / 8) + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= (n_pairs + 7) / 8 || pair >= n_pairs) return;
+  const int block = pair / (q_sub * n_chunks), r = pair % (q_sub * n_chunks);
+  const int in_block = min(q_sub, q_tiles - block * q_sub);
+  const int qt = block * q_sub + r % in_block, chunk = r / in_block;
   const int tid = threadIdx.x;
   const int lane = (int)lane_id();
   const int w = tid / kWave;
@@ -874,6 +858,27 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kerne
       for (int v = 0; v < 2; ++v) c[v] = bfi(sel[2], b4[2 * v + 1], b4[2 * v]);
       return __uint_as_float(bfi(sel[3], c[1], c[0]));
     };
+    // Survivors past their segment's capacity (rare), one device atomic each.
+    auto spill_column = [&](int t, uint64_t m, int base) {
+      const int q = q0 + 64 * wq + 32 * t + l32;                       // a lane with a survivor has q < Q
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        uint32_t bits = (uint32_t)(m >> (16 * u)) & 0xffffu;
+        while (__any(bits != 0)) {
+          const int v = (__ffs(bits) - 1) & 15;
+          const float sv = pick(acc[u][t], v);
+          if (bits != 0) {
+            const int i = 16 * u + v;
+            if (base + __popcll(m & ((1ull << i) - 1ull)) >= seg_cap) {
+              const int e = atomicAdd(&spill_count[q], 1);
+              if (e < spill_cap)
+                spill[(size_t)q * spill_cap + e] = make_key(sv, (uint32_t)(hl + 32 * u + 8 * (v >> 2) + (v & 3)));
+            }
+            bits &= bits - 1u;
+          }
+        }
+      }
+    };
     // Column t's survivors are written one column later, so that its LDS
     // atomic (the segment position) is in flight during the next column's
     // compare. Per tile, a lane's first survivor is picked from the registers;
@@ -898,6 +903,7 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kerne
           rest |= (uint64_t)(bits & (bits - 1u)) << (16 * u);
         }
       }
+      if (spill_cap > 0 && __any(m != 0 && base + __popcll(m) > seg_cap)) spill_column(t, m, base);
       if (!__any(rest != 0)) return;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -956,102 +962,6 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kerne
   if (tid < S::kBQ && q0 + tid < Q) seg_count[(size_t)(q0 + tid) * n_chunks + chunk] = cnt[tid];
 }
 
-// Select kernel: one wavefront per query, four queries per workgroup. The
-// wave reads the query's candidate keys straight from global memory (its
-// segments form one index range; kPre groups of 64 keys in flight at once)
-// and keeps its best 64 keys as a descending list across lanes: keys that
-// beat the list's last key are gathered in LDS, and each 64 of them are
-// sorted (wave bitonic sort) and folded in with C_i = max(A_i, B_{63-i}) and
-// six half-cleaner stages. One list per query means only the keys that beat
-// the query's running 64th are sorted (about k (1 + ln(n / k)) of n), not
-// those of four partial lists. A query with an overflowed segment, or with
-// fewer than min(k, N) candidates in all, is flagged for the exact fallback
-// and left untouched here. Waves work independently (no workgroup barrier).
-__global__ void __launch_bounds__(256) select_kernel(const uint64_t* __restrict__ seg,
-                                                     const int* __restrict__ seg_count, int Q, int n_chunks,
-                                                     int seg_cap, int k, int need, int* __restrict__ flags,
-                                                     uint32_t* __restrict__ flag_word,
-                                                     int32_t* __restrict__ ids, float* __restrict__ sims) {
-  __shared__ int off_s[4][kWave + 1];
-  __shared__ uint64_t pend[4][2 * kWave];
-  const int lane = (int)lane_id();
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int q = blockIdx.x * 4 + w;
-  if (q >= Q) return;
-  int* off = off_s[w];
-  // Segment c (one per lane; n_chunks <= 64) starts at off[c] of the range.
-  const int n = lane < n_chunks ? seg_count[(size_t)q * n_chunks + lane] : 0;
-  const int c = min(n, seg_cap);
-  int incl = c;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(incl, o, kWave);
-    if (lane >= o) incl += y;
-  }
-  off[lane] = incl - c;
-  if (lane == kWave - 1) off[kWave] = incl;
-  const int total = __shfl(incl, kWave - 1, kWave);
-  // Flag the query when a segment overflowed, or when fewer than min(k, N)
-  // keys beat theta0: the pre-pass scores are the filter's own, bit for
-  // bit, so the latter only follows from a raised threshold.
-  if (__any(n > seg_cap) || total < need) {
-    if (lane == 0) {
-      flags[q] = 1;
-      *flag_word = 1u;
-    }
-    return;
-  }
-  if (lane == 0) flags[q] = 0;
-  __builtin_amdgcn_wave_barrier();                    // off[] written before it is read
-  const uint64_t* src = seg + (size_t)q * n_chunks * seg_cap;
-  uint64_t* buf = pend[w];
-  uint64_t list = kPadKey;
-  int n_buf = 0;                                      // keys waiting in buf (wave-uniform, < 64)
-  auto take = [&](uint64_t cur) {
-    const uint64_t tail = lane_value_u64(list, kWave - 1);
-    const bool keep = cur > tail;
-    const uint64_t mask = __ballot(keep);
-    if (mask == 0) return;
-    const int pos = n_buf + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-    if (keep) buf[pos] = cur;
-    n_buf += __popcll(mask);
-    __builtin_amdgcn_wave_barrier();
-    if (n_buf >= kWave) {                             // fold 64, keep the rest (< 64) at the front
-      list = fold_group(list, buf[lane]);
-      n_buf -= kWave;
-      const uint64_t rest = lane < n_buf ? buf[kWave + lane] : kPadKey;
-      __builtin_amdgcn_wave_barrier();
-      if (lane < n_buf) buf[lane] = rest;
-      __builtin_amdgcn_wave_barrier();
-    }
-  };
-  constexpr int kPre = 8;
-  for (int e0 = 0; e0 < total; e0 += kWave * kPre) {
-    uint64_t cur[kPre];
-#pragma unroll
-    for (int j = 0; j < kPre; ++j) {
-      const int e = e0 + kWave * j + lane;
-      cur[j] = kPadKey;
-      if (e < total) {
-        int lo = 0, hi = n_chunks - 1;                // the last segment c with off[c] <= e
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (off[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        cur[j] = src[(size_t)lo * seg_cap + (e - off[lo])];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < kPre; ++j) take(cur[j]);
-  }
-  if (n_buf > 0) list = fold_group(list, lane < n_buf ? buf[lane] : kPadKey);
-  if (lane < k) {
-    ids[(size_t)q * k + lane] = list == kPadKey ? -1 : key_id(list);
-    sims[(size_t)q * k + lane] = list == kPadKey ? -__builtin_inff() : key_sim(list);
-  }
-}
-
 template <int NQT, int KL>
 hipError_t launch_lists(EmbView queries, int Q, EmbView hist, int N, int d, int k,
                         const SimTopkPlan& p, const float* theta0, const Flagged* only_flagged,
@@ -1090,8 +1000,12 @@ hipError_t launch_theta(EmbView queries, int Q, EmbView hist, int N, int d, int 
     } else if (sampler == Sampler::ring) {
       const int spb = p.f_spb;
       const dim3 rgrid(q_tiles, (p.n_samples + spb - 1) / spb);
-      hipLaunchKernelGGL(threshold_sample_ring_kernel<4>, rgrid, dim3(ring::Shape<4>::kThreads), 0, stream,
-                         queries, Q, hist, N, d, p.sample_every, p.n_samples, spb, gm);
+      if (p.f_tile == 128)
+        hipLaunchKernelGGL(threshold_sample_ring_kernel<2>, rgrid, dim3(ring::Shape<2>::kThreads), 0, stream,
+                           queries, Q, hist, N, d, p.sample_every, p.n_samples, spb, gm);
+      else
+        hipLaunchKernelGGL(threshold_sample_ring_kernel<4>, rgrid, dim3(ring::Shape<4>::kThreads), 0, stream,
+                           queries, Q, hist, N, d, p.sample_every, p.n_samples, spb, gm);
     } else if (p.list_len == 128) {              // the same core as sim_topk_kernel<2, 128>
       hipLaunchKernelGGL((threshold_sample_kernel<2>), grid, dim3(kThreads), 0, stream, queries, Q,
                          hist, N, d, p.sample_every, p.n_samples, gm);
@@ -1139,6 +1053,26 @@ void chunking(int q_tiles, int N, int target_blocks, int max_chunks, int* chunk_
   *n_chunks = (int)(((long)N + rows - 1) / rows);
 }
 
+// Chunks of the filter kernel: the number of 256-row steps per workgroup that
+// gives the shortest makespan of q_tiles * n_chunks workgroups on `slots`,
+// each costing its steps and about half a step for its start and end. Chunk
+// counts are multiples of 8 (whole chunks per XCD) up to what the select can
+// take: 512 with a spill array for segments that fill up, else 64.
+void filter_chunking(int q_tiles, int N, int slots, bool spill, int* chunk_rows, int* n_chunks) {
+  const long steps = ((long)N + kStepRows - 1) / kStepRows;
+  long best = 1;
+  double best_cost = -1.0;
+  const long most = !spill ? 64 : (q_tiles == 1 ? 512 : (q_tiles <= 8 ? 256 : 64));
+  for (long want = 8; want <= most; want += 8) {
+    const long per = (steps + want - 1) / want, chunks = (steps + per - 1) / per;
+    const long rounds = (chunks * q_tiles + slots - 1) / slots;
+    const double cost = rounds * per * (1.0 + 0.05 / rounds) + 0.5 * rounds;
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = per; }
+  }
+  *chunk_rows = (int)(best * kStepRows);
+  *n_chunks = (int)((steps + best - 1) / best);
+}
+
 }  // namespace
 
 
@@ -1172,27 +1106,33 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     p.sample_every = (int)sr;
     p.n_samples = (int)((steps + sr - 1) / sr);
   }
-  // Filtered path (k <= 64): 256-query tiles, segments of 8192 keys per query in all.
+  // Filtered path (k <= 64): segments of 8192 keys per query in all.
   p.fast = L == 64;
   if (p.fast) {
-    p.f_q_tiles = (Q + ring::Shape<4>::kBQ - 1) / ring::Shape<4>::kBQ;
-    // samples per sampling block: about one block per CU
+    // Up to 128 queries the search is one pass over the store, bound by HBM:
+    // a 128-query tile halves the work done for padding, and two of its
+    // workgroups share a CU.
+    p.f_tile = Q <= 128 ? 128 : 256;
+    p.f_q_tiles = (Q + p.f_tile - 1) / p.f_tile;
+    const int slots = p.f_tile == 128 ? 512 : 256;   // workgroups the chip holds at a time
+    // samples per sampling block: about one block per slot
     p.f_spb = 1;
     while (p.n_samples > 0 && (long)p.f_q_tiles * ((p.n_samples + 2 * p.f_spb - 1) / (2 * p.f_spb)) >= 256)
       p.f_spb *= 2;
-    chunking(p.f_q_tiles, N, 512, 64, &p.f_chunk_rows, &p.f_n_chunks);
-    // Query-tile groups per XCD: the fewest (of 1, 2, 4, 8) whose tiles take at
-    // most 3 MiB of an XCD's 4 MiB L2 (0: no grouping). Each history chunk is
-    // then read from HBM by as many XCDs as there are groups (two on the mid
-    // workload; four groups measured no faster and read the store twice as
-    // often).
-    p.f_q_groups = 0;
-    for (int a = 1; a <= 8; a *= 2) {
-      if (p.f_q_tiles % a != 0 || p.f_n_chunks % (8 / a) != 0) continue;
-      if ((size_t)(p.f_q_tiles / a) * ring::Shape<4>::kBQ * d * 2 <= ((size_t)3 << 20)) { p.f_q_groups = a; break; }
-    }
+    filter_chunking(p.f_q_tiles, N, slots, p.n_samples > 0, &p.f_chunk_rows, &p.f_n_chunks);
+    // Query tiles that an XCD works on at a time: as many (all of them, or a
+    // power of two) as take at most 3 MiB of its 4 MiB L2. On 64 tiles of
+    // 512 KiB, 4 at a time against all 64 against one chunk, same box:
+    // 30.45 -> 29.65 ms (2 at a time 30.25).
+    const long fit = std::max(1L, (3L << 20) / ((long)p.f_tile * d * 2));
+    p.f_q_sub = p.f_q_tiles;
+    if (p.f_q_tiles > fit)
+      for (p.f_q_sub = 1; p.f_q_sub * 2 <= fit; p.f_q_sub *= 2) {}
     p.seg_cap = 1;                                   // power of two, n_chunks * cap <= 8192
     while (p.seg_cap * 2 * p.f_n_chunks <= 8192) p.seg_cap *= 2;
+    // Segments of fewer than 128 keys (more than 64 chunks) fill easily where
+    // a chunk's rows are alike: the rest goes to the query's spill array.
+    p.spill_cap = p.f_n_chunks > 64 ? 4096 : 0;
   }
   // Few queries against a large store: the stream path (one pass over the
   // store, bound by HBM), given a threshold pre-pass. About k * SR keys
@@ -1207,20 +1147,26 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     while (p.s_cap < 4L * k * p.sample_every) p.s_cap *= 2;
   }
   size_t o = 0;
-  p.off_partial = o; o = align256(o + (size_t)Q * p.n_chunks * L * sizeof(uint64_t));
+  // The exact fallback runs after the select: its lists take the place of the
+  // candidates that the select has read.
   const int groups = merge_groups(Q, p.n_chunks, L);
-  p.off_merge = o;   o = align256(o + (groups > 1 ? (size_t)Q * groups * L * sizeof(uint64_t) : 0));
+  p.off_partial = o;
+  p.off_merge = align256(p.off_partial + (size_t)Q * p.n_chunks * L * sizeof(uint64_t));
+  const size_t lists_end = align256(p.off_merge + (groups > 1 ? (size_t)Q * groups * L * sizeof(uint64_t) : 0));
+  if (p.fast) {
+    p.off_seg = o;    o = align256(o + (size_t)Q * p.f_n_chunks * p.seg_cap * sizeof(uint64_t));
+    p.off_spill = o;  o = align256(o + (size_t)Q * p.spill_cap * sizeof(uint64_t));
+  }
+  if (p.stream) { p.off_cand = o; o = align256(o + (size_t)Q * p.s_cap * sizeof(uint64_t)); }
+  o = std::max(o, lists_end);
   p.off_gm = o;      o = align256(o + (size_t)Q * p.n_samples * 16 * sizeof(float));
   p.off_theta = o;   o = align256(o + (size_t)Q * sizeof(float));
   if (p.fast) {
-    p.off_seg = o;    o = align256(o + (size_t)Q * p.f_n_chunks * p.seg_cap * sizeof(uint64_t));
     p.off_segcnt = o; o = align256(o + (size_t)Q * p.f_n_chunks * sizeof(int));
-    p.off_flags = o;  o = align256(o + (size_t)Q * sizeof(int));
-    p.off_flag_word = o; o = align256(o + sizeof(uint32_t));
+    p.off_spillcnt = o; o = align256(o + (p.spill_cap > 0 ? (size_t)Q * sizeof(int) : 0));
   }
-  if (p.stream) {
-    p.off_cand = o;   o = align256(o + (size_t)Q * p.s_cap * sizeof(uint64_t));
-    p.off_ccount = o; o = align256(o + (size_t)Q * sizeof(int));
+  if (p.stream) { p.off_ccount = o; o = align256(o + (size_t)Q * sizeof(int)); }
+  if (p.fast || p.stream) {
     p.off_flags = o;  o = align256(o + (size_t)Q * sizeof(int));
     p.off_flag_word = o; o = align256(o + sizeof(uint32_t));
   }
@@ -1239,8 +1185,10 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
   float* theta0 = reinterpret_cast<float*>(ws + p.off_theta);
   hipError_t e;
   if (p.fast) {
-    if (p.n_samples > 0) {
-      e = launch_theta(queries, Q, hist, N, d, k, p, p.f_q_tiles, Sampler::ring, gm, theta0, nullptr, stream);
+    uint64_t* spill = reinterpret_cast<uint64_t*>(ws + p.off_spill);
+    int* spillcnt = p.spill_cap > 0 ? reinterpret_cast<int*>(ws + p.off_spillcnt) : nullptr;
+    if (p.n_samples > 0) {                             // a spill array comes with a pre-pass, which clears its counts
+      e = launch_theta(queries, Q, hist, N, d, k, p, p.f_q_tiles, Sampler::ring, gm, theta0, spillcnt, stream);
       if (e != hipSuccess) return e;
     }
     uint64_t* seg = reinterpret_cast<uint64_t*>(ws + p.off_seg);
@@ -1248,15 +1196,20 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     const Flagged fl{reinterpret_cast<int*>(ws + p.off_flags), reinterpret_cast<uint32_t*>(ws + p.off_flag_word)};
     {
       LaunchScope scope("sim_topk", stream);
-      hipLaunchKernelGGL(sim_filter_kernel<4>, dim3(p.f_q_tiles * p.f_n_chunks), dim3(ring::Shape<4>::kThreads), 0, stream,
-                         queries, Q, hist, N, d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_groups,
-                         p.n_samples > 0 ? theta0 : nullptr, p.seg_cap, seg, segcnt, fl.word);
+      const float* th = p.n_samples > 0 ? theta0 : nullptr;
+      const dim3 grid((p.f_q_tiles * p.f_n_chunks + 7) / 8 * 8);
+      if (p.f_tile == 128)
+        hipLaunchKernelGGL(sim_filter_kernel<2>, grid, dim3(ring::Shape<2>::kThreads), 0, stream, queries, Q, hist, N,
+                           d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_sub, th, p.seg_cap, seg, segcnt,
+                           p.spill_cap, spill, spillcnt, fl.word);
+      else
+        hipLaunchKernelGGL(sim_filter_kernel<4>, grid, dim3(ring::Shape<4>::kThreads), 0, stream, queries, Q, hist, N,
+                           d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_sub, th, p.seg_cap, seg, segcnt,
+                           p.spill_cap, spill, spillcnt, fl.word);
     }
-    {
-      LaunchScope scope("topk_select", stream);
-      hipLaunchKernelGGL(select_kernel, dim3((Q + 3) / 4), dim3(256), 0, stream, seg, segcnt, Q,
-                         p.f_n_chunks, p.seg_cap, k, min(k, N), fl.flags, fl.word, ids, sims);
-    }
+    const Candidates cand{seg, segcnt, p.f_n_chunks, p.seg_cap, spill, spillcnt, p.spill_cap};
+    e = launch_select(cand, Q, k, min(k, N), fl, ids, sims, stream);
+    if (e != hipSuccess) return e;
     // Exact fallback for queries whose candidates overflowed (no work otherwise).
     e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
     if (e != hipSuccess) return e;
@@ -1268,8 +1221,9 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     const Flagged fl{reinterpret_cast<int*>(ws + p.off_flags), reinterpret_cast<uint32_t*>(ws + p.off_flag_word)};
     e = launch_theta(queries, Q, hist, N, d, k, p, 1, Sampler::stream, gm, theta0, ccount, stream);
     if (e != hipSuccess) return e;
-    e = launch_stream_search(queries, Q, hist, N, d, k, p.s_chunk_rows, theta0, p.s_cap, cand, ccount, fl,
-                             ids, sims, stream);
+    e = launch_stream_search(queries, Q, hist, N, d, p.s_chunk_rows, theta0, p.s_cap, cand, ccount, fl.word, stream);
+    if (e != hipSuccess) return e;
+    e = launch_select(Candidates{nullptr, nullptr, 0, 0, cand, ccount, p.s_cap}, Q, k, min(k, N), fl, ids, sims, stream);
     if (e != hipSuccess) return e;
     // Exact fallback for queries whose candidates overflowed (no work otherwise).
     if (p.list_len == 64) e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);

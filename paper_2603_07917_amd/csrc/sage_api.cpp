@@ -448,16 +448,21 @@ SAGE_API int sage_predict_stats(const void* workspace, size_t workspace_bytes, i
     stats[4] = plan.list_len;
     return ok();
   }
+  std::vector<int32_t> spilled(plan.fast && plan.spill_cap > 0 ? Q : 0);
   counts.resize((size_t)Q * per_query);
   flags.resize(Q);
   hipError_t e = hipMemcpyAsync(counts.data(), ws + (plan.fast ? plan.off_segcnt : plan.off_ccount),
                                 counts.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(flags.data(), ws + plan.off_flags, flags.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess && !spilled.empty())
+    e = hipMemcpyAsync(spilled.data(), ws + plan.off_spillcnt, spilled.size() * sizeof(int32_t), hipMemcpyDeviceToHost,
+                       s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_status(e, "sage_predict_stats copy");
   long long keys = 0, flagged = 0;
   for (int32_t c : counts) keys += c < cap ? c : cap;
+  for (int32_t c : spilled) keys += c < plan.spill_cap ? c : plan.spill_cap;
   for (int32_t f : flags) flagged += f != 0;
   stats[1] = keys;
   stats[2] = flagged;

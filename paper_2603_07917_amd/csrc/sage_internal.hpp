@@ -50,17 +50,19 @@ struct SimTopkPlan {
   int n_samples;
   // filtered path (k <= 64)
   bool fast;
+  int f_tile;       // queries per workgroup: 256 or 128
   int f_q_tiles, f_chunk_rows, f_n_chunks;
   int f_spb;        // sampled steps per threshold-sampling workgroup
-  int f_q_groups;   // query-tile groups across the 8 XCDs (0: plain mapping)
+  int f_q_sub;      // query tiles that an XCD works on at a time
   int seg_cap;      // candidate keys per (query, chunk) segment
+  int spill_cap;    // keys past their segment, per query (0: none; an overflow goes to the exact path)
   // few-query stream path (Q <= kStreamMaxQ, any k <= 256)
   bool stream;
   int s_chunk_rows; // history rows per workgroup
   int s_cap;        // candidate keys per query
   // workspace layout (byte offsets, 256-aligned)
   size_t off_partial, off_merge, off_gm, off_theta, off_seg, off_segcnt, off_flags, off_flag_word, off_cand, off_ccount,
-      total_bytes;
+      off_spill, off_spillcnt, total_bytes;
   size_t workspace_bytes() const { return total_bytes; }
 };
 SimTopkPlan plan_sim_topk(int Q, int N, int d, int k);
@@ -83,9 +85,27 @@ struct Flagged {
   uint32_t* word;
 };
 
-hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int k, int chunk_rows,
-                                const float* theta0, int cap, uint64_t* cand, int* cand_count, Flagged fl,
-                                int32_t* ids, float* sims, hipStream_t stream);
+// Candidate keys of each query, in any order: segments [q][n_chunks][seg_cap]
+// with the keys found in each (seg_count; past seg_cap they were dropped, or
+// spilled when there is a spill array), and spill[q][spill_cap] with
+// spill_count[q] keys (past spill_cap they were dropped).
+struct Candidates {
+  const uint64_t* seg;
+  const int* seg_count;
+  int n_chunks, seg_cap;
+  const uint64_t* spill;
+  const int* spill_count;
+  int spill_cap;
+};
+// The k best of each query's candidates: ids [Q, k] and sims [Q, k], sorted
+// and padded; queries that lost candidates or have fewer than `need` are
+// flagged instead. n_chunks <= 1024 for Q <= 256, <= 256 for Q <= 2048, else <= 64.
+hipError_t launch_select(const Candidates& c, int Q, int k, int need, Flagged fl, int32_t* ids, float* sims,
+                         hipStream_t stream);
+
+hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int chunk_rows,
+                                const float* theta0, int cap, uint64_t* cand, int* cand_count, uint32_t* flag_word,
+                                hipStream_t stream);
 
 // Launchers: each enqueues kernels on `stream` and returns the HIP status of
 // the launch (hipSuccess or the first error).

@@ -1,0 +1,64 @@
+"""The filtered neighbour search (Sec. 3.1: brute-force similarity and top-k)
+at the edges of its tiles, chunk counts and candidate segments, against the
+oracle. Bounds as in tests/parity.py: similarities within the fp32
+accumulation error, neighbour sets exact outside the band around the k-th
+score, counts exact and masses within the bound that follows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2603_07917_amd import sage, workloads
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def check(w, k, layout, workspace=None):
+    qb, hb = sage.ingest_bf16(dev(w.queries), layout), sage.ingest_bf16(dev(w.hist_emb), layout)
+    out = [host(t) for t in sage.predict(qb, hb, dev(w.hist_len), k, 0.8, dev(w.bin_edges), workspace=workspace)]
+    S = oracle.similarity(oracle.round_to_bf16(w.queries), oracle.round_to_bf16(w.hist_emb))
+    parity.check_predict(*out, S, w.hist_len, w.bin_edges, 0.8, k)
+    return out
+
+
+@pytest.mark.parametrize("Q,N,d,k,layout", [
+    (17, 16640, 32, 64, "rows"),        # 128-query tile, 65 steps: the fewest chunks with a spill array
+    (64, 16641, 64, 16, "panels"),      # one row into the 66th step
+    (65, 140000, 96, 64, "panels"),     # more chunks than 512: two steps each
+    (128, 40000, 384, 50, "rows"),      # the whole 128-query tile
+    (129, 40001, 64, 64, "panels"),     # one query into the 256-query tile
+    (257, 33333, 96, 32, "panels"),     # two tiles, four waves per query in the select
+    (2049, 9000, 32, 64, "rows"),       # nine tiles, at most 64 chunks, one wave per query
+])
+def test_filtered_search_edges(Q, N, d, k, layout):
+    print(f"case Q={Q} N={N} d={d} k={k} {layout}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=64, seed=Q + N + k, clusters=12)
+    check(w, k, layout)
+
+
+@pytest.mark.parametrize("Q", [40, 200])
+def test_full_segments_spill(Q):
+    """200 rows of one 256-row step (its whole chunk here) lie around the first
+    queries' cluster, more than a segment of 64 keys holds: the keys past it go
+    to the spill arrays, and no query to the exact path."""
+    N, d, k, B = 79 * 256, 64, 16, 32
+    print(f"case Q={Q}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=31 + Q, clusters=12)
+    rng = np.random.default_rng(4)
+    x = w.queries[0] + 0.02 * rng.standard_normal((200, d)).astype(np.float32)
+    w.hist_emb[300:500] = x / np.linalg.norm(x, axis=1, keepdims=True)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, B), dtype=torch.uint8, device="cuda")
+    ids = check(w, k, "panels", ws)[0]
+    stats = sage.predict_stats(ws, Q, N, d, k, B)
+    assert stats["path"] == "filtered" and stats["segment_capacity"] == 64 and stats["flagged"] == 0
+    assert np.all((ids[0] >= 300) & (ids[0] < 500))
