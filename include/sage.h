@@ -234,7 +234,7 @@ int sage_predict_by_length(const int32_t* prompt_len, int Q, const int32_t* by_l
  * depends on the data). Copies a few counters from the workspace to the host
  * and SYNCHRONISES `stream`: not for the decision path itself.
  *   stats [5] host, out:
- *     [0] search path: 0 exact per-chunk lists, 1 filtered (k <= 64),
+ *     [0] search path: 0 exact per-chunk lists, 1 filtered,
  *         2 few-query stream search
  *     [1] candidate keys written for the select stage (list path: every
  *         list entry, Q * [3] * [4])
@@ -435,7 +435,7 @@ int sage_check_inputs(const double* bin_edges, const double* bin_repr, int B, co
 /*
  * sage_debug_theta_floor - test hook, not for production use. Later
  * sage_predict calls (any thread) raise each query's pre-pass threshold
- * theta0 to at least `floor` on the filtered (k <= 64) and few-query paths,
+ * theta0 to at least `floor` on the filtered and few-query paths,
  * which forces queries onto their exact fallback (a query left with fewer
  * than min(k, N) candidates is answered there); results must not change.
  * -inf turns it off (the default). SAGE_EINVAL for NaN. Host-only state.

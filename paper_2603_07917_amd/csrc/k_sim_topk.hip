@@ -29,6 +29,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "sage.h"
 #include "sage_device.hpp"
 #include "sage_internal.hpp"
 
@@ -1073,6 +1074,36 @@ void filter_chunking(int q_tiles, int N, int slots, bool spill, int* chunk_rows,
   *n_chunks = (int)((steps + best - 1) / best);
 }
 
+// Workspace layout (byte offsets) of a plan whose path is chosen.
+void plan_workspace(SimTopkPlan* p, int Q, int L) {
+  size_t o = 0;
+  // One region for what is dead before the next of it is written: the sampled
+  // maxima (read by the threshold select), the candidates (by the candidate
+  // select) and the exact lists (the fallback runs last).
+  const int groups = merge_groups(Q, p->n_chunks, L);
+  p->off_partial = o;
+  p->off_merge = align256(p->off_partial + (size_t)Q * p->n_chunks * L * sizeof(uint64_t));
+  const size_t lists_end = align256(p->off_merge + (groups > 1 ? (size_t)Q * groups * L * sizeof(uint64_t) : 0));
+  if (p->fast) {
+    p->off_seg = o;    o = align256(o + (size_t)Q * p->f_n_chunks * p->seg_cap * sizeof(uint64_t));
+    p->off_spill = o;  o = align256(o + (size_t)Q * p->spill_cap * sizeof(uint64_t));
+  }
+  if (p->stream) { p->off_cand = o; o = align256(o + (size_t)Q * p->s_cap * sizeof(uint64_t)); }
+  p->off_gm = 0;
+  o = std::max(std::max(o, lists_end), align256((size_t)Q * p->n_samples * 16 * sizeof(float)));
+  p->off_theta = o;   o = align256(o + (size_t)Q * sizeof(float));
+  if (p->fast) {
+    p->off_segcnt = o; o = align256(o + (size_t)Q * p->f_n_chunks * sizeof(int));
+    p->off_spillcnt = o; o = align256(o + (p->spill_cap > 0 ? (size_t)Q * sizeof(int) : 0));
+  }
+  if (p->stream) { p->off_ccount = o; o = align256(o + (size_t)Q * sizeof(int)); }
+  if (p->fast || p->stream) {
+    p->off_flags = o;  o = align256(o + (size_t)Q * sizeof(int));
+    p->off_flag_word = o; o = align256(o + sizeof(uint32_t));
+  }
+  p->total_bytes = o;
+}
+
 }  // namespace
 
 
@@ -1085,11 +1116,13 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
   p.q_tiles = (Q + p.q_tile - 1) / p.q_tile;
   chunking(p.q_tiles, N, 1024, 1 << 20, &p.chunk_rows, &p.n_chunks);
   // Threshold pre-pass: every SR-th step, >= 4k group maxima, at most 8192.
-  // SR <= 16 on the filtered path (every candidate above theta0 is written
-  // out there, so a tighter bound pays for the larger sample), else <= 32.
-  // The sample costs about Q N d / SR and the candidates about Q k SR, so the
-  // best SR grows with the square root of N d: from N d = 2^29 on (1M keys
-  // of d = 1024) the filtered path also samples every 32nd step.
+  // SR <= 16: every candidate above theta0 is written out, so a tighter bound
+  // pays for the larger sample. The sample costs about Q N d / SR and the
+  // candidates about Q k SR, so the best SR grows with the square root of
+  // N d / k: from N d = 2^29 on (1M keys of d = 1024) k <= 64 samples every
+  // 32nd step. For k > 64, decisions of 2,048 queries against 500,000 x 768 at
+  // SR 8 / 16 / 32: k = 128 1,471 / 1,421 / 1,436 us, k = 256 1,528 / 1,501 /
+  // 1,678 us.
   // Only whole steps are sampled.
   const long steps = (long)N / kStepRows;
   if (steps * 16 >= 8L * k) {
@@ -1098,7 +1131,7 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     // (streaming workload: pre-pass 44 -> 16 us, select 16 -> 25 us, call -1.5%).
     const bool wide = Q > kStreamMaxQ && (long)N * d >= (1L << 29);
     const bool few = Q <= kStreamMaxQ && d <= kStreamMaxD && k <= 256;     // the stream path's shapes
-    const long sr_max = few ? 128 : (L == 64 && !wide ? 16 : 32);
+    const long sr_max = few ? 128 : (L == 64 && wide ? 32 : 16);
     long sr = steps * 16 / (4L * k);
     if (sr > sr_max) sr = sr_max;
     if (sr < 1) sr = 1;
@@ -1106,8 +1139,15 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     p.sample_every = (int)sr;
     p.n_samples = (int)((steps + sr - 1) / sr);
   }
-  // Filtered path (k <= 64): segments of 8192 keys per query in all.
-  p.fast = L == 64;
+  // Few queries against a large store: the stream path (one pass over the
+  // store, bound by HBM), given a threshold pre-pass.
+  p.stream = Q <= kStreamMaxQ && d <= kStreamMaxD && k <= 256 && p.n_samples > 0;
+  // Filtered path: segments of 8192 keys per query in all. k > 64 needs the
+  // pre-pass (all rows of a store too small for one would be candidates); the
+  // exact lists, which it replaces there, take 4,620 against 1,421 us at
+  // 2,048 x 500,000 x 768 and k = 128, 7,803 against 1,501 us at k = 256, and
+  // 157 against 80 us at 200 x 20,000 x 768 and k = 128.
+  p.fast = !p.stream && (L == 64 || p.n_samples > 0);
   if (p.fast) {
     // Up to 128 queries the search is one pass over the store, bound by HBM:
     // a 128-query tile halves the work done for padding, and two of its
@@ -1132,45 +1172,27 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     while (p.seg_cap * 2 * p.f_n_chunks <= 8192) p.seg_cap *= 2;
     // Segments of fewer than 128 keys (more than 64 chunks) fill easily where
     // a chunk's rows are alike: the rest goes to the query's spill array.
-    p.spill_cap = p.f_n_chunks > 64 ? 4096 : 0;
+    // So do those of k > 64, whose candidates are more.
+    p.spill_cap = p.f_n_chunks > 64 || L > 64 ? 4096 : 0;
   }
-  // Few queries against a large store: the stream path (one pass over the
-  // store, bound by HBM), given a threshold pre-pass. About k * SR keys
-  // beat theta0 per query; the array holds four times that.
-  p.stream = Q <= kStreamMaxQ && d <= kStreamMaxD && k <= 256 && p.n_samples > 0;
+  // Stream path: about k * SR keys beat theta0 per query; the array holds four
+  // times that.
   if (p.stream) {
-    p.fast = false;
     long rows = ((long)N + 511) / 512;                   // about two workgroups per CU
     rows = (rows + 63) / 64 * 64;
     p.s_chunk_rows = (int)rows;
     p.s_cap = 4096;
     while (p.s_cap < 4L * k * p.sample_every) p.s_cap *= 2;
   }
-  size_t o = 0;
-  // The exact fallback runs after the select: its lists take the place of the
-  // candidates that the select has read.
-  const int groups = merge_groups(Q, p.n_chunks, L);
-  p.off_partial = o;
-  p.off_merge = align256(p.off_partial + (size_t)Q * p.n_chunks * L * sizeof(uint64_t));
-  const size_t lists_end = align256(p.off_merge + (groups > 1 ? (size_t)Q * groups * L * sizeof(uint64_t) : 0));
-  if (p.fast) {
-    p.off_seg = o;    o = align256(o + (size_t)Q * p.f_n_chunks * p.seg_cap * sizeof(uint64_t));
-    p.off_spill = o;  o = align256(o + (size_t)Q * p.spill_cap * sizeof(uint64_t));
+  plan_workspace(&p, Q, L);
+  // The exact lists alone take less: a search of k > 64 that only so fits the
+  // static scratch of the no-allocation entry point keeps to them.
+  if (p.fast && L > 64 && p.total_bytes > (size_t)SAGE_NOALLOC_SCRATCH_BYTES) {
+    SimTopkPlan lists = p;
+    lists.fast = false;
+    plan_workspace(&lists, Q, L);
+    if (lists.total_bytes <= (size_t)SAGE_NOALLOC_SCRATCH_BYTES) return lists;
   }
-  if (p.stream) { p.off_cand = o; o = align256(o + (size_t)Q * p.s_cap * sizeof(uint64_t)); }
-  o = std::max(o, lists_end);
-  p.off_gm = o;      o = align256(o + (size_t)Q * p.n_samples * 16 * sizeof(float));
-  p.off_theta = o;   o = align256(o + (size_t)Q * sizeof(float));
-  if (p.fast) {
-    p.off_segcnt = o; o = align256(o + (size_t)Q * p.f_n_chunks * sizeof(int));
-    p.off_spillcnt = o; o = align256(o + (p.spill_cap > 0 ? (size_t)Q * sizeof(int) : 0));
-  }
-  if (p.stream) { p.off_ccount = o; o = align256(o + (size_t)Q * sizeof(int)); }
-  if (p.fast || p.stream) {
-    p.off_flags = o;  o = align256(o + (size_t)Q * sizeof(int));
-    p.off_flag_word = o; o = align256(o + sizeof(uint32_t));
-  }
-  p.total_bytes = o;
   return p;
 }
 
@@ -1211,7 +1233,9 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     e = launch_select(cand, Q, k, min(k, N), fl, ids, sims, stream);
     if (e != hipSuccess) return e;
     // Exact fallback for queries whose candidates overflowed (no work otherwise).
-    e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
+    if (p.list_len == 64) e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
+    else if (p.list_len == 128) e = launch_lists<2, 128>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
+    else e = launch_lists<1, 256>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
     if (e != hipSuccess) return e;
     return launch_topk_merge(partial, Q, p.n_chunks, p.list_len, k, &fl, merge_lists, ids, sims, stream);
   }

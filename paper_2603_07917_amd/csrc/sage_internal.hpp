@@ -39,7 +39,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 
 // Launch plan of the neighbour search (threshold pre-pass, search, merge).
 struct SimTopkPlan {
-  // exact per-chunk lists (the path for k > 64, and the fallback of the filtered path)
+  // exact per-chunk lists (small stores with k > 64, and the fallback of the other paths)
   int list_len;     // list length: next power of two >= k, at least 64
   int q_tile;       // queries per workgroup
   int q_tiles;      // workgroups along the query axis
@@ -48,7 +48,7 @@ struct SimTopkPlan {
   // threshold pre-pass: every sample_every-th 256-row step (0 samples: none)
   int sample_every;
   int n_samples;
-  // filtered path (k <= 64)
+  // filtered path
   bool fast;
   int f_tile;       // queries per workgroup: 256 or 128
   int f_q_tiles, f_chunk_rows, f_n_chunks;

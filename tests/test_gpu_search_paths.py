@@ -39,11 +39,31 @@ def check(w, k, layout, workspace=None):
     (129, 40001, 64, 64, "panels"),     # one query into the 256-query tile
     (257, 33333, 96, 32, "panels"),     # two tiles, four waves per query in the select
     (2049, 9000, 32, 64, "rows"),       # nine tiles, at most 64 chunks, one wave per query
+    (17, 16384, 64, 128, "panels"),     # k > 64: the smallest store with a pre-pass at k = 128
+    (300, 40000, 96, 65, "rows"),       # two list registers per lane, four waves per query
+    (129, 65537, 32, 256, "panels"),    # four list registers, sixteen waves
+    (2100, 33000, 32, 200, "rows"),     # ... and one wave per query
 ])
 def test_filtered_search_edges(Q, N, d, k, layout):
     print(f"case Q={Q} N={N} d={d} k={k} {layout}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=64, seed=Q + N + k, clusters=12)
     check(w, k, layout)
+
+
+@pytest.mark.parametrize("Q,k", [(300, 100), (40, 256)])
+def test_long_lists_on_the_exact_fallback(Q, k):
+    """theta0 raised from the host until about half, then all, of the queries
+    have fewer than k candidates: the exact lists of 128 and 256 keys answer
+    them with the unforced run's bits (both compute the same fp32 scores)."""
+    w = workloads.small_predict(Q=Q, N=50000, d=96, k=k, B=64, seed=77 + k, clusters=6)
+    base = check(w, k, "panels")
+    try:
+        for floor in (float(np.median(base[1][:, k - 1])), 2.0):
+            sage.debug_theta_floor(floor)
+            for a, b in zip(base, check(w, k, "panels")):
+                assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), f"floor {floor}"
+    finally:
+        sage.debug_theta_floor(-np.inf)
 
 
 @pytest.mark.parametrize("Q", [40, 200])
