@@ -74,6 +74,18 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
     for (int j = 0; j < C; ++j) p[j] = p_next[j];
     if (q + n_waves < Q) load_row<C, kFull>(mass, row + (size_t)n_waves * B, b0, B, p_next);   // prefetch
     const double I = kFused ? (double)prompt_len[q] : 0.0;
+    // Refresh table: the support stays in registers across the levels (C <= 8),
+    // and lane l keeps the result of level l (mod 64), written 64 at a time.
+    constexpr bool kKeepX = kMode == kTable && C <= 8;
+    double x_row[kKeepX ? C : 1];
+    if (kKeepX) {
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const double r = (kFull || b0 + j < B) ? repr_s[b0 + j] : 0.0;
+        x_row[j] = r * fma(0.5, r, I);
+      }
+    }
+    float lane_res = 0.0f;
    for (int lv = 0; lv < n_lv; ++lv) {
     const size_t out = (size_t)lv * (size_t)Q + (size_t)q;
     double a = 0.0;                                 // service already received
@@ -86,6 +98,7 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
     // Support x_j = r (I + r / 2) (or the given cost); recomputed where used,
     // which keeps the register count (and so the occupancy) down.
     auto support = [&](int j) -> double {
+      if (kKeepX) return x_row[kKeepX ? j : 0];
       const int b = b0 + j;
       const bool in = kFull || b < B;
       if (kMode == kVariant) {
@@ -130,6 +143,14 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
     const double f_base = wave_shift_up_dpp_f64(f_incl);
     const double s_base = wave_shift_up_dpp_f64(wave_incl_scan_dpp_f64(lane_s));
     const double f_total = last_lane_f64(f_incl);
+    // No mass above a: +inf here and at every later level (a grows with the
+    // level, so what it rules out stays ruled out). A row of 64 predicted
+    // lengths passes its longest one after about 11 of 41 levels of 200.
+    if (kMode == kTable && f_total == 0.0 && I >= 0.0) {
+      for (int l = (lv & ~(kWave - 1)) + lane; l < n_lv; l += kWave)
+        index[(size_t)l * (size_t)Q + (size_t)q] = l < lv ? lane_res : __builtin_inff();
+      break;
+    }
     const double t_base = f_total - f_incl;
     if (kMode == kVariant && var.kind == 1) {        // the mean: sum p x / sum p
       const double s_incl = s_base + lane_s;
@@ -189,7 +210,14 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
       r = fmin(r, dpp_f64<kDppRowBcast15, 0xa>(r, r));
       r = fmin(r, dpp_f64<kDppRowBcast31, 0xc>(r, r));
     }
-    if (lane == kWave - 1) {
+    if (kMode == kTable) {
+      const double rr = last_lane_f64(r);
+      if (lane == (lv & (kWave - 1))) lane_res = rr < __builtin_inf() ? (float)rr : __builtin_inff();
+      if ((lv & (kWave - 1)) == kWave - 1 || lv == n_lv - 1) {
+        const int l = (lv & ~(kWave - 1)) + lane;
+        if (l <= lv) index[(size_t)l * (size_t)Q + (size_t)q] = lane_res;
+      }
+    } else if (lane == kWave - 1) {
       const bool found = r < __builtin_inf();
       index[out] = found ? (float)r : __builtin_inff();
       if (kArg) argmin[out] = found ? best_b : -1;
