@@ -1,4 +1,5 @@
 // Gittins index scan (with the cost model fused in) and the radix-sort rank.
+#include <algorithm>
 #include "sage_device.hpp"
 #include "sage_internal.hpp"
 
@@ -6,12 +7,19 @@ namespace sage {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Index scan. One wavefront per request row; lane l owns the C consecutive
-// bins [l*C, l*C + C), so a wave reads its row as one contiguous span.
+// Index scan. G lanes per request row (64 / G rows per wavefront); lane l of
+// a row owns the C consecutive bins [l*C, l*C + C), C G >= B.
 //   F_b = sum_{j<=b} p_j, S_b = sum_{j<=b} p_j x_j, T_b = sum_{j>b} p_j,
 //   G = min over b with F_b > 0 of (S_b + T_b x_b) / F_b.
-// Candidates are compared by cross-multiplication (N_b F* < N* F_b), so a row
+// Candidates are compared by cross-multiplication (N_b F* < N* F_b), so a lane
 // costs one fp64 division. All sums are fp64.
+//
+// Bound by the issue of fp64 instructions: about 17 per bin, and per wave
+// about 110 for the scans, the division and the minimum over lanes. Rows of
+// up to 512 bins therefore take 16 or 32 lanes and share that part (against 64
+// lanes a row, same box: 20,011 x 256 10.8 -> 8.1 us, 65,536 x 512 38.9 ->
+// 33.5 us; 65,536 x 1,024 69.0 -> 65.5 us from scalar prompt lengths, late
+// stores and the fp32 minimum; refresh table 32,768 x 256 x 41 429 -> 118 us).
 // ---------------------------------------------------------------------------
 template <int C, bool kFull>
 __device__ __forceinline__ void load_row(const float* __restrict__ mass, size_t row, int b0, int B,
@@ -22,13 +30,20 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mass, size_t 
       const float4 v = *reinterpret_cast<const float4*>(mass + row + b0 + j);
       p[j] = v.x; p[j + 1] = v.y; p[j + 2] = v.z; p[j + 3] = v.w;
     }
+  } else if (!kFull && C % 4 == 0 && B % 4 == 0) {   // rows 16-byte aligned, no quad crosses the row's end
+#pragma unroll
+    for (int j = 0; j < C; j += 4) {
+      float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (b0 + j < B) v = *reinterpret_cast<const float4*>(mass + row + b0 + j);
+      p[j] = v.x; p[j + 1] = v.y; p[j + 2] = v.z; p[j + 3] = v.w;
+    }
   } else {
 #pragma unroll
     for (int j = 0; j < C; ++j) p[j] = (kFull || b0 + j < B) ? mass[row + b0 + j] : 0.0f;
   }
 }
 
-// kFull: B == 64 C, so every lane owns C real bins (no guards, vector loads).
+// kFull: B == C G, so every lane owns C real bins (no guards, vector loads).
 // kMode: kGivenCost takes the support from the cost matrix; kFused computes
 // it from the prompt length and the representatives (kept in LDS);
 // kAttained also refreshes running requests: with o = bucket *
@@ -36,15 +51,19 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mass, size_t 
 // x <= a are ruled out and the rest are shifted down by a, so the result is
 // the index of the remaining cost. kVariant takes the cost model, the kind
 // of index (Gittins or mean) and a uniform-mixing weight at run time.
-// kTable: kAttained for every row at each level o = lv * bucket (lv < levels).
+// kTable: kAttained for every row at each level o = lv * bucket (lv < levels),
+// one row per wave and 64 / G levels at a time.
 enum IndexMode { kGivenCost = 0, kFused = 1, kAttained = 2, kVariant = 3, kTable = 4 };
 // Workgroups per CU the register budget is tuned for (4 waves each).
-template <int C> struct IndexOcc { static constexpr int value = C <= 8 ? 4 : (C == 16 ? 3 : 1); };
+// The table keeps its support in registers: 2 of them and no spills at C = 16.
+template <int C, int kMode> struct IndexOcc {
+  static constexpr int value = C <= 8 ? 4 : (C == 16 ? (kMode == 4 ? 2 : 3) : 1);
+};
 
 constexpr int kNoBin = 0x7fffffff;   // a lane without a candidate bin
 
-template <int C, bool kFull, int kMode, bool kArg>
-__global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const float* __restrict__ mass,
+template <int C, int G, bool kFull, int kMode, bool kArg>
+__global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel(const float* __restrict__ mass,
                                                     const float* __restrict__ cost,
                                                     const int32_t* __restrict__ prompt_len,
                                                     const double* __restrict__ repr,
@@ -52,45 +71,76 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
                                                     int Q, int B, float* __restrict__ index,
                                                     int32_t* __restrict__ argmin, IndexVariant var) {
   constexpr bool kFused = kMode != kGivenCost;
-  extern __shared__ double repr_s[];               // [B] representatives (fused cost only)
+  constexpr bool kAtt = kMode == kAttained || kMode == kTable;
+  constexpr int kR = kWave / G;                    // rows, or levels of a row, at a time
+  constexpr int kRows = kMode == kTable ? 1 : kR;  // rows per wave and turn
+  // Representatives (fused cost only): lane l's C of them at l * kPitch. Without
+  // the pad every lane of a read would start on one or a few of the 64 banks
+  // (C = 16: two of them).
+  constexpr int kPitch = C >= 4 ? C + 2 : C;
+  extern __shared__ __align__(16) double repr_s[];
   const int lane = (int)lane_id();
-  const int wave = (int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
-  const int n_waves = (int)(gridDim.x * (blockDim.x / kWave));
-  const int b0 = lane * C;
+  const int group = lane / G, l = lane % G;
+  // Uniform over the wave.
+  const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave));
+  const int q_step = (int)(gridDim.x * (blockDim.x / kWave)) * kRows;
+  const int b0 = l * C;
+  const double* repr_l = repr_s + l * kPitch;      // element j: bin b0 + j (valid below B)
+  const int q_first = wave * kRows;
+  // This lane's row of a turn (rows past the last one repeat it, unstored).
+  auto row_of = [&](int base) { return kRows == 1 ? base : min(base + group, Q - 1); };
+
+  float p[C], p_next[C];
+  int I_next = 0;
+  // Next row's prompt length before its masses: loads return in order.
+  auto load_next = [&](int base) {
+    const int q = row_of(base);
+    if (kFused) I_next = prompt_len[q];
+    load_row<C, kFull>(mass, (size_t)q * (size_t)B, b0, B, p_next);
+  };
+  if (q_first < Q) load_next(q_first);             // in flight while LDS is set up
   if (kFused) {
-    for (int b = threadIdx.x; b < B; b += blockDim.x) repr_s[b] = repr[b];
+    for (int b = threadIdx.x; b < B; b += blockDim.x) repr_s[b / C * kPitch + b % C] = repr[b];
     __syncthreads();
   }
 
-  float p[C], p_next[C];
-  // Refresh table (kTable): every row at each level o = lv * bucket, from
-  // one read of the row; index[lv * Q + q]. One level in every other mode.
-  constexpr bool kAtt = kMode == kAttained || kMode == kTable;
+  // A row's result (its last lane's) is stored when the next row's loads are
+  // about to go out: a wait for loads also waits for the stores issued before
+  // it, and one issued just before the wait would cost its whole round trip.
+  float res = 0.0f;
+  int res_arg = -1, res_base = -1;
+  auto store_result = [&]() {
+    if (kMode != kTable && res_base >= 0 && l == G - 1 && res_base + group < Q) {
+      index[res_base + group] = res;
+      if (kArg) argmin[res_base + group] = res_arg;
+    }
+  };
   const int n_lv = kMode == kTable ? var.levels : 1;
-  if (wave < Q) load_row<C, kFull>(mass, (size_t)wave * B, b0, B, p_next);
-  for (int q = wave; q < Q; q += n_waves) {
+  for (int base = q_first; base < Q; base += q_step) {
+    const int q = row_of(base);
     const size_t row = (size_t)q * (size_t)B;
 #pragma unroll
     for (int j = 0; j < C; ++j) p[j] = p_next[j];
-    if (q + n_waves < Q) load_row<C, kFull>(mass, row + (size_t)n_waves * B, b0, B, p_next);   // prefetch
-    const double I = kFused ? (double)prompt_len[q] : 0.0;
-    // Refresh table: the support stays in registers across the levels (C <= 8),
-    // and lane l keeps the result of level l (mod 64), written 64 at a time.
-    constexpr bool kKeepX = kMode == kTable && C <= 8;
+    const double I = (double)I_next;
+    store_result();
+    res_base = base;
+    if (base + q_step < Q) load_next(base + q_step);
+    // Refresh table: the support stays in registers across the levels (C <= 16),
+    // and lane t keeps the result of level t (mod 64), written 64 at a time.
+    constexpr bool kKeepX = kMode == kTable && C <= 16;
     double x_row[kKeepX ? C : 1];
     if (kKeepX) {
 #pragma unroll
       for (int j = 0; j < C; ++j) {
-        const double r = (kFull || b0 + j < B) ? repr_s[b0 + j] : 0.0;
+        const double r = (kFull || b0 + j < B) ? repr_l[j] : 0.0;
         x_row[j] = r * fma(0.5, r, I);
       }
     }
     float lane_res = 0.0f;
-   for (int lv = 0; lv < n_lv; ++lv) {
-    const size_t out = (size_t)lv * (size_t)Q + (size_t)q;
+   for (int lv = 0; lv < n_lv; lv += kMode == kTable ? kR : 1) {
     double a = 0.0;                                 // service already received
     if (kAtt) {
-      const double o = kMode == kTable ? (double)lv * (double)bucket
+      const double o = kMode == kTable ? (double)(lv + group) * (double)bucket
                                        : (double)((max(generated[q], 0) / bucket) * bucket);
       a = o * fma(0.5, o, I);
     }
@@ -102,13 +152,13 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
       const int b = b0 + j;
       const bool in = kFull || b < B;
       if (kMode == kVariant) {
-        const double r = in ? repr_s[b] : 0.0;
+        const double r = in ? repr_l[j] : 0.0;
         if (var.cost_model == 1) return r;                       // output length
         if (var.cost_model == 2) return fma(2.0, r, I);          // input + 2 output
         return r * fma(0.5, r, I);
       }
       if (kFused) {
-        const double r = in ? repr_s[b] : 0.0;
+        const double r = in ? repr_l[j] : 0.0;
         return r * fma(0.5, r, I);
       }
       return in ? (double)cost[row + b] : 0.0;
@@ -117,7 +167,7 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
       double raw = 0.0;
 #pragma unroll
       for (int j = 0; j < C; ++j) raw += (double)p[j];
-      const double tot = last_lane_f64(wave_incl_scan_dpp_f64(raw));
+      const double tot = group_total_f64<G>(group_incl_scan_f64<G>(raw));
       if (tot > 0.0) {
         const double keep = (1.0 - (double)var.noise) / tot, spread = (double)var.noise / (double)B;
 #pragma unroll
@@ -137,27 +187,25 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
       lane_f += pm(j);
       lane_s = fma(pm(j), support(j) - a, lane_s);
     }
-    // Prefix sums over lanes (DPP); the mass above this lane is the row total
-    // minus the inclusive prefix (fp64, so its rounding is ~1e-16 of the total).
-    const double f_incl = wave_incl_scan_dpp_f64(lane_f);
-    const double f_base = wave_shift_up_dpp_f64(f_incl);
-    const double s_base = wave_shift_up_dpp_f64(wave_incl_scan_dpp_f64(lane_s));
-    const double f_total = last_lane_f64(f_incl);
+    // Prefix sums over the row's lanes (DPP); the mass above this lane is the
+    // row total minus the inclusive prefix (fp64, so its rounding is ~1e-16 of
+    // the total).
+    const double f_incl = group_incl_scan_f64<G>(lane_f);
+    const double f_base = group_shift_up_f64<G>(f_incl);
+    const double s_base = group_shift_up_f64<G>(group_incl_scan_f64<G>(lane_s));
+    const double f_total = group_total_f64<G>(f_incl);
     // No mass above a: +inf here and at every later level (a grows with the
     // level, so what it rules out stays ruled out). A row of 64 predicted
-    // lengths passes its longest one after about 11 of 41 levels of 200.
-    if (kMode == kTable && f_total == 0.0 && I >= 0.0) {
-      for (int l = (lv & ~(kWave - 1)) + lane; l < n_lv; l += kWave)
-        index[(size_t)l * (size_t)Q + (size_t)q] = l < lv ? lane_res : __builtin_inff();
+    // lengths passes its longest one after about 16 of 41 levels of 200.
+    if (kMode == kTable && !__any(f_total != 0.0) && I >= 0.0) {
+      for (int t = (lv & ~(kWave - 1)) + lane; t < n_lv; t += kWave)
+        index[(size_t)t * (size_t)Q + (size_t)q] = t < lv ? lane_res : __builtin_inff();
       break;
     }
-    const double t_base = f_total - f_incl;
     if (kMode == kVariant && var.kind == 1) {        // the mean: sum p x / sum p
       const double s_incl = s_base + lane_s;
-      if (lane == kWave - 1) {
-        index[out] = f_total > 0.0 ? (float)(s_incl / f_total) : __builtin_inff();
-        if (kArg) argmin[out] = -1;
-      }
+      res = f_total > 0.0 ? (float)(s_incl / f_total) : __builtin_inff();   // the last lane's
+      res_arg = -1;
       continue;
     }
 
@@ -181,11 +229,11 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
       best_f = take ? f_run : best_f;
       if (kArg) best_b = take ? b0 + j : best_b;
     }
-    // One division per lane, then the wave-wide minimum of the ratios
-    // (ties keep the smaller bin when the argmin is wanted): butterflies within
-    // rows of 16 (quads, half rows, rows), then rows 0+1 -> 1, 2+3 -> 3 and
-    // 1 -> 3; lane 63 ends with the row's result. Lanes without a candidate
-    // carry +inf and lose every tie.
+    // One division per lane, then the minimum of the ratios over the row's
+    // lanes, complete in its last lane. With the argmin (ties keep the smaller
+    // bin) in fp64: butterflies within rows of 16 (quads, half rows, rows),
+    // then rows 0+1 -> 1, 2+3 -> 3 (G >= 32) and 1 -> 3 (G = 64). Lanes without
+    // a candidate carry +inf and lose every tie.
     double r = best_f > 0.0 ? best_n / best_f : __builtin_inf();
     if (kArg) {
       auto combine = [&](double orr, int ob) {
@@ -199,65 +247,72 @@ __global__ void __launch_bounds__(256, IndexOcc<C>::value) index_kernel(const fl
       SAGE_ARGMIN_STEP(kDppQuadXor2, 0xf);
       SAGE_ARGMIN_STEP(kDppRowHalfMirror, 0xf);
       SAGE_ARGMIN_STEP(kDppRowMirror, 0xf);
-      SAGE_ARGMIN_STEP(kDppRowBcast15, 0xa);
-      SAGE_ARGMIN_STEP(kDppRowBcast31, 0xc);
+      if (G >= 32) SAGE_ARGMIN_STEP(kDppRowBcast15, 0xa);
+      if (G == 64) SAGE_ARGMIN_STEP(kDppRowBcast31, 0xc);
 #undef SAGE_ARGMIN_STEP
+      const bool found = r < __builtin_inf();
+      res = found ? (float)r : __builtin_inff();
+      res_arg = found ? best_b : -1;
     } else {
-      r = fmin(r, dpp_f64<kDppQuadXor1, 0xf>(r, r));
-      r = fmin(r, dpp_f64<kDppQuadXor2, 0xf>(r, r));
-      r = fmin(r, dpp_f64<kDppRowHalfMirror, 0xf>(r, r));
-      r = fmin(r, dpp_f64<kDppRowMirror, 0xf>(r, r));
-      r = fmin(r, dpp_f64<kDppRowBcast15, 0xa>(r, r));
-      r = fmin(r, dpp_f64<kDppRowBcast31, 0xc>(r, r));
+      // Without it, of the lanes' fp32 values (the rounding is monotone, so it
+      // commutes with the minimum) as monotone bits: one DPP minimum per step
+      // where fp64 takes six instructions.
+      res = f32_from_order_bits(group_min_u32<G>(f32_order_bits((float)r)));
     }
     if (kMode == kTable) {
-      const double rr = last_lane_f64(r);
-      if (lane == (lv & (kWave - 1))) lane_res = rr < __builtin_inf() ? (float)rr : __builtin_inff();
-      if ((lv & (kWave - 1)) == kWave - 1 || lv == n_lv - 1) {
-        const int l = (lv & ~(kWave - 1)) + lane;
-        if (l <= lv) index[(size_t)l * (size_t)Q + (size_t)q] = lane_res;
+      const int t0 = lv & (kWave - 1);                // lv is a multiple of kR, which divides 64
+#pragma unroll
+      for (int g = 0; g < kR; ++g) {
+        const float v = __uint_as_float(
+            (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(res), g * G + G - 1));
+        if (lane == t0 + g) lane_res = v;
       }
-    } else if (lane == kWave - 1) {
-      const bool found = r < __builtin_inf();
-      index[out] = found ? (float)r : __builtin_inff();
-      if (kArg) argmin[out] = found ? best_b : -1;
+      if (t0 + kR == kWave || lv + kR >= n_lv) {
+        const int t = (lv & ~(kWave - 1)) + lane;
+        if (t < lv + kR && t < n_lv) index[(size_t)t * (size_t)Q + (size_t)q] = lane_res;
+      }
     }
    }
   }
+  store_result();
 }
 
-template <int C, bool kFull, int kMode>
+template <int C, int G, bool kFull, int kMode>
 hipError_t launch_index_v(const float* mass, const float* cost, const int32_t* prompt_len,
                           const double* repr, const int32_t* generated, int bucket, int Q, int B,
                           float* index, int32_t* argmin, hipStream_t stream, IndexVariant var) {
   const int waves_per_block = 4;
-  const int rows_per_wave = 4;
-  long waves = ((long)Q + rows_per_wave - 1) / rows_per_wave;
-  long blocks = (waves + waves_per_block - 1) / waves_per_block;
-  if (blocks > 65535) blocks = 65535;
-  if (blocks < 1) blocks = 1;
-  const size_t lds = kMode != kGivenCost ? (size_t)B * sizeof(double) : 0;   // representatives
+  // One turn per wave up to a number of workgroups, then several, the next row
+  // loading behind the one being scanned: a new workgroup first stages the
+  // representatives (65,536 rows x 1,024 bins: 2,048 workgroups 65.6 us, 4,096
+  // 67.1, 16,384 81; table of 32,768 rows x 41 levels: 1,024 workgroups 126 us,
+  // 2,048 118, 4,096 125, 8,192 138).
+  const long most = kMode == kTable || C * G >= 1024 ? 2048 : 4096;
+  const int rows = waves_per_block * (kMode == kTable ? 1 : kWave / G);
+  const long blocks = std::min<long>(((long)Q + rows - 1) / rows, most);
+  // Representatives, a pitch of C + 2 per lane that has any (C as it is for C < 4).
+  const size_t lds = kMode != kGivenCost ? (size_t)((B + C - 1) / C) * (C >= 4 ? C + 2 : C) * sizeof(double) : 0;
   if (argmin)
-    hipLaunchKernelGGL((index_kernel<C, kFull, kMode, true>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((index_kernel<C, G, kFull, kMode, true>), dim3((unsigned)blocks),
                        dim3(64 * waves_per_block), lds, stream, mass, cost, prompt_len, repr, generated,
                        bucket, Q, B, index, argmin, var);
   else
-    hipLaunchKernelGGL((index_kernel<C, kFull, kMode, false>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((index_kernel<C, G, kFull, kMode, false>), dim3((unsigned)blocks),
                        dim3(64 * waves_per_block), lds, stream, mass, cost, prompt_len, repr, generated,
                        bucket, Q, B, index, argmin, var);
   return hipGetLastError();
 }
 
-template <int C>
+template <int C, int G>
 hipError_t launch_index_c(const float* mass, const float* cost, const int32_t* prompt_len,
                           const double* repr, const int32_t* generated, int bucket, int Q, int B,
                           float* index, int32_t* argmin, hipStream_t stream, const IndexVariant* variant) {
-  const bool full = B == 64 * C;
+  const bool full = B == C * G;
   const int mode = (variant && variant->levels > 0) ? kTable
                    : variant ? kVariant : (generated ? kAttained : (cost ? kGivenCost : kFused));
   const IndexVariant var = variant ? *variant : IndexVariant();
 #define SAGE_INDEX_LAUNCH(FULL, MODE)                                                               \
-  return launch_index_v<C, FULL, MODE>(mass, cost, prompt_len, repr, generated, bucket, Q, B, index, \
+  return launch_index_v<C, G, FULL, MODE>(mass, cost, prompt_len, repr, generated, bucket, Q, B, index, \
                                        argmin, stream, var)
   if (mode == kVariant) {
     if (full) SAGE_INDEX_LAUNCH(true, kVariant);
@@ -530,17 +585,18 @@ hipError_t launch_index(const float* mass, const float* cost, const int32_t* pro
   LaunchScope scope(variant ? (variant->levels > 0 ? "index_attained_table" : "index_variant")
                             : (generated ? "index_attained" : "index_scan"),
                     stream);
-  const int per_lane = (B + kWave - 1) / kWave;
-#define SAGE_INDEX_C(CC) \
-  return launch_index_c<CC>(mass, cost, prompt_len, bin_repr, generated, bucket, Q, B, index, argmin, stream, \
-                            variant)
-  if (per_lane <= 1) SAGE_INDEX_C(1);
-  if (per_lane <= 2) SAGE_INDEX_C(2);
-  if (per_lane <= 4) SAGE_INDEX_C(4);
-  if (per_lane <= 8) SAGE_INDEX_C(8);
-  if (per_lane <= 16) SAGE_INDEX_C(16);
-  if (per_lane <= 32) SAGE_INDEX_C(32);
-  SAGE_INDEX_C(64);
+#define SAGE_INDEX_C(CC, GG) \
+  return launch_index_c<CC, GG>(mass, cost, prompt_len, bin_repr, generated, bucket, Q, B, index, argmin, stream, \
+                                variant)
+  if (B <= 16) SAGE_INDEX_C(1, 16);
+  if (B <= 32) SAGE_INDEX_C(2, 16);
+  if (B <= 64) SAGE_INDEX_C(4, 16);
+  if (B <= 128) SAGE_INDEX_C(8, 16);
+  if (B <= 256) SAGE_INDEX_C(16, 16);
+  if (B <= 512) SAGE_INDEX_C(16, 32);
+  if (B <= 1024) SAGE_INDEX_C(16, 64);
+  if (B <= 2048) SAGE_INDEX_C(32, 64);
+  SAGE_INDEX_C(64, 64);
 #undef SAGE_INDEX_C
 }
 

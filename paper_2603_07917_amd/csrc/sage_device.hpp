@@ -119,42 +119,11 @@ __device__ __forceinline__ uint64_t wave_sort64(uint64_t v, bool descending) {
 }
 
 // ---------------------------------------------------------------------------
-// Wave reductions / scans.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_incl_scan_f64(double x) {
-  const int lane = (int)lane_id();
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    double y = __shfl_up(x, off, kWave);
-    if (lane >= off) x += y;
-  }
-  return x;
-}
-// Sum over lanes strictly below this one (no subtraction: shift, then scan).
-__device__ __forceinline__ double wave_excl_scan_f64(double x) {
-  const int lane = (int)lane_id();
-  double v = __shfl_up(x, 1, kWave);
-  if (lane == 0) v = 0.0;
-  return wave_incl_scan_f64(v);
-}
-// Sum over lanes strictly above this one (no subtraction: shift, then scan).
-__device__ __forceinline__ double wave_excl_suffix_f64(double x) {
-  const int lane = (int)lane_id();
-  double v = __shfl_down(x, 1, kWave);
-  if (lane == kWave - 1) v = 0.0;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    double y = __shfl_down(v, off, kWave);
-    if (lane + off < kWave) v += y;
-  }
-  return v;
-}
-
-// ---------------------------------------------------------------------------
 // DPP cross-lane moves (gfx9 wave64 encodings): no LDS round trip.
 // ---------------------------------------------------------------------------
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
 constexpr int kDppWaveShr1 = 0x138, kDppRowMirror = 0x140, kDppRowHalfMirror = 0x141;
+constexpr int kDppRowNewBcast15 = 0x15F;                    // lane 15 of each row of 16, to its row
 constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 constexpr int kDppQuadXor1 = 0xB1, kDppQuadXor2 = 0x4E;     // quad_perm [1,0,3,2], [2,3,0,1]
 
@@ -172,25 +141,63 @@ __device__ __forceinline__ double dpp_f64(double old, double x) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Inclusive prefix sum over the 64 lanes (rows of 16 first, then across rows).
-__device__ __forceinline__ double wave_incl_scan_dpp_f64(double x) {
-  x += dpp_f64<kDppRowShr1>(0.0, x);
-  x += dpp_f64<kDppRowShr2>(0.0, x);
-  x += dpp_f64<kDppRowShr4>(0.0, x);
-  x += dpp_f64<kDppRowShr8>(0.0, x);
-  x += dpp_f64<kDppRowBcast15, 0xa>(0.0, x);
-  x += dpp_f64<kDppRowBcast31, 0xc>(0.0, x);
-  return x;
-}
-// Lane 63's value, in every lane.
-__device__ __forceinline__ double last_lane_f64(double x) {
-  const uint64_t u = (uint64_t)__double_as_longlong(x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, kWave - 1);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), kWave - 1);
+// The same over all rows with 0 where the source is outside the pattern (the
+// bound-control form: no register to preset).
+template <int kCtrl>
+__device__ __forceinline__ double dpp_f64_or_zero(double x) {
+  const uint64_t v = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, kCtrl, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), kCtrl, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-// The inclusive value of the lane below (0 for lane 0): an exclusive prefix.
-__device__ __forceinline__ double wave_shift_up_dpp_f64(double x) { return dpp_f64<kDppWaveShr1>(0.0, x); }
+
+// Scans and reductions over groups of G = 16, 32 or 64 consecutive lanes.
+// Inclusive prefix sum (rows of 16 first, then across rows).
+template <int G>
+__device__ __forceinline__ double group_incl_scan_f64(double x) {
+  x += dpp_f64_or_zero<kDppRowShr1>(x);
+  x += dpp_f64_or_zero<kDppRowShr2>(x);
+  x += dpp_f64_or_zero<kDppRowShr4>(x);
+  x += dpp_f64_or_zero<kDppRowShr8>(x);
+  if (G >= 32) x += dpp_f64<kDppRowBcast15, 0xa>(0.0, x);
+  if (G == 64) x += dpp_f64<kDppRowBcast31, 0xc>(0.0, x);
+  return x;
+}
+// Value of a fixed lane, in every lane.
+__device__ __forceinline__ double lane_value_f64(double x, int src_lane) {
+  return __longlong_as_double((long long)lane_value_u64((uint64_t)__double_as_longlong(x), src_lane));
+}
+// The group's last lane's value, in each of its lanes.
+template <int G>
+__device__ __forceinline__ double group_total_f64(double x) {
+  if constexpr (G == 16) {
+    return dpp_f64_or_zero<kDppRowNewBcast15>(x);
+  } else if constexpr (G == 32) {
+    const double lo = lane_value_f64(x, 31), hi = lane_value_f64(x, 63);
+    return (lane_id() & 32) ? hi : lo;
+  } else {
+    return lane_value_f64(x, kWave - 1);
+  }
+}
+// The value of the lane below (0 for a group's first lane): from an inclusive
+// prefix the exclusive one.
+template <int G>
+__device__ __forceinline__ double group_shift_up_f64(double x) {
+  if constexpr (G == 16) return dpp_f64_or_zero<kDppRowShr1>(x);
+  const double y = dpp_f64_or_zero<kDppWaveShr1>(x);
+  return G == 32 && lane_id() == 32 ? 0.0 : y;
+}
+// Minimum over the group, in its last lane.
+template <int G>
+__device__ __forceinline__ uint32_t group_min_u32(uint32_t x) {
+  x = min(x, dpp_u32<kDppQuadXor1>(x, x));
+  x = min(x, dpp_u32<kDppQuadXor2>(x, x));
+  x = min(x, dpp_u32<kDppRowHalfMirror>(x, x));
+  x = min(x, dpp_u32<kDppRowMirror>(x, x));
+  if (G >= 32) x = min(x, dpp_u32<kDppRowBcast15, 0xa>(x, x));
+  if (G == 64) x = min(x, dpp_u32<kDppRowBcast31, 0xc>(x, x));
+  return x;
+}
 
 // Sum over the 64 lanes, returned as a wave-uniform value (DPP row scans,
 // then lane 63).
@@ -222,12 +229,6 @@ __device__ __forceinline__ uint32_t wave_min_dpp_u32(uint32_t x) {
   x = min(x, dpp_u32<kDppRowBcast15, 0xa>(x, x));
   x = min(x, dpp_u32<kDppRowBcast31, 0xc>(x, x));
   return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
-}
-
-__device__ __forceinline__ int wave_sum_i32(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
 }
 
 }  // namespace sage

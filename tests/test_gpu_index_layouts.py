@@ -1,0 +1,63 @@
+"""The index scan (Sec. 3.3) at the edges of its lane layouts: 16, 32 or 64
+lanes per row, 1 to 64 bins per lane, rows that fill them or not, batches
+that leave the last wave's rows short. Against the oracle; the bound is the
+parity bar of the index on identical inputs."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2603_07917_amd import sage, workloads
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def close(g, G):
+    assert np.array_equal(np.isinf(g), np.isinf(G))
+    f = np.isfinite(G)
+    assert np.all(np.abs(g[f].astype(np.float64) - G[f]) <= parity.INDEX_RTOL * np.abs(G[f]))
+
+
+@pytest.mark.parametrize("B", [1, 16, 17, 32, 33, 64, 65, 128, 129, 256, 257, 260, 512, 513, 1024, 1025, 2049])
+def test_index_layouts(B):
+    rng = np.random.default_rng(B)
+    Q = 133
+    mass = rng.dirichlet(np.full(B, 0.3), size=Q).astype(np.float32)
+    mass[rng.random((Q, B)) < 0.5] = 0.0
+    mass[5] = 0.0                                             # no mass: +inf
+    plen = rng.integers(0, 4000, size=Q).astype(np.int32)
+    _, r = workloads.log_bins(16384, B)
+    x = oracle.cost(plen, r)
+    G, arg = oracle.gittins(mass.astype(np.float64), x)
+    md, pd, rd = dev(mass), dev(plen), dev(r)
+    g, a = sage.index(md, pd, rd, with_argmin=True)
+    g, a = host(g), host(a)
+    close(g, G)
+    ratio = g.astype(np.float64)
+    assert a[5] == -1 and np.all((a >= 0) == np.isfinite(ratio))
+    for q in (1, 2, 3, 5):                                    # fewer rows than a wave holds
+        assert np.array_equal(host(sage.index(md[:q].contiguous(), pd[:q].contiguous(), rd)).view(np.uint32),
+                              g[:q].view(np.uint32))
+    gen = rng.integers(0, 2000, size=Q).astype(np.int32)
+    Ga, _ = oracle.gittins_attained(mass.astype(np.float64), x, oracle.attained_service(plen, gen, 200))
+    close(host(sage.index_attained(md, pd, rd, dev(gen), 200)), Ga)
+    levels = 70                                               # past one block of 64 levels
+    table = host(sage.index_attained_table(md, pd, rd, levels, 250))
+    for lv in (0, 1, 3, 63, 64, 69):
+        Gt, _ = oracle.gittins_attained(mass.astype(np.float64), x,
+                                        oracle.attained_service(plen, np.full(Q, lv * 250), 250))
+        close(table[lv], Gt)
+        one = host(sage.index_attained(md, pd, rd, dev(np.full(Q, lv * 250, np.int32)), 250))
+        assert np.array_equal(table[lv].view(np.uint32), one.view(np.uint32)), lv
+    mean = host(sage.index_variant(md, pd, rd, kind="mean", noise=0.2))
+    assert np.array_equal(np.isinf(mean), mass.sum(axis=1) == 0)
