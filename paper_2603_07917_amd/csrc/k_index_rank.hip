@@ -499,7 +499,7 @@ __global__ void __launch_bounds__(kRankThreads) rank_scatter_kernel(
 // them takes the exact rule. Q^2 compares, one compare and one add each:
 // at these sizes a few microseconds spread over the whole chip, where the
 // four-pass radix sort in one workgroup ran serially.
-constexpr int kRankSmallMax = 16384;
+constexpr int kRankSmallMax = 8192;
 constexpr int kRankCountThreads = 1024;
 constexpr int kRankCountWaves = kRankCountThreads / kWave;
 
@@ -570,6 +570,133 @@ __global__ void __launch_bounds__(kRankCountThreads) rank_count_kernel(const flo
   }
 }
 
+// ---------------------------------------------------------------------------
+// Rank of a medium queue (kRankSmallMax < Q <= kRankMergeMax): sorted tiles,
+// then every request's position by binary searches in all of them. Two
+// launches, where the radix sort takes eight (four digits, each a count and a
+// scatter on a few workgroups).
+//
+// rank_tile_kernel: a workgroup sorts a tile of T consecutive requests by
+// (key, id): each wave sorts 64 (bitonic, across lanes), and a request's place
+// in the tile is its place in its wave plus, for every other wave, the number
+// of its keys before it: key <= its own in an earlier wave, < in a later one
+// (ids rise with the wave). Keys and ids go out in sorted order, the last tile
+// padded with the largest key.
+//
+// rank_merge_kernel: the same rule over tiles gives the final position. A
+// workgroup takes E requests of one tile; 1024 / E threads share a request,
+// each searching its part of the tiles, whose keys pass through LDS in groups
+// of kGroupTiles. Neighbouring lanes hold neighbouring keys, so their searches
+// read mostly the same words. The work grows as Q^2 / T: 20,011 requests 56.8
+// (radix) -> 11.6 us, 65,536 72.8 -> 21.8, 131,072 88.2 -> 44.9, but 160,000
+// 67.6 -> 89.7. Below kRankSmallMax one launch of counting is as fast (8,192:
+// 8.9 against 9.1 us; 16,384: 24.1 against 10.2).
+// ---------------------------------------------------------------------------
+constexpr int kRankMergeMax = 131072;
+constexpr uint32_t kRankPad = 0xFFFFFFFFu;          // above every key but NaN's
+
+// Number of the n (a power of two) ascending keys of `a` below k (or, with
+// `or_equal`, at most k).
+__device__ __forceinline__ int count_before(const uint32_t* a, int n, uint32_t k, bool or_equal) {
+  // key <= k is key < k + 1 except at k = 2^32 - 1, where all are at most k.
+  const uint32_t lim = or_equal ? k + 1u : k;
+  if (or_equal && lim == 0u) return n;
+  int pos = 0;
+  for (int step = n >> 1; step > 0; step >>= 1) pos += a[pos + step - 1] < lim ? step : 0;
+  return pos + (a[pos] < lim ? 1 : 0);
+}
+
+template <int T>
+__global__ void __launch_bounds__(T) rank_tile_kernel(const float* __restrict__ g_in, int Q,
+                                                      uint32_t* __restrict__ keys_out, int32_t* __restrict__ ids_out) {
+  constexpr int kWaves = T / kWave;
+  __shared__ uint32_t keys[T];
+  const int lane = (int)lane_id();
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int base = blockIdx.x * T;
+  const int i = base + (int)threadIdx.x;
+  // Sorted ascending by (key, place): the pads keep distinct places.
+  const uint64_t mine = wave_sort64(((uint64_t)(i < Q ? index_key(g_in[i]) : kRankPad) << 32) | threadIdx.x, false);
+  const uint32_t key = (uint32_t)(mine >> 32);
+  keys[threadIdx.x] = key;
+  __syncthreads();
+  int pos = lane;
+#pragma unroll
+  for (int o = 0; o < kWaves; ++o)
+    if (o != w) pos += count_before(keys + o * kWave, kWave, key, o < w);
+  keys_out[base + pos] = key;
+  ids_out[base + pos] = base + (int)(uint32_t)mine;
+}
+
+template <int T, int E>
+__global__ void __launch_bounds__(1024) rank_merge_kernel(const uint32_t* __restrict__ keys_in,
+                                                          const int32_t* __restrict__ ids_in, int Q, int n_tiles,
+                                                          int32_t* __restrict__ order) {
+  constexpr int kGroupTiles = 32768 / T;            // 128 KiB of keys in LDS at a time
+  constexpr int kShare = 1024 / E;                  // threads per request
+  constexpr int kIlp = 4;                           // searches of a thread in flight
+  __shared__ __align__(16) uint32_t keys[kGroupTiles * T];
+  __shared__ int part[kShare][E];
+  const int e = (int)threadIdx.x % E, s = (int)threadIdx.x / E;
+  const int at = blockIdx.x * E + e;                // place among the sorted tiles
+  const int own = blockIdx.x * E / T;               // E divides T
+  const uint32_t k = keys_in[at];
+  int cnt = s == 0 ? at - own * T : 0;              // place in its own tile
+  for (int t0 = 0; t0 < n_tiles; t0 += kGroupTiles) {
+    const int n = min(kGroupTiles, n_tiles - t0);
+    __syncthreads();                                // the previous group's searches are done
+    const uint4* src = reinterpret_cast<const uint4*>(keys_in + (size_t)t0 * T);
+    for (int i = threadIdx.x; i < n * T / 4; i += 1024) reinterpret_cast<uint4*>(keys)[i] = src[i];
+    __syncthreads();
+    for (int t = s; t < n; t += kShare * kIlp) {
+      // kIlp tiles t, t + kShare, ...: the same search steps on each. A tile
+      // past the group searches the last one, uncounted.
+      const uint32_t* a[kIlp];
+      uint32_t lim[kIlp];
+      int pos[kIlp];
+#pragma unroll
+      for (int u = 0; u < kIlp; ++u) {
+        const int tt = min(t + u * kShare, n - 1);
+        a[u] = keys + tt * T;
+        lim[u] = t0 + tt < own ? k + 1u : k;        // no real key is 2^32 - 1
+        pos[u] = 0;
+      }
+#pragma unroll
+      for (int step = T / 2; step > 0; step >>= 1)
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u) pos[u] += a[u][pos[u] + step - 1] < lim[u] ? step : 0;
+#pragma unroll
+      for (int u = 0; u < kIlp; ++u) {
+        pos[u] += a[u][pos[u]] < lim[u] ? 1 : 0;
+        const int tt = t + u * kShare;
+        if (tt < n && t0 + tt != own) cnt += pos[u];
+      }
+    }
+  }
+  part[s][e] = cnt;
+  __syncthreads();
+  if (s != 0) return;
+  int rank = 0;
+#pragma unroll
+  for (int i = 0; i < kShare; ++i) rank += part[i][e];
+  const int id = ids_in[at];
+  if (id < Q) order[rank] = id;                     // not a pad
+}
+
+template <int T, int E>
+void launch_rank_merge(const float* index, int Q, int32_t* order, void* ws, hipStream_t stream) {
+  const int n_tiles = (Q + T - 1) / T;
+  uint32_t* keys = static_cast<uint32_t*>(ws);
+  int32_t* ids = reinterpret_cast<int32_t*>(keys + (size_t)n_tiles * T);
+  {
+    LaunchScope scope("rank_tiles", stream);
+    hipLaunchKernelGGL(rank_tile_kernel<T>, dim3(n_tiles), dim3(T), 0, stream, index, Q, keys, ids);
+  }
+  LaunchScope scope("rank_merge", stream);
+  hipLaunchKernelGGL((rank_merge_kernel<T, E>), dim3(n_tiles * (T / E)), dim3(1024), 0, stream, keys, ids, Q, n_tiles,
+                     order);
+}
+
 }  // namespace
 
 size_t rank_workspace_bytes(int Q) {
@@ -608,10 +735,18 @@ hipError_t launch_rank(const float* index, int Q, int32_t* order, void* ws, hipS
     LaunchScope scope("rank_small", stream);
     if (Q <= 4096)
       hipLaunchKernelGGL(rank_count_kernel<16>, dim3((Q + 15) / 16), dim3(kRankCountThreads), 0, stream, index, Q, order);
-    else if (Q <= 8192)
-      hipLaunchKernelGGL(rank_count_kernel<32>, dim3((Q + 31) / 32), dim3(kRankCountThreads), 0, stream, index, Q, order);
     else
-      hipLaunchKernelGGL(rank_count_kernel<64>, dim3((Q + 63) / 64), dim3(kRankCountThreads), 0, stream, index, Q, order);
+      hipLaunchKernelGGL(rank_count_kernel<32>, dim3((Q + 31) / 32), dim3(kRankCountThreads), 0, stream, index, Q, order);
+    return hipGetLastError();
+  }
+  if (Q <= kRankMergeMax) {
+    // Tiles of 512 sort faster, tiles of 1,024 are half as many to search; more
+    // requests per workgroup read the tiles less often, fewer give more
+    // workgroups. <512, 128> / <1024, 256> / <1024, 512>: 20,011 requests
+    // 11.6 / 14.5 / 15.8 us, 65,536 26.9 / 21.8 / 27.3, 131,072 78.9 / 50.8 / 44.9.
+    if (Q <= 32768) launch_rank_merge<512, 128>(index, Q, order, ws, stream);
+    else if (Q <= 81920) launch_rank_merge<1024, 256>(index, Q, order, ws, stream);
+    else launch_rank_merge<1024, 512>(index, Q, order, ws, stream);
     return hipGetLastError();
   }
   const int n_tiles = (Q + kRankTile - 1) / kRankTile;
