@@ -235,7 +235,7 @@ int sage_predict_by_length(const int32_t* prompt_len, int Q, const int32_t* by_l
  * and SYNCHRONISES `stream`: not for the decision path itself.
  *   stats [5] host, out:
  *     [0] search path: 0 exact per-chunk lists, 1 filtered,
- *         2 few-query stream search
+ *         2 few-query stream search, 3 every score written out (small stores)
  *     [1] candidate keys written for the select stage (list path: every
  *         list entry, Q * [3] * [4])
  *     [2] queries sent to the exact fallback

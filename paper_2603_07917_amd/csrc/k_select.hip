@@ -2,37 +2,10 @@
 // search wrote for it (the keys at or above its pre-pass threshold).
 #include "sage_device.hpp"
 #include "sage_internal.hpp"
+#include "sage_toplist.hpp"
 
 namespace sage {
 namespace {
-
-// The list of a wave's S * 64 best keys, descending over positions
-// p = 64 s + lane (register s, lane). Half-cleaners sort a bitonic list.
-template <int S>
-__device__ __forceinline__ void list_clean(uint64_t (&lv)[S]) {
-#pragma unroll
-  for (int st = S / 2; st >= 1; st >>= 1)
-#pragma unroll
-    for (int s = 0; s < S; ++s)
-      if ((s & st) == 0) {
-        const uint64_t x = lv[s], y = lv[s + st];
-        lv[s] = x > y ? x : y;
-        lv[s + st] = x > y ? y : x;
-      }
-#pragma unroll
-  for (int s = 0; s < S; ++s)
-#pragma unroll
-    for (int stride = 32; stride > 0; stride >>= 1) lv[s] = cx_lanes(lv[s], stride, true);
-}
-// Fold 64 keys (one per lane, any order) into the list: sorted ascending
-// they are the reversed tail of a descending list, so max(A_p, B_(KL-1-p))
-// touches the last register only and leaves a bitonic list.
-template <int S>
-__device__ __forceinline__ void list_fold(uint64_t (&lv)[S], uint64_t key) {
-  const uint64_t asc = wave_sort64(key, false);
-  lv[S - 1] = lv[S - 1] > asc ? lv[S - 1] : asc;
-  list_clean<S>(lv);
-}
 
 // W wavefronts per query. Wave w takes the w-th share of the query's segments
 // (at most 64; they form one index range, kPre groups of 64 keys in flight)
@@ -110,29 +83,7 @@ __global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) select_kernel(Candidate
   if (lane == 0 && w == 0) fl.flags[q] = 0;
   __builtin_amdgcn_wave_barrier();                    // off[] written before it is read
 
-  uint64_t* buf = pend[wg];
-  uint64_t lv[S];
-#pragma unroll
-  for (int s = 0; s < S; ++s) lv[s] = kPadKey;
-  int n_buf = 0;                                      // keys waiting in buf (wave-uniform, < 64)
-  auto take = [&](uint64_t cur) {
-    const bool keep = cur > lane_value_u64(lv[S - 1], kWave - 1);
-    const uint64_t mask = __ballot(keep);
-    if (mask == 0) return;
-    const int pos = n_buf + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-    if (keep) buf[pos] = cur;
-    n_buf += __popcll(mask);
-    __builtin_amdgcn_wave_barrier();
-    if (n_buf >= kWave) {                             // fold 64, keep the rest (< 64) at the front
-      list_fold<S>(lv, buf[lane]);
-      n_buf -= kWave;
-      const uint64_t rest = lane < n_buf ? buf[kWave + lane] : kPadKey;
-      __builtin_amdgcn_wave_barrier();
-      if (lane < n_buf) buf[lane] = rest;
-      __builtin_amdgcn_wave_barrier();
-    }
-  };
+  TopList<S> top(pend[wg]);
   constexpr int kPre = W == 1 ? 8 : 4;                // loads in flight per wave
   const uint64_t* src = c.seg + ((size_t)q * c.n_chunks + c0) * c.seg_cap;
   for (int e0 = 0; kSeg && e0 < total; e0 += kWave * kPre) {
@@ -151,7 +102,7 @@ __global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) select_kernel(Candidate
       }
     }
 #pragma unroll
-    for (int j = 0; j < kPre; ++j) take(cur[j]);
+    for (int j = 0; j < kPre; ++j) top.take(cur[j]);
   }
   const uint64_t* more = c.spill + (size_t)q * c.spill_cap;
   for (int e0 = w * kWave; e0 < n_spill; e0 += kPre * W * kWave) {
@@ -162,36 +113,14 @@ __global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) select_kernel(Candidate
       cur[j] = e < n_spill ? more[e] : kPadKey;
     }
 #pragma unroll
-    for (int j = 0; j < kPre; ++j) take(cur[j]);
+    for (int j = 0; j < kPre; ++j) top.take(cur[j]);
   }
-  if (n_buf > 0) list_fold<S>(lv, lane < n_buf ? buf[lane] : kPadKey);
+  top.flush();
   if constexpr (W > 1) {
-#pragma unroll
-    for (int s = 0; s < S; ++s) lists[w][64 * s + lane] = lv[s];
-    __syncthreads();
-    for (int h = 1; h < W; h <<= 1) {
-      if ((w & (2 * h - 1)) == 0) {
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const uint64_t o = lists[w + h][64 * (S - 1 - s) + (kWave - 1 - lane)];
-          lv[s] = lv[s] > o ? lv[s] : o;
-        }
-        list_clean<S>(lv);
-#pragma unroll
-        for (int s = 0; s < S; ++s) lists[w][64 * s + lane] = lv[s];
-      }
-      __syncthreads();
-    }
+    merge_lists<S, W>(top.lv, &lists[0][0], w, W);
     if (w != 0) return;
   }
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const int p = 64 * s + lane;
-    if (p < k) {
-      ids[(size_t)q * k + p] = lv[s] == kPadKey ? -1 : key_id(lv[s]);
-      sims[(size_t)q * k + p] = lv[s] == kPadKey ? -__builtin_inff() : key_sim(lv[s]);
-    }
-  }
+  top.write(k, ids + (size_t)q * k, sims + (size_t)q * k);
 }
 
 // Wavefronts per query: 16 while the workgroups of 16 fit the chip at once

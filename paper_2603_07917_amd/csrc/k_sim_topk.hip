@@ -1139,6 +1139,13 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     p.sample_every = (int)sr;
     p.n_samples = (int)((steps + sr - 1) / sr);
   }
+  // Small store and batch: every score written out (up to 20 MB of them).
+  p.dense = N <= kDenseMaxRows && d <= kDenseMaxD && (long)Q * N <= kDenseMaxScores;
+  p.dense_ld = (N + 31) / 32 * 32;
+  if (p.dense) {
+    p.total_bytes = align256((size_t)Q * p.dense_ld * sizeof(float));
+    return p;
+  }
   // Few queries against a large store: the stream path (one pass over the
   // store, bound by HBM), given a threshold pre-pass.
   p.stream = Q <= kStreamMaxQ && d <= kStreamMaxD && k <= 256 && p.n_samples > 0;
@@ -1201,6 +1208,9 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
                              hipStream_t stream) {
   if (Q == 0) return hipSuccess;
   char* ws = static_cast<char*>(workspace);
+  if (p.dense)
+    return launch_dense(queries, Q, hist, N, d, k, p.dense_ld, reinterpret_cast<float*>(ws + p.off_scores), ids, sims,
+                        stream);
   uint64_t* partial = reinterpret_cast<uint64_t*>(ws + p.off_partial);
   uint64_t* merge_lists = reinterpret_cast<uint64_t*>(ws + p.off_merge);
   float* gm = reinterpret_cast<float*>(ws + p.off_gm);

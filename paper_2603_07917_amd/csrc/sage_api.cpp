@@ -433,6 +433,13 @@ SAGE_API int sage_predict_stats(const void* workspace, size_t workspace_bytes, i
   hipStream_t s = (hipStream_t)stream;
   std::vector<int32_t> counts, flags;
   int per_query = 0, cap = 0;
+  if (plan.dense) {
+    stats[0] = 3;
+    stats[1] = (long long)Q * N;
+    stats[3] = 1;
+    stats[4] = N;
+    return ok();
+  }
   if (plan.fast) {
     stats[0] = 1;
     per_query = plan.f_n_chunks;

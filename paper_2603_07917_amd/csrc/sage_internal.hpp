@@ -56,13 +56,16 @@ struct SimTopkPlan {
   int f_q_sub;      // query tiles that an XCD works on at a time
   int seg_cap;      // candidate keys per (query, chunk) segment
   int spill_cap;    // keys past their segment, per query (0: none; an overflow goes to the exact path)
+  // small stores: every score written out (row pitch in scores)
+  bool dense;
+  int dense_ld;
   // few-query stream path (Q <= kStreamMaxQ, any k <= 256)
   bool stream;
   int s_chunk_rows; // history rows per workgroup
   int s_cap;        // candidate keys per query
   // workspace layout (byte offsets, 256-aligned)
   size_t off_partial, off_merge, off_gm, off_theta, off_seg, off_segcnt, off_flags, off_flag_word, off_cand, off_ccount,
-      off_spill, off_spillcnt, total_bytes;
+      off_spill, off_spillcnt, off_scores, total_bytes;
   size_t workspace_bytes() const { return total_bytes; }
 };
 SimTopkPlan plan_sim_topk(int Q, int N, int d, int k);
@@ -102,6 +105,13 @@ struct Candidates {
 // flagged instead. n_chunks <= 1024 for Q <= 256, <= 256 for Q <= 2048, else <= 64.
 hipError_t launch_select(const Candidates& c, int Q, int k, int need, Flagged fl, int32_t* ids, float* sims,
                          hipStream_t stream);
+
+// Small stores (N <= kDenseMaxRows): scores [Q][ld] and the k best of each row.
+constexpr int kDenseMaxRows = 32768;
+constexpr int kDenseMaxD = 8192;
+constexpr long kDenseMaxScores = 5L << 20;
+hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
+                        int32_t* ids, float* sims, hipStream_t stream);
 
 hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int chunk_rows,
                                 const float* theta0, int cap, uint64_t* cand, int* cand_count, uint32_t* flag_word,

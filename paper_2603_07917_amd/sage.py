@@ -379,7 +379,7 @@ def predict_stats(workspace: torch.Tensor, Q: int, N: int, d: int, k: int, B: in
     out = (ctypes.c_longlong * 5)()
     _check(load_library().sage_predict_stats(workspace.data_ptr(), workspace.numel(), Q, N, d, k, B, out,
                                              _stream()))
-    path = {0: "lists", 1: "filtered", 2: "stream"}[int(out[0])]
+    path = {0: "lists", 1: "filtered", 2: "stream", 3: "dense"}[int(out[0])]
     return {"path": path, "candidate_keys": int(out[1]), "flagged": int(out[2]),
             "segments_per_query": int(out[3]), "segment_capacity": int(out[4])}
 

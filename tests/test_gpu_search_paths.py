@@ -32,14 +32,14 @@ def check(w, k, layout, workspace=None):
 
 
 @pytest.mark.parametrize("Q,N,d,k,layout", [
-    (17, 16640, 32, 64, "rows"),        # 128-query tile, 65 steps: the fewest chunks with a spill array
-    (64, 16641, 64, 16, "panels"),      # one row into the 66th step
+    (17, 32769, 32, 64, "rows"),        # 128-query tile, one row past the stores whose scores are all written
+    (64, 33024, 64, 16, "panels"),      # 129 whole steps, each a chunk with a small segment
     (65, 140000, 96, 64, "panels"),     # more chunks than 512: two steps each
     (128, 40000, 384, 50, "rows"),      # the whole 128-query tile
     (129, 40001, 64, 64, "panels"),     # one query into the 256-query tile
     (257, 33333, 96, 32, "panels"),     # two tiles, four waves per query in the select
     (2049, 9000, 32, 64, "rows"),       # nine tiles, at most 64 chunks, one wave per query
-    (17, 16384, 64, 128, "panels"),     # k > 64: the smallest store with a pre-pass at k = 128
+    (321, 16384, 64, 128, "panels"),    # k > 64: the smallest store with a pre-pass at k = 128
     (300, 40000, 96, 65, "rows"),       # two list registers per lane, four waves per query
     (129, 65537, 32, 256, "panels"),    # four list registers, sixteen waves
     (2100, 33000, 32, 200, "rows"),     # ... and one wave per query
@@ -69,9 +69,9 @@ def test_long_lists_on_the_exact_fallback(Q, k):
 @pytest.mark.parametrize("Q", [40, 200])
 def test_full_segments_spill(Q):
     """200 rows of one 256-row step (its whole chunk here) lie around the first
-    queries' cluster, more than a segment of 64 keys holds: the keys past it go
+    queries' cluster, more than a segment of 32 keys holds: the keys past it go
     to the spill arrays, and no query to the exact path."""
-    N, d, k, B = 79 * 256, 64, 16, 32
+    N, d, k, B = 139 * 256, 64, 16, 32
     print(f"case Q={Q}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=31 + Q, clusters=12)
     rng = np.random.default_rng(4)
@@ -80,5 +80,34 @@ def test_full_segments_spill(Q):
     ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, B), dtype=torch.uint8, device="cuda")
     ids = check(w, k, "panels", ws)[0]
     stats = sage.predict_stats(ws, Q, N, d, k, B)
-    assert stats["path"] == "filtered" and stats["segment_capacity"] == 64 and stats["flagged"] == 0
+    assert stats["path"] == "filtered" and stats["segment_capacity"] == 32 and stats["flagged"] == 0
     assert np.all((ids[0] >= 300) & (ids[0] < 500))
+
+
+@pytest.mark.parametrize("Q,N,d,k,layout", [
+    (1, 1, 32, 1, "rows"),              # one score
+    (3, 31, 64, 64, "panels"),          # fewer rows than neighbours: padded
+    (32, 1023, 96, 16, "rows"),         # a whole query tile; less than one score per thread
+    (33, 1025, 416, 64, "panels"),      # one query and one row past; 13 panels: two rounds of loads
+    (5, 10000, 768, 128, "rows"),       # two list registers, every fourth thread a group
+    (160, 32768, 32, 129, "panels"),    # the largest store; a group per thread; as many scores as allowed
+    (7, 20011, 64, 256, "rows"),
+])
+def test_dense_search_edges(Q, N, d, k, layout):
+    """Stores small enough that every score is written out."""
+    print(f"case Q={Q} N={N} d={d} k={k} {layout}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=64, seed=Q + N + k, clusters=4)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, 64), dtype=torch.uint8, device="cuda")
+    check(w, k, layout, ws)
+    assert sage.predict_stats(ws, Q, N, d, k, 64)["path"] == "dense"
+
+
+@pytest.mark.parametrize("k", [16, 100, 256])
+def test_dense_search_many_equal_scores(k):
+    """6,000 copies of one row: more keys reach the bound than the select
+    gathers, so every wave folds its keys; the lowest ids come first."""
+    w = workloads.small_predict(Q=9, N=12000, d=64, k=k, B=16, seed=21, clusters=4)
+    w.hist_emb[:6000] = w.hist_emb[6000]
+    w.queries[:4] = w.hist_emb[6000]
+    ids = check(w, k, "rows")[0]
+    assert list(ids[0]) == list(range(k))
