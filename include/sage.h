@@ -455,6 +455,28 @@ int sage_rank(const float* index, int Q, int32_t* order,
               void* workspace, size_t workspace_bytes, sage_stream_t stream);
 
 /*
+ * sage_decide - one scheduling decision for a batch of pending requests, in
+ * one call: the query ingest (for fp32 embeddings), sage_predict_layout,
+ * sage_index on the fused cost, and sage_rank, enqueued in this order on the
+ * stream. Outputs are those of the separate calls.
+ *   queries     [Q, d]: bf16 in SAGE_LAYOUT_ROWS or SAGE_LAYOUT_PANELS, or
+ *               fp32 row-major (SAGE_QUERIES_F32; rounded to bf16 in the
+ *               workspace, in the store's layout)
+ *   prompt_len [Q] int32, bin_repr [B] f64: as in sage_index
+ *   index [Q] f32, order [Q] int32 out; the rest as in sage_predict_layout
+ *   workspace   >= sage_decide_workspace_bytes(query_kind, Q, N, d, k, B) bytes
+ * Errors as in the separate calls; a call that returns SAGE_EINVAL or
+ * SAGE_EWORKSPACE has enqueued nothing. Q = 0 is a no-op.
+ */
+enum { SAGE_QUERIES_F32 = 2 };
+size_t sage_decide_workspace_bytes(int query_kind, int Q, int N, int d, int k, int B);
+int sage_decide(const void* queries, int query_kind, int Q,
+                const uint16_t* hist_emb, int hist_layout, const int32_t* hist_len, int N, int d,
+                int k, float tau, const double* bin_edges, const int32_t* prompt_len, const double* bin_repr, int B,
+                int32_t* nbr_ids, float* nbr_sims, int32_t* counts, float* mass, float* index, int32_t* order,
+                void* workspace, size_t workspace_bytes, sage_stream_t stream);
+
+/*
  * sage_simulate - replay of a request trace against a queue served in a
  * given priority order: a discrete-event simulation run on the HOST (all
  * pointers are host pointers, nothing is enqueued on a stream). It measures

@@ -761,6 +761,81 @@ SAGE_API int sage_rank(const float* index, int Q, int32_t* order, void* workspac
   return hip_status(sage::launch_rank(index, Q, order, workspace, (hipStream_t)stream), "rank launch");
 }
 
+// -------------------------------------------------------------- decide
+namespace {
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+// Workspace of sage_decide: bf16 queries (fp32 input only), predict, rank.
+struct DecideLayout {
+  size_t queries, predict, rank, total;
+  size_t predict_bytes, rank_bytes;
+};
+DecideLayout decide_layout(int query_kind, int Q, int N, int d, int k) {
+  DecideLayout l{};
+  l.predict = query_kind == SAGE_QUERIES_F32 ? align256((size_t)Q * d * sizeof(uint16_t)) : 0;
+  l.predict_bytes = sage::plan_sim_topk(Q, N, d, k).workspace_bytes();
+  l.rank = l.predict + align256(l.predict_bytes);
+  l.rank_bytes = sage::rank_workspace_bytes(Q);
+  l.total = l.rank + l.rank_bytes;
+  return l;
+}
+bool is_query_kind(int kind) {
+  return kind == SAGE_LAYOUT_ROWS || kind == SAGE_LAYOUT_PANELS || kind == SAGE_QUERIES_F32;
+}
+}  // namespace
+
+SAGE_API size_t sage_decide_workspace_bytes(int query_kind, int Q, int N, int d, int k, int B) {
+  std::string keep = g_last_error;
+  if (!is_query_kind(query_kind) || check_predict_sizes(Q, N, d, k, B) != SAGE_OK) return 0;
+  g_last_error = keep;
+  return Q == 0 ? 0 : decide_layout(query_kind, Q, N, d, k).total;
+}
+
+SAGE_API int sage_decide(const void* queries, int query_kind, int Q, const uint16_t* hist_emb, int hist_layout,
+                         const int32_t* hist_len, int N, int d, int k, float tau, const double* bin_edges,
+                         const int32_t* prompt_len, const double* bin_repr, int B, int32_t* nbr_ids, float* nbr_sims,
+                         int32_t* counts, float* mass, float* index, int32_t* order, void* workspace,
+                         size_t workspace_bytes, sage_stream_t stream) {
+  // Everything that the calls below validate, before the first of them.
+  if (!is_query_kind(query_kind)) return fail(SAGE_EINVAL, "query_kind=%d is not a layout or SAGE_QUERIES_F32", query_kind);
+  if (hist_layout != SAGE_LAYOUT_ROWS && hist_layout != SAGE_LAYOUT_PANELS)
+    return fail(SAGE_EINVAL, "layout=%d is not a SAGE_LAYOUT_* value", hist_layout);
+  int st = check_predict_sizes(Q, N, d, k, B);
+  if (st != SAGE_OK) return st;
+  if (Q >= (1 << 29)) return fail(SAGE_EINVAL, "Q=%d not below 2^29", Q);
+  if ((st = check_tau(tau)) != SAGE_OK) return st;
+  if (Q == 0) return ok();
+  if ((st = check_bins(bin_edges, B)) != SAGE_OK) return st;
+  const void* ptrs[] = {queries, hist_emb, hist_len, prompt_len, bin_repr, nbr_ids,
+                        nbr_sims, counts, mass, index, order, workspace};
+  const char* names[] = {"queries", "hist_emb", "hist_len", "prompt_len", "bin_repr", "nbr_ids",
+                         "nbr_sims", "counts", "mass", "index", "order", "workspace"};
+  for (int i = 0; i < 12; ++i) {
+    if (!ptrs[i]) return fail(SAGE_EINVAL, "sage_decide: %s is NULL", names[i]);
+    if (!aligned16(ptrs[i])) return fail(SAGE_EINVAL, "sage_decide: %s is not 16-byte aligned", names[i]);
+  }
+  const DecideLayout l = decide_layout(query_kind, Q, N, d, k);
+  if (workspace_bytes < l.total)
+    return fail(SAGE_EWORKSPACE, "sage_decide: workspace of %zu bytes, %zu needed", workspace_bytes, l.total);
+  char* ws = static_cast<char*>(workspace);
+  const uint16_t* qb = static_cast<const uint16_t*>(queries);
+  int q_layout = query_kind;
+  if (query_kind == SAGE_QUERIES_F32) {
+    uint16_t* dst = reinterpret_cast<uint16_t*>(ws + l.queries);
+    const float* src = static_cast<const float*>(queries);
+    q_layout = hist_layout;
+    st = hist_layout == SAGE_LAYOUT_PANELS ? sage_ingest_bf16_panels(src, Q, d, dst, stream)
+                                           : sage_ingest_bf16(src, (size_t)Q * d, dst, stream);
+    if (st != SAGE_OK) return st;
+    qb = dst;
+  }
+  st = sage_predict_layout(qb, q_layout, Q, hist_emb, hist_layout, hist_len, N, d, k, tau, bin_edges, B, nbr_ids,
+                           nbr_sims, counts, mass, ws + l.predict, l.predict_bytes, stream);
+  if (st != SAGE_OK) return st;
+  st = sage_index(mass, nullptr, prompt_len, bin_repr, Q, B, index, nullptr, stream);
+  if (st != SAGE_OK) return st;
+  return sage_rank(index, Q, order, ws + l.rank, l.rank_bytes, stream);
+}
+
 // ------------------------------------------------------------ simulate
 SAGE_API int sage_simulate(const double* arrival, const int32_t* prompt_len, const int32_t* output_len,
                            int R, const int32_t* order, int levels, int informed, int bucket,

@@ -62,6 +62,8 @@ def load_library():
         "sage_length_index": (I, [P, I, I, P, P, P, P, Z, S]),
         "sage_predict_by_length": (I, [P, I, P, P, P, I, P, I, I, F, P, I, P, P, P, P, S]),
         "sage_debug_theta_floor": (I, [F]),
+        "sage_decide_workspace_bytes": (Z, [I, I, I, I, I, I]),
+        "sage_decide": (I, [P, I, I, P, I, P, I, I, I, F, P, P, P, I, P, P, P, P, P, P, P, Z, S]),
         "sage_status_string": (ctypes.c_char_p, [I]),
         "sage_last_error": (ctypes.c_char_p, []),
         "sage_timer_create": (I, [I, ctypes.POINTER(P)]),
@@ -88,7 +90,9 @@ def _check(status: int):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # The current device's current stream as its raw handle (the Stream object
+    # around it costs 2.5 us a call).
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -513,8 +517,63 @@ class Store:
         return predict(queries, self.hist_emb, self.hist_len, self.k, self.tau, self.bin_edges,
                        workspace=self._workspace(Q), out=out)
 
+    # decide() may use sage_decide: false for a subclass with a predict of its own.
+    _one_call = True
+
+    def __init_subclass__(cls, **kwargs):
+        super().__init_subclass__(**kwargs)
+        if "predict" in cls.__dict__ and "_one_call" not in cls.__dict__:
+            cls._one_call = False
+
+    def _decide_once(self, queries: torch.Tensor, f32: bool, prompt_len: torch.Tensor, out):
+        """decide() as one library call, or None where a check of the separate
+        calls would not pass (they then raise their own errors)."""
+        if f32:
+            (Q, d), kind = queries.shape, 2
+        else:
+            Q, d, kind = emb_shape(queries)
+        N, d_h, h_layout = emb_shape(self.hist_emb)
+        edges, repr_, lens = self.bin_edges, self.bin_repr, self.hist_len
+        B = edges.shape[0] - 1
+        if f32 and h_layout != LAYOUTS[self.layout]:
+            return None                                  # the separate calls ingest in the store's declared layout
+        for t, dtype, ndim in ((self.hist_emb, torch.bfloat16, None), (lens, torch.int32, 1),
+                               (edges, torch.float64, 1), (repr_, torch.float64, 1), (prompt_len, torch.int32, 1),
+                               (queries, queries.dtype, None)):
+            if not t.is_cuda or t.dtype != dtype or not t.is_contiguous() or (ndim is not None and t.dim() != ndim):
+                return None
+        if d != d_h or lens.shape[0] != N or prompt_len.shape[0] != Q or repr_.shape[0] != B:
+            return None
+        lib = load_library()
+        need = lib.sage_decide_workspace_bytes(kind, Q, N, d, self.k, B)
+        if self._ws.numel() < need:
+            self._ws = torch.empty(need, dtype=torch.uint8, device=self.hist_emb.device)
+        dev, k = queries.device, self.k
+        if out is None:
+            out = (torch.empty((Q, k), dtype=torch.int32, device=dev), torch.empty((Q, k), dtype=torch.float32, device=dev),
+                   torch.empty((Q, B), dtype=torch.int32, device=dev), torch.empty((Q, B), dtype=torch.float32, device=dev),
+                   torch.empty(Q, dtype=torch.float32, device=dev), torch.empty(Q, dtype=torch.int32, device=dev))
+        ids, sims, counts, mass, g, order = out[:6]
+        _check(lib.sage_decide(queries.data_ptr(), kind, Q, self.hist_emb.data_ptr(), h_layout, lens.data_ptr(), N, d, k,
+                               self.tau, edges.data_ptr(), prompt_len.data_ptr(), repr_.data_ptr(), B, ids.data_ptr(),
+                               sims.data_ptr(), counts.data_ptr(), mass.data_ptr(), g.data_ptr(), order.data_ptr(),
+                               self._ws.data_ptr(), self._ws.numel(), _stream()))
+        return ids, sims, counts, mass, g, order
+
     def decide(self, queries: torch.Tensor, prompt_len: torch.Tensor, out=None):
-        """One scheduling decision for a batch: predict, cost+index, rank."""
+        """One scheduling decision for a batch: predict, cost+index, rank.
+
+        One library call (sage_decide) where the inputs are in the forms that
+        it takes; other forms go through the separate calls, which convert or
+        reject them."""
+        f32 = isinstance(queries, torch.Tensor) and queries.dtype == torch.float32
+        if (self._one_call and (f32 or (isinstance(queries, torch.Tensor) and queries.dtype == torch.bfloat16))
+                and queries.is_cuda and queries.dim() == (2 if f32 or queries.dim() != 3 else 3)
+                and isinstance(prompt_len, torch.Tensor)):
+            queries = queries.contiguous() if f32 else queries
+            res = self._decide_once(queries, f32, prompt_len, out)
+            if res is not None:
+                return res
         ids, sims, counts, mass = self.predict(queries, out=None if out is None else out[:4])
         g = index(mass, prompt_len, self.bin_repr, out=None if out is None else out[4])
         Q = g.shape[0]
@@ -563,10 +622,15 @@ class RingStore(Store):
         self.hist_emb = self.ring_emb[:self.rows]
         self.hist_len = self.ring_len[:self.rows]
 
+    _one_call = True
+
     def predict(self, queries: torch.Tensor, out=None):
         if self.total == 0:
             raise SageError("the history window is empty")
         return super().predict(queries, out=out)
+
+    def _decide_once(self, queries, f32, prompt_len, out):
+        return None if self.total == 0 else super()._decide_once(queries, f32, prompt_len, out)
 
 
 class Queue:

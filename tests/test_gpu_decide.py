@@ -1,0 +1,70 @@
+"""sage_decide: a whole decision (ingest, predict, index, rank) in one call gives
+the separate calls' bits, for every form of the queries and the store that it
+takes; forms that it does not take go through the separate calls."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_07917_amd import sage, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def same(a, b):
+    torch.cuda.synchronize()
+    return all(x.dtype == y.dtype and torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip(a, b))
+
+
+def separate(store, queries, plen):
+    pred = store.predict(queries)
+    g = sage.index(pred[3], plen, store.bin_repr)
+    return (*pred, g, sage.rank(g))
+
+
+@pytest.mark.parametrize("Q,N,k", [(1, 900, 8), (9, 50000, 64), (33, 3000, 100), (300, 40000, 64), (9000, 2000, 16)])
+@pytest.mark.parametrize("layout", ["rows", "panels"])
+def test_decide_equals_the_separate_calls(Q, N, k, layout):
+    w = workloads.small_predict(Q=Q, N=N, d=96, k=k, B=64, seed=Q + N, clusters=6)
+    store = sage.Store(dev(w.hist_emb), dev(w.hist_len), dev(w.bin_edges), dev(w.bin_repr), k, layout=layout)
+    qf, plen = dev(w.queries), dev(w.prompt_len)
+    want = separate(store, qf, plen)
+    wide = torch.zeros((Q, 128), device="cuda")
+    wide[:, :96] = qf
+    forms = [qf, sage.ingest_bf16(qf), sage.ingest_bf16(qf, "panels"), wide[:, :96]]      # the last: not contiguous
+    for q in forms:
+        assert same(store.decide(q, plen), want)
+    out = [torch.full_like(t, 7) for t in want]
+    got = store.decide(qf, plen, out=out)
+    assert all(a is b for a, b in zip(got, out)) and same(out, want)
+    # a store in the other layout than the one declared: the separate calls
+    other = sage.Store(sage.ingest_bf16(dev(w.hist_emb), "panels" if layout == "rows" else "rows"), dev(w.hist_len),
+                       dev(w.bin_edges), dev(w.bin_repr), k, layout=layout)
+    assert same(other.decide(qf, plen), want)
+
+
+def test_decide_keeps_errors_and_overrides():
+    w = workloads.small_predict(Q=4, N=500, d=64, k=8, B=16, seed=2, clusters=3)
+    store = sage.Store(dev(w.hist_emb), dev(w.hist_len), dev(w.bin_edges), dev(w.bin_repr), 8)
+    qf, plen = dev(w.queries), dev(w.prompt_len)
+    for q, p in ((qf, plen[:3]), (qf.cpu(), plen), (qf, plen.long()), (qf[:, :32], plen), (qf.double(), plen)):
+        with pytest.raises(sage.SageError):
+            store.decide(q, p)
+    ring = sage.RingStore(100, 64, dev(w.bin_edges), dev(w.bin_repr), 8)
+    with pytest.raises(sage.SageError, match="empty"):
+        ring.decide(qf, plen)
+    ring.insert(dev(w.hist_emb[:300]), dev(w.hist_len[:300]))
+    assert same(ring.decide(qf, plen), separate(ring, qf, plen))
+
+    class Mine(sage.Store):
+        def predict(self, queries, out=None):
+            self.called = True
+            return super().predict(queries, out=out)
+
+    mine = Mine(dev(w.hist_emb), dev(w.hist_len), dev(w.bin_edges), dev(w.bin_repr), 8)
+    assert same(mine.decide(qf, plen), store.decide(qf, plen)) and mine.called
+    empty = store.decide(qf[:0], plen[:0])
+    assert [t.shape[0] for t in empty] == [0] * 6
