@@ -25,16 +25,19 @@
 // The records above sigma* (fewer than k) are one contiguous range of the
 // sorted positions; those at sigma* sit in at most one length run on each
 // side, each sorted by index, so the lowest indices are the first ones of
-// each run. At most 2k keys (similarity bits, ~index) are then sorted in
-// LDS and the first k written.
+// each run. At most 2k keys (similarity bits, ~index) then go through the
+// wave's running list, whose first k are written (4,096 queries against
+// 262,144 records at k = 64: 38.2 us with binary searches for the ends of a
+// level's interval and a bitonic sort in LDS, 18.7 us so).
 #include "sage_device.hpp"
 #include "sage_internal.hpp"
+#include "sage_toplist.hpp"
 
 namespace sage {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxKeys = 512;                      // 2 SAGE_MAX_K
+constexpr int kMaxNeighbours = 256;                // SAGE_MAX_K
 
 __device__ __forceinline__ int clamp_len(int L, int max_len) { return min(max(L, 1), max_len); }
 
@@ -45,23 +48,24 @@ __device__ __forceinline__ float len_sim(int I, int L) {
 }
 
 // [Lmin, Lmax] of lengths in [1, max_len] with len_sim >= sigma; Lmin > Lmax
-// when none. P = min(I, max_len) has the largest similarity.
+// when none. P = min(I, max_len) has the largest similarity. The similarity
+// is monotone on each side of I, so each end is found from an estimate (sigma I
+// and I / sigma, off by one at most where lengths are exact in fp32) by single
+// steps under the similarity itself: about four quotients, where two binary
+// searches over the lengths take 26.
 __device__ __forceinline__ int2 level_range(float sigma, int I, int max_len) {
   const int P = min(I, max_len);
   if (!(len_sim(I, P) >= sigma)) return make_int2(1, 0);
-  int lo = 1, hi = P;                              // smallest L in [1, P] with s >= sigma
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (len_sim(I, mid) >= sigma) hi = mid; else lo = mid + 1;
-  }
-  const int lmin = lo;
-  lo = P;
-  hi = max_len;                                    // largest L in [P, max_len] with s >= sigma
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (len_sim(I, mid) >= sigma) lo = mid; else hi = mid - 1;
-  }
-  return make_int2(lmin, lo);
+  const float fI = (float)I;
+  int lo = (int)fminf(ceilf(sigma * fI), (float)P);          // smallest L in [1, P] with s >= sigma
+  lo = min(max(lo, 1), P);
+  while (lo < P && !(len_sim(I, lo) >= sigma)) ++lo;
+  while (lo > 1 && len_sim(I, lo - 1) >= sigma) --lo;
+  int hi = (int)fminf(floorf(fI / sigma), (float)max_len);   // largest L in [P, max_len] with s >= sigma
+  hi = min(max(hi, P), max_len);
+  while (hi > P && !(len_sim(I, hi) >= sigma)) --hi;
+  while (hi < max_len && len_sim(I, hi + 1) >= sigma) ++hi;
+  return make_int2(lo, hi);
 }
 
 __device__ __forceinline__ int count_range(const int32_t* off, int2 r) {
@@ -92,16 +96,16 @@ __global__ void length_offsets_kernel(const int32_t* __restrict__ sorted_len, in
   off[L] = lo;
 }
 
+template <int S>
 __global__ void __launch_bounds__(kThreads) length_neighbours_kernel(
     const int32_t* __restrict__ prompt_len, int Q, const int32_t* __restrict__ by_len,
     const int32_t* __restrict__ sorted_len, const int32_t* __restrict__ off, int max_len, int N, int k,
     int32_t* __restrict__ ids, float* __restrict__ sims) {
-  __shared__ uint64_t keys_s[kThreads / kWave][kMaxKeys];
+  __shared__ uint64_t pend[kThreads / kWave][2 * kWave];
   const int lane = (int)lane_id();
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = blockIdx.x * (kThreads / kWave) + w;
   if (q >= Q) return;                               // whole wavefronts; no workgroup barrier below
-  uint64_t* keys = keys_s[w];
   const int I = max(prompt_len[q], 1);
   const int total = off[max_len + 1] - off[1];      // every record (lengths are clamped to [1, max_len])
 
@@ -147,34 +151,18 @@ __global__ void __launch_bounds__(kThreads) length_neighbours_kernel(
   // Gather the keys: the range above sigma*, then the first r of each run.
   const int n_mid = me - mb, n_l = min(r, le - lb), n_r = min(r, re - rb);
   const int n_keys = n_mid + n_l + n_r;             // <= 2k (or every record when total <= k)
-  int n_pow = kWave;                               // a power of two holding the keys and the k outputs
-  while (n_pow < n_keys || n_pow < k) n_pow <<= 1;
-  for (int i = lane; i < n_pow; i += kWave) {
+  TopList<S> top(pend[w]);
+  for (int i0 = 0; i0 < n_keys; i0 += kWave) {
+    const int i = i0 + lane;
     uint64_t key = kPadKey;
     if (i < n_keys) {
       const int p = i < n_mid ? mb + i : (i < n_mid + n_l ? lb + (i - n_mid) : rb + (i - n_mid - n_l));
       key = make_key(len_sim(I, sorted_len[p]), (uint32_t)by_len[p]);
     }
-    keys[i] = key;
+    top.take(key);
   }
-  __builtin_amdgcn_wave_barrier();
-  // Bitonic sort of the n_pow keys in LDS, descending (one wave).
-  for (int size = 2; size <= n_pow; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = lane; i < n_pow / 2; i += kWave) {
-        const int a = 2 * stride * (i / stride) + (i % stride), b = a + stride;
-        const bool desc = (a & size) == 0;
-        const uint64_t x = keys[a], y = keys[b];
-        if ((x < y) == desc) { keys[a] = y; keys[b] = x; }
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-  }
-  for (int i = lane; i < k; i += kWave) {
-    const uint64_t key = keys[i];
-    ids[(size_t)q * k + i] = key == kPadKey ? -1 : key_id(key);
-    sims[(size_t)q * k + i] = key == kPadKey ? -__builtin_inff() : key_sim(key);
-  }
+  top.flush();
+  top.write(k, ids + (size_t)q * k, sims + (size_t)q * k);
 }
 
 }  // namespace
@@ -203,10 +191,18 @@ hipError_t launch_length_neighbours(const int32_t* prompt_len, int Q, const int3
                                     const int32_t* sorted_len, const int32_t* off, int max_len, int N, int k,
                                     int32_t* ids, float* sims, hipStream_t stream) {
   if (Q == 0) return hipSuccess;
-  if (k > kMaxKeys / 2) return hipErrorInvalidValue;
+  if (k > kMaxNeighbours) return hipErrorInvalidValue;
   LaunchScope scope("length_neighbours", stream);
-  hipLaunchKernelGGL(length_neighbours_kernel, dim3((Q + 3) / 4), dim3(kThreads), 0, stream, prompt_len, Q, by_len,
-                     sorted_len, off, max_len, N, k, ids, sims);
+  const dim3 grid((Q + 3) / 4);
+  if (k <= 64)
+    hipLaunchKernelGGL(length_neighbours_kernel<1>, grid, dim3(kThreads), 0, stream, prompt_len, Q, by_len, sorted_len,
+                       off, max_len, N, k, ids, sims);
+  else if (k <= 128)
+    hipLaunchKernelGGL(length_neighbours_kernel<2>, grid, dim3(kThreads), 0, stream, prompt_len, Q, by_len, sorted_len,
+                       off, max_len, N, k, ids, sims);
+  else
+    hipLaunchKernelGGL(length_neighbours_kernel<4>, grid, dim3(kThreads), 0, stream, prompt_len, Q, by_len, sorted_len,
+                       off, max_len, N, k, ids, sims);
   return hipGetLastError();
 }
 
