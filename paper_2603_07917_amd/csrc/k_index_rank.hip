@@ -337,7 +337,10 @@ hipError_t launch_index_c(const float* mass, const float* cost, const int32_t* p
 // Rank: stable least-significant-digit radix sort of the index keys (fp32
 // bits made monotone, -0 folded onto +0), 8-bit digits, 4 passes. Each pass:
 // per-tile digit counts, one exclusive scan over (digit, tile), then a stable
-// scatter where each wave ranks equal digits with ballots.
+// scatter where each wave ranks equal digits of its own quarter of the tile
+// with ballots (three barriers a tile; with three for every 256 requests and
+// the scatter's own sum of the counts, 1.34 M keys took 14.4 us a scatter, now
+// 11.7, and 131,073 keys 88 us in all, now 54).
 // ---------------------------------------------------------------------------
 constexpr int kRankThreads = 256;
 constexpr int kRankItems = 8;
@@ -360,16 +363,21 @@ __global__ void __launch_bounds__(kRankThreads) rank_hist_kernel(const float* __
 #pragma unroll
   for (int it = 0; it < kRankItems; ++it) {
     const int i = base + it * kRankThreads + threadIdx.x;
-    if (i < Q) {
-      const uint32_t key = k_in ? k_in[i] : index_key(g_in[i]);
-      atomicAdd(&cnt[(key >> shift) & 255u], 1u);
+    const bool in = i < Q;
+    const uint32_t digit = in ? ((k_in ? k_in[i] : index_key(g_in[i])) >> shift) & 255u : 256u;
+    // A wave of one digit (runs of equal keys: exhausted requests at +inf)
+    // counts it once; 64 atomics on one word would queue up.
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)digit);
+    if (__all(digit == d0)) {
+      if (d0 < 256u && lane_id() == 0) atomicAdd(&cnt[d0], (uint32_t)kWave);
+    } else if (in) {
+      atomicAdd(&cnt[digit], 1u);
     }
   }
   __syncthreads();
   hist[threadIdx.x * n_tiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
-// Exclusive scan of n entries in one workgroup of 1024 threads.
 // Per-digit exclusive scan over the tiles: workgroup d scans hist[d][0..n_tiles)
 // in place (contiguous, 256 counts per turn) and leaves the digit's total in
 // total[d]. The scatter adds the exclusive scan of the 256 totals.
@@ -404,61 +412,51 @@ __global__ void __launch_bounds__(256) rank_scan_kernel(uint32_t* __restrict__ h
 __global__ void __launch_bounds__(kRankThreads) rank_scatter_kernel(
     const float* __restrict__ g_in, const uint32_t* __restrict__ k_in,
     const uint32_t* __restrict__ v_in, int Q, int shift, int n_tiles,
-    const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ digit_total, int fused,
+    const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ digit_total,
     uint32_t* __restrict__ k_out, uint32_t* __restrict__ v_out) {
   constexpr int kWaves = kRankThreads / kWave;
   __shared__ uint32_t base_off[256];
-  __shared__ uint32_t running[256];
-  __shared__ uint32_t wave_cnt[kWaves][256];
+  __shared__ uint32_t wtot[kWaves];
+  __shared__ uint32_t cnt[kWaves][256];
   const int t = threadIdx.x;
   const int lane = (int)lane_id();
-  const int w = t / kWave;
+  const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+  // Wave w owns the w-th quarter of the tile (kRankItems turns of 64 requests,
+  // in order): it ranks its requests among its own by digit with no barrier,
+  // and the waves' counts are combined once.
+  const int first = blockIdx.x * kRankTile + w * (kRankItems * kWave) + lane;
+  uint32_t key[kRankItems], val[kRankItems];
+#pragma unroll
+  for (int it = 0; it < kRankItems; ++it) {
+    const int i = first + it * kWave;
+    const bool valid = i < Q;
+    key[it] = valid ? (k_in ? k_in[i] : index_key(g_in[i])) : 0u;
+    val[it] = valid ? (v_in ? v_in[i] : (uint32_t)i) : 0u;
+  }
+  // Exclusive scan of the 256 digit totals (one per thread), plus this tile's
+  // offset within the digit.
   {
-    // exclusive scan of the 256 digit totals (one per thread), plus this
-    // tile's offset within the digit. `fused` (few tiles): both from the raw
-    // per-tile counts, offsets[digit][tile], read here (no scan kernel).
-    uint32_t v, tile_off;
-    if (fused) {
-      const uint32_t* row = offsets + (size_t)t * n_tiles;
-      v = 0;
-      tile_off = 0;
-      for (int i = 0; i < n_tiles; ++i) {
-        const uint32_t c = row[i];
-        if (i == (int)blockIdx.x) tile_off = v;
-        v += c;
-      }
-    } else {
-      v = digit_total[t];
-      tile_off = offsets[t * n_tiles + blockIdx.x];
-    }
+    const uint32_t v = digit_total[t], tile_off = offsets[t * n_tiles + blockIdx.x];
     uint32_t incl = v;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
       const uint32_t y = (uint32_t)__shfl_up((int)incl, o, kWave);
       if (lane >= o) incl += y;
     }
-    if (lane == kWave - 1) running[w] = incl;           // wave totals (running is reset below)
+    if (lane == kWave - 1) wtot[w] = incl;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) cnt[i][t] = 0;
     __syncthreads();
     uint32_t before = 0;
-    for (int ww = 0; ww < w; ++ww) before += running[ww];
+    for (int ww = 0; ww < w; ++ww) before += wtot[ww];
     base_off[t] = before + incl - v + tile_off;
-    __syncthreads();
   }
-  running[t] = 0;
-#pragma unroll
-  for (int i = 0; i < kWaves; ++i) wave_cnt[i][t] = 0;
-  __syncthreads();
-  const int tile0 = blockIdx.x * kRankTile;
   const uint64_t lt_mask = (1ull << lane) - 1ull;
+  uint32_t rank[kRankItems];                       // among the wave's requests of the same digit
+#pragma unroll
   for (int it = 0; it < kRankItems; ++it) {
-    const int i = tile0 + it * kRankThreads + t;
-    const bool valid = i < Q;
-    uint32_t key = 0, val = 0;
-    if (valid) {
-      key = k_in ? k_in[i] : index_key(g_in[i]);
-      val = v_in ? v_in[i] : (uint32_t)i;
-    }
-    const uint32_t digit = (key >> shift) & 255u;
+    const bool valid = first + it * kWave < Q;
+    const uint32_t digit = (key[it] >> shift) & 255u;
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) {
@@ -466,24 +464,29 @@ __global__ void __launch_bounds__(kRankThreads) rank_scatter_kernel(
       const uint64_t m = __ballot(on);
       peers &= on ? m : ~m;
     }
-    const uint32_t rank_in_wave = (uint32_t)__popcll(peers & lt_mask);
-    if (valid && rank_in_wave == 0) wave_cnt[w][digit] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    uint32_t pos = 0;
-    if (valid) {
-      pos = base_off[digit] + running[digit] + rank_in_wave;
-      for (int ww = 0; ww < w; ++ww) pos += wave_cnt[ww][digit];
-    }
-    __syncthreads();
-    uint32_t add = 0;
+    const uint32_t seen = cnt[w][digit];           // LDS operations of a wave complete in order
+    rank[it] = seen + (uint32_t)__popcll(peers & lt_mask);
+    __builtin_amdgcn_wave_barrier();
+    if (valid && (peers & lt_mask) == 0) cnt[w][digit] = seen + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  {
+    uint32_t run = base_off[t];                    // counts -> first positions, wave by wave
 #pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) { add += wave_cnt[ww][t]; wave_cnt[ww][t] = 0; }
-    running[t] += add;
-    if (valid) {
-      if (k_out) k_out[pos] = key;
-      v_out[pos] = val;
+    for (int ww = 0; ww < kWaves; ++ww) {
+      const uint32_t c = cnt[ww][t];
+      cnt[ww][t] = run;
+      run += c;
     }
-    __syncthreads();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kRankItems; ++it) {
+    if (first + it * kWave >= Q) continue;
+    const uint32_t pos = cnt[w][(key[it] >> shift) & 255u] + rank[it];
+    if (k_out) k_out[pos] = key[it];
+    v_out[pos] = val[it];
   }
 }
 
@@ -756,9 +759,6 @@ hipError_t launch_rank(const float* index, int Q, int32_t* order, void* ws, hipS
   uint32_t* vB = kB + Q;
   uint32_t* hist = vB + Q;
   uint32_t* totals = hist + 256 * (size_t)n_tiles;
-  // With few tiles each scatter workgroup sums the per-tile counts itself
-  // (n_tiles loads per digit) and the scan launch is skipped.
-  const bool fused = n_tiles <= 64;
   const uint32_t* k_in = nullptr;
   const uint32_t* v_in = nullptr;
   for (int pass = 0; pass < 4; ++pass) {
@@ -771,14 +771,14 @@ hipError_t launch_rank(const float* index, int Q, int32_t* order, void* ws, hipS
       hipLaunchKernelGGL(rank_hist_kernel, dim3(n_tiles), dim3(kRankThreads), 0, stream, index, k_in,
                          Q, shift, n_tiles, hist);
     }
-    if (!fused) {
+    {
       LaunchScope scope("rank_scan", stream);
       hipLaunchKernelGGL(rank_scan_kernel, dim3(256), dim3(256), 0, stream, hist, n_tiles, totals);
     }
     {
       LaunchScope scope("rank_scatter", stream);
       hipLaunchKernelGGL(rank_scatter_kernel, dim3(n_tiles), dim3(kRankThreads), 0, stream, index,
-                         k_in, v_in, Q, shift, n_tiles, hist, totals, fused ? 1 : 0, k_out, v_out);
+                         k_in, v_in, Q, shift, n_tiles, hist, totals, k_out, v_out);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
