@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "sage_device.hpp"
+#include "sage_hist.hpp"
 #include "sage_internal.hpp"
 #include "sage_toplist.hpp"
 
@@ -72,9 +73,14 @@ __global__ void __launch_bounds__(256, 2) dense_score_kernel(EmbView queries, in
 // (1.15 k at k = 64) reach it. They are gathered in LDS, sorted 64 to a wave
 // and merged (as in the candidate select). Where more than the LDS holds reach
 // T (equal scores), every wave folds all of its keys instead: slower, exact.
+//
+// With counts, the neighbours then go through the histogram in place (as in
+// the histogram kernel: exact fixed-point weights, so the same bits), which
+// saves its launch.
 template <int S, int kPer>
 __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restrict__ scores, int N, int ld, int k,
-                                                            int32_t* __restrict__ ids, float* __restrict__ sims) {
+                                                            int32_t* __restrict__ ids, float* __restrict__ sims,
+                                                            DenseHist h) {
   constexpr int KL = 64 * S;
   constexpr int W = 16;
   constexpr int kCap = 1024;
@@ -84,7 +90,13 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
   __shared__ uint64_t cand[kCap];
   __shared__ uint32_t gmax[64 * kGroups];
   __shared__ uint32_t bound;
-  __shared__ int n_cand;
+  __shared__ int n_cand, n_nbr;
+  __shared__ uint64_t w_all;
+  // Histogram (8-byte words): weights [B], edges [B + 1], then counts [B] (4-byte).
+  extern __shared__ __align__(16) unsigned char hist_smem[];
+  uint64_t* wsum = reinterpret_cast<uint64_t*>(hist_smem);
+  double* edges = reinterpret_cast<double*>(hist_smem) + h.B;
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(edges + h.B + 1);
   const int q = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = (int)lane_id();
@@ -107,7 +119,18 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
   } else {
     gmax[tid] = m;
   }
-  if (tid == 0) n_cand = 0;
+  if (tid == 0) {
+    n_cand = 0;
+    n_nbr = 0;
+    w_all = 0;
+  }
+  for (int b = tid; b <= h.B; b += 1024) {          // no histogram: B = -1
+    edges[b] = h.edges[b];
+    if (b < h.B) {
+      wsum[b] = 0;
+      cnt[b] = 0;
+    }
+  }
   __syncthreads();
   if (w == 0) {
     uint32_t key[kGroups], hi = 0, lo = 0xffffffffu;
@@ -157,26 +180,64 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
   top.flush();
   merge_lists<S, W>(top.lv, &lists[0][0], w, n <= kCap ? (n + kWave - 1) / kWave : W);
   if (w == 0) top.write(k, ids + (size_t)q * k, sims + (size_t)q * k);
+  if (h.B < 1) return;
+  if (w == 0) {
+    int32_t len[S];
+    bool in[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      in[s] = 64 * s + lane < k && top.lv[s] != kPadKey;
+      len[s] = in[s] ? h.hist_len[key_id(top.lv[s])] : 0;
+    }
+    uint64_t mine_w = 0;
+    int mine_n = 0;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      if (in[s]) {
+        const int b = length_bin(edges, h.B, len[s]);
+        const float sim = key_sim(top.lv[s]);
+        atomicAdd(&cnt[b], 1u);
+        ++mine_n;
+        if (sim >= h.tau) {
+          const uint64_t fx = weight_fixed(sim, false);
+          atomicAdd(reinterpret_cast<unsigned long long*>(&wsum[b]), (unsigned long long)fx);
+          mine_w += fx;
+        }
+      }
+    if (mine_n > 0) {
+      atomicAdd(&n_nbr, mine_n);
+      atomicAdd(reinterpret_cast<unsigned long long*>(&w_all), (unsigned long long)mine_w);
+    }
+  }
+  __syncthreads();
+  const uint64_t wtot = w_all;
+  const bool weighted = wtot > 0;
+  const double scale = weighted ? 1.0 / (double)wtot : (n_nbr > 0 ? 1.0 / (double)n_nbr : 0.0);
+  for (int b = tid; b < h.B; b += 1024) {
+    h.counts[(size_t)q * h.B + b] = (int32_t)cnt[b];
+    h.mass[(size_t)q * h.B + b] = (float)((weighted ? (double)wsum[b] : (double)cnt[b]) * scale);
+  }
 }
 
 template <int S>
 void launch_dense_select(const float* scores, int Q, int N, int ld, int k, int32_t* ids, float* sims,
-                         hipStream_t stream) {
+                         const DenseHist& h, hipStream_t stream) {
+  const size_t lds = h.B > 0 ? (size_t)h.B * 20 + 8 : 0;
   if (N <= 8192)
-    hipLaunchKernelGGL((dense_select_kernel<S, 8>), dim3(Q), dim3(1024), 0, stream, scores, N, ld, k, ids, sims);
+    hipLaunchKernelGGL((dense_select_kernel<S, 8>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ids, sims, h);
   else if (N <= 16384)
-    hipLaunchKernelGGL((dense_select_kernel<S, 16>), dim3(Q), dim3(1024), 0, stream, scores, N, ld, k, ids, sims);
+    hipLaunchKernelGGL((dense_select_kernel<S, 16>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ids, sims, h);
   else
-    hipLaunchKernelGGL((dense_select_kernel<S, 32>), dim3(Q), dim3(1024), 0, stream, scores, N, ld, k, ids, sims);
+    hipLaunchKernelGGL((dense_select_kernel<S, 32>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ids, sims, h);
 }
 static_assert(kDenseMaxRows == 32 * 1024, "the last case holds the largest store");
 
 }  // namespace
 
 hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
-                        int32_t* ids, float* sims, hipStream_t stream) {
+                        int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream) {
   if (Q <= 0 || N <= 0 || N > kDenseMaxRows || ld < N || k < 1 || k > 256 || d % 32 != 0 ||
-      d > kDenseMaxD) return hipErrorInvalidValue;
+      d > kDenseMaxD || h.B > kDenseHistMaxBins) return hipErrorInvalidValue;
   {
     LaunchScope scope("sim_topk", stream);
     // Single-wave workgroups while the waves are fewer than the chip's SIMDs:
@@ -185,10 +246,10 @@ hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int 
     hipLaunchKernelGGL(dense_score_kernel, dim3((N + 32 * per - 1) / (32 * per), (Q + 31) / 32), dim3(kWave * per), 0,
                        stream, queries, Q, hist, N, d, ld, scores);
   }
-  LaunchScope scope("topk_select", stream);
-  if (k <= 64) launch_dense_select<1>(scores, Q, N, ld, k, ids, sims, stream);
-  else if (k <= 128) launch_dense_select<2>(scores, Q, N, ld, k, ids, sims, stream);
-  else launch_dense_select<4>(scores, Q, N, ld, k, ids, sims, stream);
+  LaunchScope scope(h.B > 0 ? "hist" : "topk_select", stream);   // the histogram ends it, where it is part
+  if (k <= 64) launch_dense_select<1>(scores, Q, N, ld, k, ids, sims, h, stream);
+  else if (k <= 128) launch_dense_select<2>(scores, Q, N, ld, k, ids, sims, h, stream);
+  else launch_dense_select<4>(scores, Q, N, ld, k, ids, sims, h, stream);
   return hipGetLastError();
 }
 

@@ -1,28 +1,13 @@
 // Predicted output-length distribution of each request from its neighbours:
 // counts per log-spaced length bin and the similarity-weighted mass.
 #include "sage_device.hpp"
+#include "sage_hist.hpp"
 #include "sage_internal.hpp"
 
 #include <algorithm>
 
 namespace sage {
 namespace {
-
-// Fixed-point scale for the weights: every fp32 weight >= 2^-20 is an integer
-// multiple of 2^-43, so w * 2^43 is an exact integer; weights below 2^11 keep
-// a sum of up to 256 of them below 2^63. Integer sums are order independent.
-constexpr double kWeightScale = 8796093022208.0;  // 2^43
-
-// Largest b in [0, B-1] with edges[b] <= L (0 when L < edges[0]); edges in LDS.
-__device__ __forceinline__ int length_bin(const double* edges, int B, int L) {
-  const double x = (double)L;
-  int lo = 0, hi = B;   // invariant: edges[lo] <= x or lo == 0; the answer is < hi
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (edges[mid] <= x) lo = mid; else hi = mid;
-  }
-  return lo;
-}
 
 constexpr int kMaxNbr = 256;   // SAGE_MAX_K
 
@@ -82,7 +67,7 @@ __global__ void __launch_bounds__(64 * QPB * WPR) hist_kernel(
     atomicAdd(&cnt[b], 1u);
     ++m;
     if (sim[j] >= tau) {
-      const uint64_t fx = (uint64_t)((uniform ? 1.0 : (double)sim[j]) * kWeightScale);
+      const uint64_t fx = weight_fixed(sim[j], uniform);
       atomicAdd(reinterpret_cast<unsigned long long*>(&wsum[b]), (unsigned long long)fx);
       wtot += fx;
     }
@@ -192,7 +177,7 @@ __global__ void __launch_bounds__(256) hist_wave_kernel(
       atomicAdd(&cnt[b], 1u);
       ++m;
       if (sim_a[j] >= tau) {
-        const uint64_t fx = (uint64_t)((uniform ? 1.0 : (double)sim_a[j]) * kWeightScale);
+        const uint64_t fx = weight_fixed(sim_a[j], uniform);
         atomicAdd(reinterpret_cast<unsigned long long*>(&wsum[b]), (unsigned long long)fx);
         wtot += fx;
       }

@@ -1205,12 +1205,12 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
 
 hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d, int k,
                              const SimTopkPlan& p, void* workspace, int32_t* ids, float* sims,
-                             hipStream_t stream) {
+                             const DenseHist& hist_part, hipStream_t stream) {
   if (Q == 0) return hipSuccess;
   char* ws = static_cast<char*>(workspace);
   if (p.dense)
     return launch_dense(queries, Q, hist, N, d, k, p.dense_ld, reinterpret_cast<float*>(ws + p.off_scores), ids, sims,
-                        stream);
+                        hist_part, stream);
   uint64_t* partial = reinterpret_cast<uint64_t*>(ws + p.off_partial);
   uint64_t* merge_lists = reinterpret_cast<uint64_t*>(ws + p.off_merge);
   float* gm = reinterpret_cast<float*>(ws + p.off_gm);

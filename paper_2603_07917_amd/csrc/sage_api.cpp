@@ -362,8 +362,18 @@ SAGE_API int sage_predict_layout(const uint16_t* queries, int query_layout, int 
                                                               : sage::rows_view(queries, d);
   const sage::EmbView hv = hist_layout == SAGE_LAYOUT_PANELS ? sage::panels_view(hist_emb, N)
                                                              : sage::rows_view(hist_emb, d);
-  hipError_t e = sage::launch_neighbours(qv, Q, hv, N, d, k, plan, workspace, nbr_ids, nbr_sims, s);
+  sage::DenseHist part;
+  if (plan.dense && B <= sage::kDenseHistMaxBins) {
+    part.hist_len = hist_len;
+    part.tau = tau;
+    part.edges = bin_edges;
+    part.B = B;
+    part.counts = counts;
+    part.mass = mass;
+  }
+  hipError_t e = sage::launch_neighbours(qv, Q, hv, N, d, k, plan, workspace, nbr_ids, nbr_sims, part, s);
   if (e != hipSuccess) return hip_status(e, "neighbour search launch");
+  if (part.B > 0) return ok();
   e = sage::launch_hist(nbr_ids, nbr_sims, Q, k, hist_len, N, tau, bin_edges, B, 0, counts, mass, s);
   return hip_status(e, "hist launch");
 }

@@ -110,8 +110,18 @@ hipError_t launch_select(const Candidates& c, int Q, int k, int need, Flagged fl
 constexpr int kDenseMaxRows = 32768;
 constexpr int kDenseMaxD = 8192;
 constexpr long kDenseMaxScores = 5L << 20;
+constexpr int kDenseHistMaxBins = 1024;
+// The histogram of the found neighbours as part of the select (B = -1: none).
+struct DenseHist {
+  const int32_t* hist_len = nullptr;
+  float tau = 0.0f;
+  const double* edges = nullptr;
+  int B = -1;
+  int32_t* counts = nullptr;
+  float* mass = nullptr;
+};
 hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
-                        int32_t* ids, float* sims, hipStream_t stream);
+                        int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream);
 
 hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int chunk_rows,
                                 const float* theta0, int cap, uint64_t* cand, int* cand_count, uint32_t* flag_word,
@@ -151,10 +161,11 @@ hipError_t launch_index(const float* mass, const float* cost, const int32_t* pro
                         const IndexVariant* variant = nullptr);
 size_t rank_workspace_bytes(int Q);
 hipError_t launch_rank(const float* index, int Q, int32_t* order, void* ws, hipStream_t stream);
-// Neighbours of every query: ids [Q, k] and sims [Q, k] (sorted, padded).
+// Neighbours of every query: ids [Q, k] and sims [Q, k] (sorted, padded). On
+// the dense path hist_part, where it is given, is done as well.
 hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d, int k,
                              const SimTopkPlan& plan, void* workspace, int32_t* ids, float* sims,
-                             hipStream_t stream);
+                             const DenseHist& hist_part, hipStream_t stream);
 // Merge of per-chunk lists; with `only_flagged`, queries whose flag is 0 are skipped.
 // Number of first-level groups of the list merge (1: single level).
 int merge_groups(int Q, int n_lists, int list_len);
