@@ -1136,6 +1136,14 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     if (sr > sr_max) sr = sr_max;
     if (sr < 1) sr = 1;
     while ((steps + sr - 1) / sr > 512) ++sr;
+    // A batch of few 256-query tiles leaves CUs idle while it samples: twice
+    // the samples cost nothing there, and halve the candidates, while they
+    // still fit one round of workgroups and the threshold select's smallest
+    // kernel (1,024 maxima; 2,048 with 16 waves per query).
+    if (Q > 128) {
+      const long tiles = (Q + 255) / 256, most = std::min(256 / tiles, Q >= 512 ? 64L : 128L);
+      while (sr > 1 && (steps + sr / 2 - 1) / (sr / 2) <= most) sr /= 2;
+    }
     p.sample_every = (int)sr;
     p.n_samples = (int)((steps + sr - 1) / sr);
   }
