@@ -18,28 +18,32 @@ namespace {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
-// S[q][n] for a tile of 32 queries (blockIdx.y) and 32 history rows per wave: d / 16 chained v_mfma_f32_32x32x16_bf16 from zero in
+// S[q][n] for a tile of 32 queries (blockIdx.y) and 32 kTiles history rows per wave: d / 16 chained v_mfma_f32_32x32x16_bf16 from zero in
 // column order, which gives the bits of every other search path. Operands go
 // straight from global memory to registers, kPanels 32-column panels in
 // flight: a wave waits d / (32 kPanels) times, and there is no barrier.
 // A operand: queries; B operand: history rows, so that a store instruction
 // writes 32 consecutive scores of a query. Rows and queries past the end are
 // read clamped and not stored.
+template <int kTiles>
 __global__ void __launch_bounds__(256, 2) dense_score_kernel(EmbView queries, int Q, EmbView hist, int N, int d,
                                                              int ld, float* __restrict__ scores) {
-  constexpr int kPanels = 12;
+  constexpr int kPanels = kTiles == 1 ? 12 : 6;
   const int lane = (int)lane_id();
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int l32 = lane & 31, half = lane >> 5;
-  const int n0 = (int)(blockIdx.x * (blockDim.x / kWave) + w) * 32, q0 = blockIdx.y * 32;
+  const int n0 = (int)(blockIdx.x * (blockDim.x / kWave) + w) * (32 * kTiles), q0 = blockIdx.y * 32;
   if (n0 >= N) return;                              // whole waves; no barrier below
   // Uniform panel address plus a per-lane byte offset (below 2^32: d <= kDenseMaxD).
   const uint32_t q_off = ((uint32_t)min(q0 + l32, Q - 1) * (uint32_t)queries.row + 8u * half) * 2u;
-  const uint32_t h_off = ((uint32_t)min(n0 + l32, N - 1) * (uint32_t)hist.row + 8u * half) * 2u;
+  uint32_t h_off[kTiles];
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t)
+    h_off[t] = ((uint32_t)min(n0 + 32 * t + l32, N - 1) * (uint32_t)hist.row + 8u * half) * 2u;
   const int KB = d / 32;
-  floatx16 acc = {};
+  floatx16 acc[kTiles] = {};
   for (int k0 = 0; k0 < KB; k0 += kPanels) {
-    bf16x8 a[kPanels][2], b[kPanels][2];
+    bf16x8 a[kPanels][2], b[kPanels][kTiles][2];
 #pragma unroll
     for (int i = 0; i < kPanels; ++i)
       if (k0 + i < KB) {
@@ -48,21 +52,29 @@ __global__ void __launch_bounds__(256, 2) dense_score_kernel(EmbView queries, in
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           a[i][j] = *reinterpret_cast<const bf16x8*>(qi + q_off + 32 * j);
-          b[i][j] = *reinterpret_cast<const bf16x8*>(hi + h_off + 32 * j);
+#pragma unroll
+          for (int t = 0; t < kTiles; ++t) b[i][t][j] = *reinterpret_cast<const bf16x8*>(hi + h_off[t] + 32 * j);
         }
       }
 #pragma unroll
     for (int i = 0; i < kPanels; ++i)
       if (k0 + i < KB) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][j], b[i][j], acc, 0, 0, 0);
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int t = 0; t < kTiles; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][j], b[i][t][j], acc[t], 0, 0, 0);
       }
   }
-  if (n0 + l32 >= N) return;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int q = q0 + 8 * (v >> 2) + 4 * half + (v & 3);
-    if (q < Q) scores[(size_t)q * ld + n0 + l32] = acc[v];
+  for (int t = 0; t < kTiles; ++t) {
+    const int n = n0 + 32 * t + l32;
+    if (n >= N) continue;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int q = q0 + 8 * (v >> 2) + 4 * half + (v & 3);
+      if (q < Q) scores[(size_t)q * ld + n] = acc[t][v];
+    }
   }
 }
 
@@ -240,11 +252,21 @@ hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int 
       d > kDenseMaxD || h.B > kDenseHistMaxBins) return hipErrorInvalidValue;
   {
     LaunchScope scope("sim_topk", stream);
-    // Single-wave workgroups while the waves are fewer than the chip's SIMDs:
-    // they spread over more CUs.
-    const int per = (long)((N + 31) / 32) * ((Q + 31) / 32) <= 1024 ? 1 : 4;
-    hipLaunchKernelGGL(dense_score_kernel, dim3((N + 32 * per - 1) / (32 * per), (Q + 31) / 32), dim3(kWave * per), 0,
-                       stream, queries, Q, hist, N, d, ld, scores);
+    // Up to one 32 x 32 tile per SIMD: single-wave workgroups, which spread
+    // over more CUs. From two per SIMD on, two tiles per wave share the query
+    // operands, a quarter less to read through L2 (128 x 32,768 x 768: decision
+    // 50.9 -> 41.1 us, 500 x 10,000 x 768 64.0 -> 55.5, 256 x 8,192 x 384 the same).
+    const long tiles = (long)((N + 31) / 32) * ((Q + 31) / 32);
+    const unsigned gy = (unsigned)((Q + 31) / 32);
+    if (tiles <= 1024)
+      hipLaunchKernelGGL(dense_score_kernel<1>, dim3((N + 31) / 32, gy), dim3(kWave), 0, stream, queries, Q, hist, N, d,
+                         ld, scores);
+    else if (tiles < 2048)
+      hipLaunchKernelGGL(dense_score_kernel<1>, dim3((N + 127) / 128, gy), dim3(4 * kWave), 0, stream, queries, Q, hist,
+                         N, d, ld, scores);
+    else
+      hipLaunchKernelGGL(dense_score_kernel<2>, dim3((N + 255) / 256, gy), dim3(4 * kWave), 0, stream, queries, Q, hist,
+                         N, d, ld, scores);
   }
   LaunchScope scope(h.B > 0 ? "hist" : "topk_select", stream);   // the histogram ends it, where it is part
   if (k <= 64) launch_dense_select<1>(scores, Q, N, ld, k, ids, sims, h, stream);

@@ -92,6 +92,7 @@ def test_full_segments_spill(Q):
     (5, 10000, 768, 128, "rows"),       # two list registers, every fourth thread a group
     (160, 32768, 32, 129, "panels"),    # the largest store; a group per thread; as many scores as allowed
     (7, 20011, 64, 256, "rows"),
+    (97, 20011, 224, 50, "panels"),     # two history tiles per wave, the last one ragged
 ])
 def test_dense_search_edges(Q, N, d, k, layout):
     """Stores small enough that every score is written out."""
