@@ -53,6 +53,13 @@ def test_decide_keeps_errors_and_overrides():
     for q, p in ((qf, plen[:3]), (qf.cpu(), plen), (qf, plen.long()), (qf[:, :32], plen), (qf.double(), plen)):
         with pytest.raises(sage.SageError):
             store.decide(q, p)
+    full = store.decide(qf, plen)
+    for i, t in ((3, full[3].double()), (3, full[3].repeat(2, 1)), (3, torch.zeros((16, 4), device="cuda").t()),
+                 (3, full[3].int()), (4, full[4].double()), (4, full[4].reshape(2, 2))):
+        out = [torch.zeros_like(x) for x in full]
+        out[i] = t                                             # of the size written or larger
+        with pytest.raises(sage.SageError):
+            store.decide(qf, plen, out=out)
     ring = sage.RingStore(100, 64, dev(w.bin_edges), dev(w.bin_repr), 8)
     with pytest.raises(sage.SageError, match="empty"):
         ring.decide(qf, plen)
