@@ -18,10 +18,11 @@ namespace {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
-// S[q][n] for a tile of 32 queries (blockIdx.y) and 32 kTiles history rows per wave: d / 16 chained v_mfma_f32_32x32x16_bf16 from zero in
-// column order, which gives the bits of every other search path. Operands go
-// straight from global memory to registers, kPanels 32-column panels in
-// flight: a wave waits d / (32 kPanels) times, and there is no barrier.
+// S[q][n] for a tile of 32 queries (blockIdx.y) and 32 kTiles history rows per
+// wave: d / 16 chained v_mfma_f32_32x32x16_bf16 from zero in column order,
+// which gives the bits of the filtered search. Operands go straight from
+// global memory to registers, kPanels 32-column panels in flight: a wave waits
+// d / (32 kPanels) times, and there is no barrier.
 // A operand: queries; B operand: history rows, so that a store instruction
 // writes 32 consecutive scores of a query. Rows and queries past the end are
 // read clamped and not stored.
@@ -248,7 +249,7 @@ static_assert(kDenseMaxRows == 32 * 1024, "the last case holds the largest store
 
 hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
                         int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream) {
-  if (Q <= 0 || N <= 0 || N > kDenseMaxRows || ld < N || k < 1 || k > 256 || d % 32 != 0 ||
+  if (Q <= 0 || Q > kDenseMaxQ || N <= 0 || N > kDenseMaxRows || ld < N || k < 1 || k > 256 || d % 32 != 0 ||
       d > kDenseMaxD || h.B > kDenseHistMaxBins) return hipErrorInvalidValue;
   {
     LaunchScope scope("sim_topk", stream);

@@ -1147,8 +1147,13 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     p.sample_every = (int)sr;
     p.n_samples = (int)((steps + sr - 1) / sr);
   }
-  // Small store and batch: every score written out (up to 20 MB of them).
-  p.dense = N <= kDenseMaxRows && d <= kDenseMaxD && (long)Q * N <= kDenseMaxScores;
+  // Small store and batch: every score written out (up to 20 MB of them). The
+  // select takes a workgroup of 16 waves per query whatever the store, about
+  // 36 ns a query from a few thousand queries on, where the filtered path has
+  // a wave per query: predict at d = 384, k = 64, dense against filtered,
+  // 1,000 x 2,000 48 / 82 us, 1,024 x 5,000 59 / 114, 2,048 x 2,500 91 / 94,
+  // 4,096 x 300 160 / 70, 16,384 x 300 613 / 170.
+  p.dense = Q <= kDenseMaxQ && N <= kDenseMaxRows && d <= kDenseMaxD && (long)Q * N <= kDenseMaxScores;
   p.dense_ld = (N + 31) / 32 * 32;
   if (p.dense) {
     p.total_bytes = align256((size_t)Q * p.dense_ld * sizeof(float));

@@ -106,8 +106,10 @@ struct Candidates {
 hipError_t launch_select(const Candidates& c, int Q, int k, int need, Flagged fl, int32_t* ids, float* sims,
                          hipStream_t stream);
 
-// Small stores (N <= kDenseMaxRows): scores [Q][ld] and the k best of each row.
+// Small batches (Q <= kDenseMaxQ) against small stores (N <= kDenseMaxRows):
+// scores [Q][ld] and the k best of each row.
 constexpr int kDenseMaxRows = 32768;
+constexpr int kDenseMaxQ = 1024;
 constexpr int kDenseMaxD = 8192;
 constexpr long kDenseMaxScores = 5L << 20;
 constexpr int kDenseHistMaxBins = 1024;

@@ -103,6 +103,16 @@ def test_dense_search_edges(Q, N, d, k, layout):
     assert sage.predict_stats(ws, Q, N, d, k, 64)["path"] == "dense"
 
 
+@pytest.mark.parametrize("Q,N,k,path", [(1024, 300, 32, "dense"), (1025, 300, 32, "filtered"),
+                                        (1025, 2500, 100, "lists"), (3000, 40, 64, "filtered")])
+def test_batches_past_the_dense_search(Q, N, k, path):
+    print(f"case Q={Q} N={N} k={k}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=64, k=k, B=64, seed=Q + N + k, clusters=4)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, 64, k, 64), dtype=torch.uint8, device="cuda")
+    check(w, k, "panels", ws)
+    assert sage.predict_stats(ws, Q, N, 64, k, 64)["path"] == path
+
+
 @pytest.mark.parametrize("k", [16, 100, 256])
 def test_dense_search_many_equal_scores(k):
     """6,000 copies of one row: more keys reach the bound than the select
