@@ -86,7 +86,9 @@ def stage_rooflines(stages, rows_per_launch: float, d: int, k: int, B: int, sear
     per = {"ingest_bf16": 6.0 * rows_per_launch * d,
            "hist": rows_per_launch * (12.0 * k + 8.0 * B),
            "index_scan": rows_per_launch * (4.0 * B + 8.0)}
-    if search is not None:
+    if search is not None and search["path"] == "dense":      # its select is timed with the histogram
+        per["hist"] += 4.0 * search["candidate_keys"]
+    elif search is not None:
         per["topk_select"] = (8.0 * search["candidate_keys"] + 4.0 * rows_per_launch * search["segments_per_query"]
                               + rows_per_launch * (4.0 + 8.0 * k))
     out = {}
@@ -152,12 +154,13 @@ def graph_replay(step, steps: int, rows: int, torch) -> dict:
     return {"ms_per_step": 1e3 * elapsed / steps, "value": rows * steps / elapsed}
 
 
-def kernel_name(k: int, Q: int = 1 << 30) -> str:
-    """The kernel behind the `sim_topk` timer label: the stream search for at
-    most 16 queries (large stores), else the filtered path for k <= 64."""
-    if Q <= 16:
-        return "sim_stream_kernel"
-    return "sim_filter_kernel" if k <= 64 else "sim_topk_kernel"
+KERNELS = {"lists": "sim_topk_kernel", "filtered": "sim_filter_kernel", "stream": "sim_stream_kernel",
+           "dense": "dense_score_kernel"}
+
+
+def kernel_name(path: str) -> str:
+    """The kernel behind the `sim_topk` timer label of a search path."""
+    return KERNELS[path]
 
 
 def oracle_threads() -> int:
@@ -331,7 +334,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": workloads.WORKLOAD_NAMES[args.config], "Q": Q, "N": N, "d": d,
                    "k": k, "B": B, "tau": spec.tau, "layout": "panels", "seed": w.seed},
-        "roofline": {"bound": "mfma", "kernel": kernel_name(k), "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": kernel_name(search["path"]), "achieved": achieved,
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": traffic,
                      "avg_launch_us": k1_avg_s * 1e6, "flops_per_launch": flops},
@@ -340,8 +343,8 @@ def main():
         "search": search,
     }
     # measured HBM bytes per launch of the stage kernels, where a current counter summary exists
-    for stage, kern, srcs in (("hist", "hist_kernel", ("k_hist.hip", "sage_device.hpp")),
-                              ("topk_select", "select_kernel", ("k_sim_topk.hip", "sage_device.hpp"))):
+    for stage, kern, srcs in (("hist", "hist_kernel", ("k_hist.hip", "sage_hist.hpp", "sage_device.hpp")),
+                              ("topk_select", "select_kernel", ("k_select.hip", "sage_toplist.hpp", "sage_device.hpp"))):
         if stage in line["stage_rooflines"]:
             line["stage_rooflines"][stage]["traffic"] = read_traffic(kern, workload_key, srcs)
     if args.graph:
@@ -486,7 +489,7 @@ def run_streaming(args, torch, sage, workloads):
                    "tau": spec.tau, "seed": [workloads.SEED_BASE, 5]},
         "latency_ms": {"p50": float(np.percentile(lat, 50)), "p99": float(np.percentile(lat, 99))},
         "reindexed_rows_per_s": queue.slots * args.steps / elapsed,
-        "roofline": {"bound": "hbm", "kernel": kernel_name(spec.k, batch), "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": kernel_name("stream"), "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": read_traffic("sim_stream_kernel", "streaming",
                                              sources=("k_sim_stream.hip", "sage_device.hpp")), "avg_launch_us": k1_avg_s * 1e6, "bytes_per_launch": k1_bytes},
@@ -633,7 +636,7 @@ def run_ttlt(args, torch, sage, workloads):
         "policies": policies,
         "single_server": {"rps": 8.0, "rate_cost_per_s": rate1, "policies": single},
         "gpu_us_per_request": 1e6 * elapsed / args.steps / R,
-        "roofline": {"bound": "mfma", "kernel": kernel_name(spec.k), "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": kernel_name("filtered"), "achieved": achieved,
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                      "avg_launch_us": k1_avg_s * 1e6, "flops_per_launch": flops},
