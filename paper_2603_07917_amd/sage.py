@@ -517,13 +517,11 @@ class Store:
         return predict(queries, self.hist_emb, self.hist_len, self.k, self.tau, self.bin_edges,
                        workspace=self._workspace(Q), out=out)
 
-    # decide() may use sage_decide: false for a subclass with a predict of its own.
-    _one_call = True
-
-    def __init_subclass__(cls, **kwargs):
-        super().__init_subclass__(**kwargs)
-        if "predict" in cls.__dict__ and "_one_call" not in cls.__dict__:
-            cls._one_call = False
+    def _library_predict(self) -> bool:
+        """Whether predict, and every predict that it may call through super(),
+        is the library's own."""
+        return "predict" not in self.__dict__ and all(
+            c.__dict__["predict"] in _LIBRARY_PREDICT for c in type(self).__mro__ if "predict" in c.__dict__)
 
     def _decide_once(self, queries: torch.Tensor, f32: bool, prompt_len: torch.Tensor, out):
         """decide() as one library call, or None where a check of the separate
@@ -570,9 +568,10 @@ class Store:
 
         One library call (sage_decide) where the inputs are in the forms that
         it takes; other forms go through the separate calls, which convert or
-        reject them."""
+        reject them, and so does a store with a predict of its own (from a
+        subclass, a mixin, or set on the class or the object)."""
         f32 = isinstance(queries, torch.Tensor) and queries.dtype == torch.float32
-        if (self._one_call and (f32 or (isinstance(queries, torch.Tensor) and queries.dtype == torch.bfloat16))
+        if (self._library_predict() and (f32 or (isinstance(queries, torch.Tensor) and queries.dtype == torch.bfloat16))
                 and queries.is_cuda and queries.dim() == (2 if f32 or queries.dim() != 3 else 3)
                 and isinstance(prompt_len, torch.Tensor)):
             queries = queries.contiguous() if f32 else queries
@@ -627,8 +626,6 @@ class RingStore(Store):
         self.hist_emb = self.ring_emb[:self.rows]
         self.hist_len = self.ring_len[:self.rows]
 
-    _one_call = True
-
     def predict(self, queries: torch.Tensor, out=None):
         if self.total == 0:
             raise SageError("the history window is empty")
@@ -636,6 +633,10 @@ class RingStore(Store):
 
     def _decide_once(self, queries, f32, prompt_len, out):
         return None if self.total == 0 else super()._decide_once(queries, f32, prompt_len, out)
+
+
+# The predict functions that sage_decide stands for, as they are defined here.
+_LIBRARY_PREDICT = (Store.predict, RingStore.predict)
 
 
 class Queue:

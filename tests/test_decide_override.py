@@ -1,0 +1,85 @@
+"""Store.decide uses a predict that a program put in place of the library's,
+wherever it put it (CPU only: the calls end in the replacement)."""
+import pytest
+import torch
+
+from paper_2603_07917_amd import sage
+
+
+class Called(Exception):
+    pass
+
+
+class OnDevice(torch.Tensor):
+    is_cuda = property(lambda self: True)
+
+
+def replacement(self, queries, out=None):
+    raise Called
+
+
+def bare(cls, monkeypatch):
+    """An object of cls whose one-call path, if taken, returns a marker."""
+    monkeypatch.setattr(sage.Store, "_decide_once", lambda *a: "one call")
+    monkeypatch.setattr(sage.RingStore, "_decide_once", lambda *a: "one call")
+    return cls.__new__(cls)
+
+
+def decide(store):
+    q = torch.zeros((2, 32)).as_subclass(OnDevice)
+    return store.decide(q, torch.ones(2, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("base", [sage.Store, sage.RingStore])
+@pytest.mark.parametrize("where", ["body", "mixin", "class later", "base class", "object", "child"])
+def test_replaced_predict_is_called(base, where, monkeypatch):
+    class Mixin:
+        predict = replacement
+
+    class Sub(base):
+        pass
+
+    cls = base
+    if where == "body":
+        cls = type("Body", (base,), {"predict": replacement})
+    elif where == "child":
+        cls = type("Child", (type("Body", (base,), {"predict": replacement}),), {})
+    elif where == "mixin":
+        cls = type("Mixed", (Mixin, base), {})
+    elif where == "class later":
+        cls = Sub
+        Sub.predict = replacement
+    elif where == "base class":
+        monkeypatch.setattr(base, "predict", replacement)
+    store = bare(cls, monkeypatch)
+    if base is sage.RingStore:
+        store.total = 1
+    if where == "object":
+        store.predict = lambda queries, out=None: replacement(store, queries, out)
+    with pytest.raises(Called):
+        decide(store)
+
+
+def test_replacement_behind_the_ring_store(monkeypatch):
+    """RingStore.predict goes on to the next predict: one between it and Store,
+    or one put in Store's place."""
+    between = type("Between", (sage.Store,), {"predict": replacement})
+    store = bare(type("Ring", (sage.RingStore, between), {}), monkeypatch)
+    store.total = 1
+    with pytest.raises(Called):
+        decide(store)
+    monkeypatch.setattr(sage.Store, "predict", replacement)
+    store = bare(sage.RingStore, monkeypatch)
+    store.total = 1
+    with pytest.raises(Called):
+        decide(store)
+
+
+@pytest.mark.parametrize("base", [sage.Store, sage.RingStore])
+def test_library_predict_keeps_the_one_call(base, monkeypatch):
+    class Plain(base):
+        def extra(self):
+            return 1
+
+    for cls in (base, Plain):
+        assert decide(bare(cls, monkeypatch)) == "one call"
