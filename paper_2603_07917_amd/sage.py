@@ -542,10 +542,13 @@ class Store:
                 return None
         if d != d_h or lens.shape[0] != N or prompt_len.shape[0] != Q or repr_.shape[0] != B:
             return None
-        if out is not None:                              # what the index and the rank check of their inputs
+        if out is not None:
+            if len(out) < 6 or not all(isinstance(t, torch.Tensor) for t in out[:6]):
+                return None                              # an output left out: allocated (index, order) or refused
+            # what the index and the rank check of their inputs
             for t, shape in ((out[3], (Q, B)), (out[4], (Q,))):
-                if (not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.float32
-                        or tuple(t.shape) != shape or not t.is_contiguous()):
+                if (not t.is_cuda or t.dtype != torch.float32 or tuple(t.shape) != shape
+                        or not t.is_contiguous()):
                     return None
         lib = load_library()
         need = lib.sage_decide_workspace_bytes(kind, Q, N, d, self.k, B)

@@ -83,3 +83,21 @@ def test_library_predict_keeps_the_one_call(base, monkeypatch):
 
     for cls in (base, Plain):
         assert decide(bare(cls, monkeypatch)) == "one call"
+
+
+@pytest.mark.parametrize("drop", [0, 1, 2, 3, 4, 5, "short"])
+def test_outputs_left_out_go_to_the_separate_calls(drop):
+    """They allocate an index or an order that is None, and refuse the rest."""
+    dev = lambda *a: torch.zeros(*a).as_subclass(OnDevice)
+    Q, d, k, B = 2, 32, 4, 8
+    store = sage.Store.__new__(sage.Store)
+    store.layout, store.k, store.tau = "rows", k, 0.8
+    store.hist_emb, store.hist_len = dev(10, d).bfloat16(), dev(10).int()
+    store.bin_edges, store.bin_repr = dev(B + 1).double(), dev(B).double()
+    store._ws = torch.empty(1 << 20, dtype=torch.uint8)
+    out = [dev(Q, k).int(), dev(Q, k), dev(Q, B).int(), dev(Q, B), dev(Q), dev(Q).int()]
+    if drop == "short":
+        out.pop()
+    else:
+        out[drop] = None
+    assert store._decide_once(dev(Q, d), True, dev(Q).int(), tuple(out)) is None

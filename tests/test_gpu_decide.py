@@ -60,6 +60,11 @@ def test_decide_keeps_errors_and_overrides():
         out[i] = t                                             # of the size written or larger
         with pytest.raises(sage.SageError):
             store.decide(qf, plen, out=out)
+    for left_out in ((4, 5), (5,)):                            # allocated by the index and the rank
+        out = [None if i in left_out else torch.zeros_like(x) for i, x in enumerate(full)]
+        assert same(store.decide(qf, plen, out=out), full)
+    with pytest.raises(sage.SageError):
+        store.decide(qf, plen, out=[None, *full[1:]])
     ring = sage.RingStore(100, 64, dev(w.bin_edges), dev(w.bin_repr), 8)
     with pytest.raises(sage.SageError, match="empty"):
         ring.decide(qf, plen)
