@@ -464,7 +464,8 @@ int sage_rank(const float* index, int Q, int32_t* order,
  *               workspace, in the store's layout)
  *   prompt_len [Q] int32, bin_repr [B] f64: as in sage_index
  *   index [Q] f32, order [Q] int32 out; the rest as in sage_predict_layout
- *   workspace   >= sage_decide_workspace_bytes(query_kind, Q, N, d, k, B) bytes
+ *   workspace   >= sage_decide_workspace_bytes(query_kind, Q, N, d, k, B)
+ *               bytes; sage_predict_stats takes it for the decision's search
  * Errors as in the separate calls; a call that returns SAGE_EINVAL or
  * SAGE_EWORKSPACE has enqueued nothing. Q = 0 is a no-op.
  */

@@ -774,16 +774,16 @@ SAGE_API int sage_rank(const float* index, int Q, int32_t* order, void* workspac
 // -------------------------------------------------------------- decide
 namespace {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-// Workspace of sage_decide: bf16 queries (fp32 input only), predict, rank.
+// Workspace of sage_decide: predict (first, where sage_predict_stats looks for
+// it), bf16 queries (fp32 input only), rank.
 struct DecideLayout {
-  size_t queries, predict, rank, total;
-  size_t predict_bytes, rank_bytes;
+  size_t predict_bytes, queries, rank, rank_bytes, total;
 };
 DecideLayout decide_layout(int query_kind, int Q, int N, int d, int k) {
   DecideLayout l{};
-  l.predict = query_kind == SAGE_QUERIES_F32 ? align256((size_t)Q * d * sizeof(uint16_t)) : 0;
   l.predict_bytes = sage::plan_sim_topk(Q, N, d, k).workspace_bytes();
-  l.rank = l.predict + align256(l.predict_bytes);
+  l.queries = align256(l.predict_bytes);
+  l.rank = l.queries + (query_kind == SAGE_QUERIES_F32 ? align256((size_t)Q * d * sizeof(uint16_t)) : 0);
   l.rank_bytes = sage::rank_workspace_bytes(Q);
   l.total = l.rank + l.rank_bytes;
   return l;
@@ -839,7 +839,7 @@ SAGE_API int sage_decide(const void* queries, int query_kind, int Q, const uint1
     qb = dst;
   }
   st = sage_predict_layout(qb, q_layout, Q, hist_emb, hist_layout, hist_len, N, d, k, tau, bin_edges, B, nbr_ids,
-                           nbr_sims, counts, mass, ws + l.predict, l.predict_bytes, stream);
+                           nbr_sims, counts, mass, ws, l.predict_bytes, stream);
   if (st != SAGE_OK) return st;
   st = sage_index(mass, nullptr, prompt_len, bin_repr, Q, B, index, nullptr, stream);
   if (st != SAGE_OK) return st;

@@ -80,3 +80,28 @@ def test_decide_keeps_errors_and_overrides():
     assert same(mine.decide(qf, plen), store.decide(qf, plen)) and mine.called
     empty = store.decide(qf[:0], plen[:0])
     assert [t.shape[0] for t in empty] == [0] * 6
+
+
+@pytest.mark.parametrize("Q,N,k,path", [(40, 50000, 32, "filtered"), (4, 60000, 16, "stream")])
+@pytest.mark.parametrize("f32", [True, False])
+def test_stats_of_a_decision(Q, N, k, path, f32):
+    """predict_stats on the store's workspace after decide: what the same search
+    reports after predict (the candidates depend on the inputs only), with every
+    query flagged and with none."""
+    w = workloads.small_predict(Q=Q, N=N, d=64, k=k, B=32, seed=Q + N, clusters=6)
+    store = sage.Store(dev(w.hist_emb), dev(w.hist_len), dev(w.bin_edges), dev(w.bin_repr), k)
+    queries, plen = dev(w.queries), dev(w.prompt_len)
+    if not f32:
+        queries = sage.ingest_bf16(queries, "panels")
+    stats = lambda: sage.predict_stats(store._ws, Q, N, 64, k, 32)
+    try:
+        for floor, flagged in ((-np.inf, 0), (2.0, Q)):
+            sage.debug_theta_floor(floor)
+            store.predict(queries)
+            want = stats()
+            assert want["path"] == path and want["flagged"] == flagged
+            store._ws.fill_(0x5A)
+            store.decide(queries, plen)
+            assert stats() == want
+    finally:
+        sage.debug_theta_floor(-np.inf)
