@@ -561,7 +561,7 @@ class Store:
                    torch.empty(Q, dtype=torch.float32, device=dev), torch.empty(Q, dtype=torch.int32, device=dev))
         ids, sims, counts, mass, g, order = out[:6]
         _check(lib.sage_decide(queries.data_ptr(), kind, Q, self.hist_emb.data_ptr(), h_layout, lens.data_ptr(), N, d, k,
-                               float(self.tau), edges.data_ptr(), prompt_len.data_ptr(), repr_.data_ptr(), B, ids.data_ptr(),
+                               self.tau, edges.data_ptr(), prompt_len.data_ptr(), repr_.data_ptr(), B, ids.data_ptr(),
                                sims.data_ptr(), counts.data_ptr(), mass.data_ptr(), g.data_ptr(), order.data_ptr(),
                                self._ws.data_ptr(), self._ws.numel(), _stream()))
         return ids, sims, counts, mass, g, order

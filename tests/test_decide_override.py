@@ -1,8 +1,5 @@
 """Store.decide uses a predict that a program put in place of the library's,
 wherever it put it (CPU only: the calls end in the replacement)."""
-import ctypes
-
-import numpy as np
 import pytest
 import torch
 
@@ -88,48 +85,19 @@ def test_library_predict_keeps_the_one_call(base, monkeypatch):
         assert decide(bare(cls, monkeypatch)) == "one call"
 
 
-def dev(*shape):
-    return torch.zeros(*shape).as_subclass(OnDevice)
-
-
-def small_store(d, k, B):
+@pytest.mark.parametrize("drop", [0, 1, 2, 3, 4, 5, "short"])
+def test_outputs_left_out_go_to_the_separate_calls(drop):
+    """They allocate an index or an order that is None, and refuse the rest."""
+    dev = lambda *a: torch.zeros(*a).as_subclass(OnDevice)
+    Q, d, k, B = 2, 32, 4, 8
     store = sage.Store.__new__(sage.Store)
     store.layout, store.k, store.tau = "rows", k, 0.8
     store.hist_emb, store.hist_len = dev(10, d).bfloat16(), dev(10).int()
     store.bin_edges, store.bin_repr = dev(B + 1).double(), dev(B).double()
     store._ws = torch.empty(1 << 20, dtype=torch.uint8)
-    return store
-
-
-@pytest.mark.parametrize("drop", [0, 1, 2, 3, 4, 5, "short"])
-def test_outputs_left_out_go_to_the_separate_calls(drop):
-    """They allocate an index or an order that is None, and refuse the rest."""
-    Q, d, k, B = 2, 32, 4, 8
-    store = small_store(d, k, B)
     out = [dev(Q, k).int(), dev(Q, k), dev(Q, B).int(), dev(Q, B), dev(Q), dev(Q).int()]
     if drop == "short":
         out.pop()
     else:
         out[drop] = None
     assert store._decide_once(dev(Q, d), True, dev(Q).int(), tuple(out)) is None
-
-
-@pytest.mark.parametrize("tau", [1, np.float32(0.8), torch.tensor(0.8)])
-def test_tau_of_any_number_type(tau, monkeypatch):
-    """A tau that float() takes, as predict does."""
-    seen = []
-
-    class Library:
-        sage_decide_workspace_bytes = staticmethod(lambda *a: 1 << 10)
-
-        @staticmethod
-        def sage_decide(*a):
-            seen.append(ctypes.c_float(a[9]).value)
-            return 0
-
-    monkeypatch.setattr(sage, "load_library", lambda: Library)
-    monkeypatch.setattr(sage, "_stream", lambda: 0)
-    store = small_store(32, 4, 8)
-    store.tau = tau
-    assert store._decide_once(dev(2, 32), True, dev(2).int(), None) is not None
-    assert seen == [ctypes.c_float(float(tau)).value]
