@@ -596,7 +596,7 @@ __global__ void __launch_bounds__(kRankCountThreads) rank_count_kernel(const flo
 // 8.9 against 9.1 us; 16,384: 24.1 against 10.2).
 // ---------------------------------------------------------------------------
 constexpr int kRankMergeMax = 131072;
-constexpr uint32_t kRankPad = 0xFFFFFFFFu;          // above every key but NaN's
+constexpr uint32_t kRankPad = 0xFFFFFFFFu;          // above every key but that of the NaN 0x7fffffff, which is it
 
 // Number of the n (a power of two) ascending keys of `a` below k (or, with
 // `or_equal`, at most k).
@@ -645,6 +645,9 @@ __global__ void __launch_bounds__(1024) rank_merge_kernel(const uint32_t* __rest
   const int own = blockIdx.x * E / T;               // E divides T
   const uint32_t k = keys_in[at];
   int cnt = s == 0 ? at - own * T : 0;              // place in its own tile
+  // Of the tiles before, every key comes before one of kRankPad's bits (one NaN's);
+  // k + 1 wraps to 0 there, so that the searches below count none of them.
+  if (s == 0 && k == kRankPad) cnt += own * T;
   for (int t0 = 0; t0 < n_tiles; t0 += kGroupTiles) {
     const int n = min(kGroupTiles, n_tiles - t0);
     __syncthreads();                                // the previous group's searches are done
@@ -661,7 +664,7 @@ __global__ void __launch_bounds__(1024) rank_merge_kernel(const uint32_t* __rest
       for (int u = 0; u < kIlp; ++u) {
         const int tt = min(t + u * kShare, n - 1);
         a[u] = keys + tt * T;
-        lim[u] = t0 + tt < own ? k + 1u : k;        // no real key is 2^32 - 1
+        lim[u] = t0 + tt < own ? k + 1u : k;
         pos[u] = 0;
       }
 #pragma unroll
