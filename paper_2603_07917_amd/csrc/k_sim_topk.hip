@@ -1175,9 +1175,10 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     p.f_tile = Q <= 128 ? 128 : 256;
     p.f_q_tiles = (Q + p.f_tile - 1) / p.f_tile;
     const int slots = p.f_tile == 128 ? 512 : 256;   // workgroups the chip holds at a time
-    // samples per sampling block: about one block per slot
+    // samples per sampling block: about one block per slot (with 256 query
+    // tiles and more, one block per tile)
     p.f_spb = 1;
-    while (p.n_samples > 0 && (long)p.f_q_tiles * ((p.n_samples + 2 * p.f_spb - 1) / (2 * p.f_spb)) >= 256)
+    while (p.f_spb < p.n_samples && (long)p.f_q_tiles * ((p.n_samples + 2 * p.f_spb - 1) / (2 * p.f_spb)) >= 256)
       p.f_spb *= 2;
     filter_chunking(p.f_q_tiles, N, slots, p.n_samples > 0, &p.f_chunk_rows, &p.f_n_chunks);
     // Query tiles that an XCD works on at a time: as many (all of them, or a

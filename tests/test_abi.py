@@ -4,6 +4,8 @@ import ctypes
 import math
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -286,3 +288,14 @@ def test_length_predictor_validation(lib):
     for bad in (dict(Q=-1), dict(N=0), dict(k=0), dict(k=257), dict(B=0), dict(max_len=0), dict(tau=0.0)):
         assert call(**bad) == SAGE_EINVAL, bad
     assert call(Q=0) == SAGE_OK
+
+
+@pytest.mark.parametrize("Q,N,k", [(65280, 300, 1), (65281, 300, 1), (65281, 300, 64), (65281, 100000, 128),
+                                   (1 << 20, 1 << 20, 64), ((1 << 29) - 1, 300, 1), ((1 << 29) - 1, 1 << 22, 256)])
+def test_sizes_of_very_large_batches(Q, N, k):
+    """256 and more query tiles: in a process of its own, which a fault in the
+    plan would end."""
+    code = (f"import ctypes; f = ctypes.CDLL({LIB!r}).sage_predict_workspace_bytes; f.restype = ctypes.c_size_t; "
+            f"print(f({Q}, {N}, 384, {k}, 256))")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and int(r.stdout) >= Q * (8 * k + 4)
