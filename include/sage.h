@@ -132,8 +132,8 @@ int sage_queue_dispatch(const int32_t* order, int batch, const int64_t* request,
 
 /*
  * sage_predict_workspace_bytes - bytes of device workspace sage_predict needs
- * for these sizes (holds the per-stream partial neighbour lists). Returns 0
- * for invalid sizes.
+ * for these sizes (it holds scores, candidate keys or partial neighbour
+ * lists). Returns 0 for invalid sizes.
  */
 size_t sage_predict_workspace_bytes(int Q, int N, int d, int k, int B);
 
@@ -165,6 +165,9 @@ size_t sage_predict_workspace_bytes(int Q, int N, int d, int k, int B);
  *                         same sum over all neighbours; if no neighbour reaches
  *                         tau, counts / (number of valid neighbours)
  *   workspace             >= sage_predict_workspace_bytes(Q, N, d, k, B) bytes
+ *                         (else SAGE_EWORKSPACE). The size does not always
+ *                         grow with Q: a buffer for batches of several sizes
+ *                         needs the largest of their sizes
  * Constraints: Q >= 0, N >= 1, d >= 32 and d % 32 == 0.
  */
 int sage_predict(const uint16_t* queries, int Q,
@@ -257,9 +260,11 @@ int sage_predict_stats(const void* workspace, size_t workspace_bytes, int Q, int
  * the caller's, as in sage_predict_layout, and the outputs are identical to
  * that call's.
  *   SAGE_EWORKSPACE (nothing enqueued) when the search needs more scratch
- *   than the array holds: sage_predict_workspace_bytes(Q, N, d, k, B) must
- *   not exceed SAGE_NOALLOC_SCRATCH_BYTES (few-query decisions against a
- *   store of millions of rows fit; so do batches of a few hundred queries).
+ *   than the array holds. A search of which sage_predict_workspace_bytes(Q,
+ *   N, d, k, B) does not exceed SAGE_NOALLOC_SCRATCH_BYTES fits (few-query
+ *   decisions against a store of millions of rows do, and batches of a few
+ *   hundred queries); one of k > 64 also fits, on its slower search, where
+ *   that one's lists do.
  * Every call on one GPU shares that GPU's array: calls that overlap in time
  * on one GPU (other streams, other host threads) race and must be ordered by
  * the caller. Nothing in the array needs to start cleared: each call writes

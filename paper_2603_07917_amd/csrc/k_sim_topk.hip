@@ -1107,7 +1107,7 @@ void plan_workspace(SimTopkPlan* p, int Q, int L) {
 }  // namespace
 
 
-SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
+SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit) {
   SimTopkPlan p{};
   int L = 64;
   while (L < k) L <<= 1;
@@ -1206,13 +1206,14 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k) {
     while (p.s_cap < 4L * k * p.sample_every) p.s_cap *= 2;
   }
   plan_workspace(&p, Q, L);
-  // The exact lists alone take less: a search of k > 64 that only so fits the
-  // static scratch of the no-allocation entry point keeps to them.
-  if (p.fast && L > 64 && p.total_bytes > (size_t)SAGE_NOALLOC_SCRATCH_BYTES) {
+  // The exact lists alone take less. They are three times slower (figures
+  // above), so a search of k > 64 keeps to them only where the scratch is
+  // given and holds them and not the candidates.
+  if (p.fast && L > 64 && p.total_bytes > limit) {
     SimTopkPlan lists = p;
     lists.fast = false;
     plan_workspace(&lists, Q, L);
-    if (lists.total_bytes <= (size_t)SAGE_NOALLOC_SCRATCH_BYTES) return lists;
+    if (lists.total_bytes <= limit) return lists;
   }
   return p;
 }

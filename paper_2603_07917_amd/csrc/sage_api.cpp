@@ -332,11 +332,12 @@ SAGE_API size_t sage_predict_workspace_bytes(int Q, int N, int d, int k, int B) 
   return sage::plan_sim_topk(Q, N, d, k).workspace_bytes();
 }
 
-SAGE_API int sage_predict_layout(const uint16_t* queries, int query_layout, int Q, const uint16_t* hist_emb,
-                                 int hist_layout, const int32_t* hist_len, int N, int d, int k, float tau,
-                                 const double* bin_edges, int B, int32_t* nbr_ids, float* nbr_sims,
-                                 int32_t* counts, float* mass, void* workspace, size_t workspace_bytes,
-                                 sage_stream_t stream) {
+namespace {
+// The search and histogram with the plan for `scratch_limit` bytes.
+int predict_within(size_t scratch_limit, const uint16_t* queries, int query_layout, int Q, const uint16_t* hist_emb,
+                   int hist_layout, const int32_t* hist_len, int N, int d, int k, float tau, const double* bin_edges,
+                   int B, int32_t* nbr_ids, float* nbr_sims, int32_t* counts, float* mass, void* workspace,
+                   size_t workspace_bytes, sage_stream_t stream) {
   for (int layout : {query_layout, hist_layout})
     if (layout != SAGE_LAYOUT_ROWS && layout != SAGE_LAYOUT_PANELS)
       return fail(SAGE_EINVAL, "layout=%d is not a SAGE_LAYOUT_* value", layout);
@@ -351,7 +352,7 @@ SAGE_API int sage_predict_layout(const uint16_t* queries, int query_layout, int 
     if (!ptrs[i]) return fail(SAGE_EINVAL, "sage_predict: %s is NULL", names[i]);
     if (!aligned16(ptrs[i])) return fail(SAGE_EINVAL, "sage_predict: %s is not 16-byte aligned", names[i]);
   }
-  const sage::SimTopkPlan plan = sage::plan_sim_topk(Q, N, d, k);
+  const sage::SimTopkPlan plan = sage::plan_sim_topk(Q, N, d, k, scratch_limit);
   if (workspace_bytes < plan.workspace_bytes() || !workspace)
     return fail(SAGE_EWORKSPACE, "sage_predict: workspace of %zu bytes, %zu needed", workspace_bytes,
                 plan.workspace_bytes());
@@ -376,6 +377,16 @@ SAGE_API int sage_predict_layout(const uint16_t* queries, int query_layout, int 
   if (part.B > 0) return ok();
   e = sage::launch_hist(nbr_ids, nbr_sims, Q, k, hist_len, N, tau, bin_edges, B, 0, counts, mass, s);
   return hip_status(e, "hist launch");
+}
+}  // namespace
+
+SAGE_API int sage_predict_layout(const uint16_t* queries, int query_layout, int Q, const uint16_t* hist_emb,
+                                 int hist_layout, const int32_t* hist_len, int N, int d, int k, float tau,
+                                 const double* bin_edges, int B, int32_t* nbr_ids, float* nbr_sims,
+                                 int32_t* counts, float* mass, void* workspace, size_t workspace_bytes,
+                                 sage_stream_t stream) {
+  return predict_within(SIZE_MAX, queries, query_layout, Q, hist_emb, hist_layout, hist_len, N, d, k, tau, bin_edges,
+                        B, nbr_ids, nbr_sims, counts, mass, workspace, workspace_bytes, stream);
 }
 
 // ------------------------------------------------ predict, no allocation
@@ -415,7 +426,7 @@ SAGE_API int sage_predict_noalloc(const uint16_t* queries, int query_layout, int
   if (st != SAGE_OK) return st;
   if (Q == 0) return sage_predict_layout(queries, query_layout, 0, hist_emb, hist_layout, hist_len, N, d, k, tau,
                                          bin_edges, B, nbr_ids, nbr_sims, counts, mass, nullptr, 0, stream);
-  const size_t need = sage::plan_sim_topk(Q, N, d, k).workspace_bytes();
+  const size_t need = sage::plan_sim_topk(Q, N, d, k, SAGE_NOALLOC_SCRATCH_BYTES).workspace_bytes();
   if (need > (size_t)SAGE_NOALLOC_SCRATCH_BYTES)
     return fail(SAGE_EWORKSPACE, "sage_predict_noalloc: this search needs %zu bytes of scratch, the static "
                 "array holds %zu (use sage_predict_layout with a workspace)", need,
@@ -423,8 +434,8 @@ SAGE_API int sage_predict_noalloc(const uint16_t* queries, int query_layout, int
   if ((st = check_device()) != SAGE_OK) return st;
   void* ws = nullptr;
   if ((st = scratch_address(&ws)) != SAGE_OK) return st;
-  return sage_predict_layout(queries, query_layout, Q, hist_emb, hist_layout, hist_len, N, d, k, tau, bin_edges, B,
-                             nbr_ids, nbr_sims, counts, mass, ws, (size_t)SAGE_NOALLOC_SCRATCH_BYTES, stream);
+  return predict_within(SAGE_NOALLOC_SCRATCH_BYTES, queries, query_layout, Q, hist_emb, hist_layout, hist_len, N, d, k,
+                        tau, bin_edges, B, nbr_ids, nbr_sims, counts, mass, ws, SAGE_NOALLOC_SCRATCH_BYTES, stream);
 }
 
 SAGE_API int sage_predict_stats(const void* workspace, size_t workspace_bytes, int Q, int N, int d, int k, int B,

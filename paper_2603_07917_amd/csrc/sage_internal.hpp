@@ -68,7 +68,9 @@ struct SimTopkPlan {
       off_spill, off_spillcnt, off_scores, total_bytes;
   size_t workspace_bytes() const { return total_bytes; }
 };
-SimTopkPlan plan_sim_topk(int Q, int N, int d, int k);
+// `limit`: scratch bytes that the search has to do with. A plan that needs more
+// is returned only when no other fits either.
+SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit = SIZE_MAX);
 // Few-query stream path: limits, and the search + candidate select.
 constexpr int kStreamMaxQ = 16;
 constexpr int kStreamMaxD = 2048;

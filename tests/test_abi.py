@@ -299,3 +299,29 @@ def test_sizes_of_very_large_batches(Q, N, k):
             f"print(f({Q}, {N}, 384, {k}, 256))")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and int(r.stdout) >= Q * (8 * k + 4)
+
+
+@pytest.mark.parametrize("Q,N,k,fits", [(8, 400000, 128, True), (300, 30000, 64, True), (2047, 100000, 128, True),
+                                        (2047, 500000, 128, True), (2048, 500000, 128, False),
+                                        (4096, 262144, 64, False), (16384, 60000, 128, False)])
+def test_noalloc_takes_what_fits_its_scratch(lib, Q, N, k, fits):
+    """Refused before a device is looked for; what fits gets as far as that.
+    The fourth fits by its exact lists only."""
+    P, I, F = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
+    lib.sage_predict_noalloc.argtypes = [P, I, I, P, I, P, I, I, I, F, P, I, P, P, P, P, P]
+    lib.sage_predict_noalloc.restype = I
+    st = lib.sage_predict_noalloc(A + 4, 1, Q, A, 1, A, N, 768, k, 0.8, A, 64, A, A, A, A, None)
+    assert (st != SAGE_EWORKSPACE) == fits      # the misaligned queries end it on a GPU
+
+
+def test_workspace_of_long_lists_follows_the_filtered_search(lib):
+    """No switch to the exact lists (a third of the size) where those fit a
+    scratch that the caller does not use: a smaller batch never needs twice what
+    a larger one does. The list fallback, whose chunk count falls as query tiles
+    are added, gives the factor of almost two at small batches."""
+    for N, k in ((500000, 128), (100000, 256), (60000, 100)):
+        most = 0
+        for Q in range(1, 4000):
+            size = lib.sage_predict_workspace_bytes(Q, N, 768, k, 512)
+            most = max(most, size)
+            assert most <= 2 * size, (Q, N, k)

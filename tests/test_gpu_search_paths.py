@@ -113,6 +113,33 @@ def test_batches_past_the_dense_search(Q, N, k, path):
     assert sage.predict_stats(ws, Q, N, 64, k, 64)["path"] == path
 
 
+@pytest.mark.parametrize("Q,N,k", [(2047, 100000, 128), (2048, 100000, 128), (1001, 100003, 128), (481, 60001, 256),
+                                   (963, 50000, 100)])
+def test_long_lists_of_any_batch_are_filtered(Q, N, k):
+    """k > 64 with a workspace of its own takes the filtered search, whether or
+    not the exact lists would fit the scratch of sage_predict_noalloc; that call
+    takes them there, and gives the same bits."""
+    d, B = 32, 16
+    print(f"case Q={Q} N={N} k={k}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=Q + N + k, clusters=12)
+    qb, hb = sage.ingest_bf16(dev(w.queries), "panels"), sage.ingest_bf16(dev(w.hist_emb), "panels")
+    hist_len, edges = dev(w.hist_len), dev(w.bin_edges)
+    need = sage.predict_workspace_bytes(Q, N, d, k, B)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    out = sage.predict(qb, hb, hist_len, k, 0.8, edges, workspace=ws)
+    stats = sage.predict_stats(ws, Q, N, d, k, B)
+    assert stats["path"] == "filtered" and stats["flagged"] == 0
+    rows = np.unique(np.linspace(0, Q - 1, 64).astype(int))
+    S = oracle.similarity(oracle.round_to_bf16(w.queries[rows]), oracle.round_to_bf16(w.hist_emb))
+    parity.check_predict(*[host(t)[rows] for t in out], S, w.hist_len, w.bin_edges, 0.8, k)
+    again = [torch.full_like(t, 7) for t in out]
+    assert sage.load_library().sage_predict_noalloc(
+        qb.data_ptr(), 1, Q, hb.data_ptr(), 1, hist_len.data_ptr(), N, d, k, 0.8, edges.data_ptr(), B,
+        *[t.data_ptr() for t in again], sage._stream()) == 0
+    for a, b in zip(out, again):
+        assert np.array_equal(host(a).view(np.uint8), host(b).view(np.uint8))
+
+
 @pytest.mark.parametrize("k", [16, 100, 256])
 def test_dense_search_many_equal_scores(k):
     """6,000 copies of one row: more keys reach the bound than the select
