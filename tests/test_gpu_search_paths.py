@@ -113,6 +113,40 @@ def test_batches_past_the_dense_search(Q, N, k, path):
     assert sage.predict_stats(ws, Q, N, 64, k, 64)["path"] == path
 
 
+@pytest.mark.parametrize("Q,k,path,cap", [
+    (12, 8, "stream", 4096),        # the stream search's array
+    (12, 128, "stream", 0),
+    (100, 64, "filtered", 0),       # more than 64 chunks: segments and the spill array
+    (300, 100, "filtered", 0),      # k > 64: the same
+    (300, 256, "filtered", 0),
+    (2200, 32, "filtered", 0),      # segments without a spill array, one wave per query in the select
+    (2200, 128, "filtered", 0),     # with one, two list registers
+    (2200, 200, "filtered", 0),     # four
+])
+@pytest.mark.parametrize("layout", ["panels", "rows"])
+def test_overflowing_candidates_take_the_exact_path(Q, k, path, cap, layout):
+    """Half of the store repeats one row: a query equal to it has more candidates
+    than any array holds, and is answered by the exact path (the lowest ids of
+    the copies, in order); the others are not disturbed. Every seventh query is
+    one, so that tiles hold both."""
+    N, d, B = 60000, 64, 16
+    print(f"case Q={Q} k={k} {layout}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=21 + Q + k, clusters=12)
+    w.hist_emb[: N // 2] = w.hist_emb[N // 2]
+    w.queries[::7] = w.hist_emb[N // 2]
+    qb, hb = sage.ingest_bf16(dev(w.queries), layout), sage.ingest_bf16(dev(w.hist_emb), layout)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, B), dtype=torch.uint8, device="cuda")
+    for _ in range(2):                               # the second call with the first one's counters and flags
+        out = [host(t) for t in sage.predict(qb, hb, dev(w.hist_len), k, 0.8, dev(w.bin_edges), workspace=ws)]
+        stats = sage.predict_stats(ws, Q, N, d, k, B)
+        assert stats["path"] == path and len(w.queries[::7]) <= stats["flagged"] < Q
+        assert cap == 0 or stats["segment_capacity"] == cap
+        assert np.array_equal(out[0][::7], np.tile(np.arange(k), (len(w.queries[::7]), 1)))
+    rows = np.unique(np.concatenate([np.arange(0, Q, max(1, Q // 60)), [Q - 1]]))
+    S = oracle.similarity(oracle.round_to_bf16(w.queries[rows]), oracle.round_to_bf16(w.hist_emb))
+    parity.check_predict(*[t[rows] for t in out], S, w.hist_len, w.bin_edges, 0.8, k)
+
+
 @pytest.mark.parametrize("Q,N,k", [(2047, 100000, 128), (2048, 100000, 128), (1001, 100003, 128), (481, 60001, 256),
                                    (963, 50000, 100)])
 def test_long_lists_of_any_batch_are_filtered(Q, N, k):
