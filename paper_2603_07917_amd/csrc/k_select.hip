@@ -75,12 +75,12 @@ __global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) select_kernel(Candidate
   }
   if (over || all + n_spill < need) {                 // the same for every wave of the query
     if (lane == 0 && w == 0) {
-      fl.flags[q] = 1;
+      fl.flags[q] = over ? kOverflowed : kTooFew;
       *fl.word = 1u;
     }
     return;
   }
-  if (lane == 0 && w == 0) fl.flags[q] = 0;
+  if (lane == 0 && w == 0) fl.flags[q] = kNotFlagged;
   __builtin_amdgcn_wave_barrier();                    // off[] written before it is read
 
   TopList<S> top(pend[wg]);

@@ -271,8 +271,7 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
   const int h_begin = chunk * chunk_rows;
   const int h_end = min(N, h_begin + chunk_rows);
 
-  // As the exact fallback of the filtered path, only tiles holding a flagged
-  // query do any work.
+  // As the exact fallback, only tiles holding a flagged query do any work.
   if (only_flagged) {
     if (tid == 0) sm.rounds = 0;
     __syncthreads();
@@ -284,7 +283,17 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
   for (int i = tid; i < BQ * KL; i += kThreads) sm.list[i] = kPadKey;
   for (int i = tid; i < BQ; i += kThreads) {
     sm.theta[i] = -__builtin_inff();
-    sm.theta0[i] = (theta0 && q0 + i < Q) ? theta0[q0 + i] : -__builtin_inff();
+    // As the fallback: no candidates for a query that is not flagged, and the
+    // threshold again for one that has more candidates than its arrays hold
+    // (50,000 equal rows of 100,000, 300 queries of which 100 are equal to them,
+    // k = 128, d = 384: 852 us without it). It is a bound that k of this
+    // query's scores reach; only where too few did, it is not.
+    float bound = (theta0 && q0 + i < Q) ? theta0[q0 + i] : -__builtin_inff();
+    if (only_flagged) {
+      const int f = q0 + i < Q ? only_flagged[q0 + i] : kNotFlagged;
+      bound = f == kNotFlagged ? __builtin_inff() : (f == kOverflowed ? bound : -__builtin_inff());
+    }
+    sm.theta0[i] = bound;
     sm.fill[i] = 0;
   }
 
@@ -1272,9 +1281,11 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     e = launch_select(cand, Q, k, min(k, N), fl, ids, sims, stream);
     if (e != hipSuccess) return e;
     // Exact fallback for queries whose candidates overflowed (no work otherwise).
-    if (p.list_len == 64) e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
-    else if (p.list_len == 128) e = launch_lists<2, 128>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
-    else e = launch_lists<1, 256>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
+    // Its scores are the filter kernel's, bit for bit, so theta0 bounds them too.
+    const float* th = p.n_samples > 0 ? theta0 : nullptr;
+    if (p.list_len == 64) e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, th, &fl, partial, stream);
+    else if (p.list_len == 128) e = launch_lists<2, 128>(queries, Q, hist, N, d, k, p, th, &fl, partial, stream);
+    else e = launch_lists<1, 256>(queries, Q, hist, N, d, k, p, th, &fl, partial, stream);
     if (e != hipSuccess) return e;
     return launch_topk_merge(partial, Q, p.n_chunks, p.list_len, k, &fl, merge_lists, ids, sims, stream);
   }
@@ -1288,7 +1299,8 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     if (e != hipSuccess) return e;
     e = launch_select(Candidates{nullptr, nullptr, 0, 0, cand, ccount, p.s_cap}, Q, k, min(k, N), fl, ids, sims, stream);
     if (e != hipSuccess) return e;
-    // Exact fallback for queries whose candidates overflowed (no work otherwise).
+    // Exact fallback for queries whose candidates overflowed (no work otherwise);
+    // its scores may differ from the stream kernel's in the last bit: no threshold.
     if (p.list_len == 64) e = launch_lists<4, 64>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
     else if (p.list_len == 128) e = launch_lists<2, 128>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);
     else e = launch_lists<1, 256>(queries, Q, hist, N, d, k, p, nullptr, &fl, partial, stream);

@@ -80,11 +80,13 @@ hipError_t launch_stream_sample(EmbView queries, int Q, EmbView hist, int N, int
 // Test hook (sage_debug_theta_floor): a floor on the pre-pass threshold of the
 // filtered and stream paths; -inf when unset.
 float debug_theta_floor();
-// Queries sent to the exact fallback: flags[q] = 1 for each, and *word = 1
-// once any query is flagged. The search's first kernel that always runs (the
+// Queries sent to the exact fallback: flags[q] says why (more candidates than
+// their arrays hold, or fewer than min(k, N)), and *word = 1 once any query is
+// flagged. The search's first kernel that always runs (the
 // filter kernel, the stream search) clears the word, so that the fallback
 // kernels return at once when it is still 0; nothing here depends on the
 // call, so a captured graph replays it as it stands.
+enum FlagReason { kNotFlagged = 0, kOverflowed = 1, kTooFew = 2 };
 struct Flagged {
   int* flags;
   uint32_t* word;
