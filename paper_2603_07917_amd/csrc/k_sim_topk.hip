@@ -798,7 +798,12 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) threshold_sample
 // spill array (many small segments) the keys past a full segment go to the
 // query's spill[q][0..spill_cap): a chunk whose rows are alike fills its
 // segment without sending the query to the exact path.
-template <int WQ>
+//
+// kAll: a store too small for a pre-pass, no threshold, every row of a chunk a
+// candidate. Row h of the chunk goes to place h - h_begin of its segment, four
+// keys to two stores. Found and picked one by one, 16,000 queries against 2,000
+// rows (d = 384) took 565 us a predict, so 243; 60,000 against 1,000 1,194, 520.
+template <int WQ, bool kAll>
 __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kernel(
     EmbView queries, int Q, EmbView hist, int N, int d,
     int chunk_rows, int n_chunks, int q_tiles, int q_sub, const float* __restrict__ theta0,
@@ -831,10 +836,33 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kerne
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int q = q0 + 64 * wq + 32 * t + l32;
-    thr[t] = q < Q ? float_below(theta0 ? theta0[q] : -__builtin_inff()) : __builtin_inff();
+    thr[t] = !kAll && q < Q ? float_below(theta0[q]) : __builtin_inff();
   }
   // Score acc[u][t][v] of this lane is row h0 + 128 wh + 4 half + r(i) for
   // bit i = 16 u + v, r(i) = 32 (i / 16) + 8 ((i / 4) % 4) + i % 4.
+  auto epi_all = [&](floatx16 (&acc)[4][2], int h0, int step_end) {
+    const int hl = h0 + 128 * wh + 4 * half;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int q = q0 + 64 * wq + 32 * t + l32;
+      if (q >= Q) continue;
+      uint64_t* dst = seg + ((size_t)q * n_chunks + chunk) * seg_cap;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+          const int h = hl + 32 * u + 2 * v, j = h - h_begin;      // rows h .. h + 3
+          // A quad that the chunk's end cuts is written whole: its segment is the
+          // chunk's own, a multiple of four keys, and the count leaves the rest out.
+          if (h < step_end && j < seg_cap) {
+            ulonglong2* to = reinterpret_cast<ulonglong2*>(dst + j);
+            to[0] = make_ulonglong2(make_key(acc[u][t][v], (uint32_t)h), make_key(acc[u][t][v + 1], (uint32_t)h + 1u));
+            to[1] = make_ulonglong2(make_key(acc[u][t][v + 2], (uint32_t)h + 2u),
+                                    make_key(acc[u][t][v + 3], (uint32_t)h + 3u));
+          }
+        }
+    }
+  };
   auto epi = [&](floatx16 (&acc)[4][2], int h0, int step_end) {
     const int lim = step_end - h0 - 128 * wh - 4 * half;     // r(i) < lim: row inside the step
     const int hl = h0 + 128 * wh + 4 * half;
@@ -981,9 +1009,14 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kerne
     if (__any(m_prev != 0)) write_column(1, m_prev, base_prev, f_prev, fv_prev);
   };
   const int n_steps = (h_end - h_begin + kStepRows - 1) / kStepRows;
-  ring::sweep<WQ>(hist, N, h_begin, kStepRows, n_steps, h_end, queries, Q, q0, d, lds, epi);
-  __syncthreads();
-  if (tid < S::kBQ && q0 + tid < Q) seg_count[(size_t)(q0 + tid) * n_chunks + chunk] = cnt[tid];
+  if constexpr (kAll) {
+    ring::sweep<WQ>(hist, N, h_begin, kStepRows, n_steps, h_end, queries, Q, q0, d, lds, epi_all);
+  } else {
+    ring::sweep<WQ>(hist, N, h_begin, kStepRows, n_steps, h_end, queries, Q, q0, d, lds, epi);
+    __syncthreads();
+  }
+  if (tid < S::kBQ && q0 + tid < Q)
+    seg_count[(size_t)(q0 + tid) * n_chunks + chunk] = kAll ? h_end - h_begin : cnt[tid];
 }
 
 template <int NQT, int KL>
@@ -1266,16 +1299,17 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     const Flagged fl{reinterpret_cast<int*>(ws + p.off_flags), reinterpret_cast<uint32_t*>(ws + p.off_flag_word)};
     {
       LaunchScope scope("sim_topk", stream);
-      const float* th = p.n_samples > 0 ? theta0 : nullptr;
       const dim3 grid((p.f_q_tiles * p.f_n_chunks + 7) / 8 * 8);
-      if (p.f_tile == 128)
-        hipLaunchKernelGGL(sim_filter_kernel<2>, grid, dim3(ring::Shape<2>::kThreads), 0, stream, queries, Q, hist, N,
-                           d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_sub, th, p.seg_cap, seg, segcnt,
-                           p.spill_cap, spill, spillcnt, fl.word);
-      else
-        hipLaunchKernelGGL(sim_filter_kernel<4>, grid, dim3(ring::Shape<4>::kThreads), 0, stream, queries, Q, hist, N,
-                           d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_sub, th, p.seg_cap, seg, segcnt,
-                           p.spill_cap, spill, spillcnt, fl.word);
+#define SAGE_FILTER(WQ, ALL)                                                                                       \
+  hipLaunchKernelGGL((sim_filter_kernel<WQ, ALL>), grid, dim3(ring::Shape<WQ>::kThreads), 0, stream, queries, Q,    \
+                     hist, N, d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_sub, theta0, p.seg_cap, seg, segcnt, \
+                     p.spill_cap, spill, spillcnt, fl.word)
+      if (p.n_samples > 0) {
+        if (p.f_tile == 128) SAGE_FILTER(2, false); else SAGE_FILTER(4, false);
+      } else {
+        if (p.f_tile == 128) SAGE_FILTER(2, true); else SAGE_FILTER(4, true);
+      }
+#undef SAGE_FILTER
     }
     const Candidates cand{seg, segcnt, p.f_n_chunks, p.seg_cap, spill, spillcnt, p.spill_cap};
     e = launch_select(cand, Q, k, min(k, N), fl, ids, sims, stream);

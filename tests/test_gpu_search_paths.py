@@ -103,14 +103,21 @@ def test_dense_search_edges(Q, N, d, k, layout):
     assert sage.predict_stats(ws, Q, N, d, k, 64)["path"] == "dense"
 
 
-@pytest.mark.parametrize("Q,N,k,path", [(1024, 300, 32, "dense"), (1025, 300, 32, "filtered"),
-                                        (1025, 2500, 100, "lists"), (3000, 40, 64, "filtered")])
-def test_batches_past_the_dense_search(Q, N, k, path):
-    print(f"case Q={Q} N={N} k={k}", flush=True)
-    w = workloads.small_predict(Q=Q, N=N, d=64, k=k, B=64, seed=Q + N + k, clusters=4)
-    ws = torch.empty(sage.predict_workspace_bytes(Q, N, 64, k, 64), dtype=torch.uint8, device="cuda")
+@pytest.mark.parametrize("Q,N,d,k,path", [
+    (1024, 300, 64, 32, "dense"), (1025, 300, 64, 32, "filtered"), (1025, 2500, 64, 100, "lists"),
+    (3000, 40, 64, 64, "filtered"),
+    # no pre-pass: every row of a chunk is a candidate
+    (1025, 8191, 32, 64, "filtered"),   # the largest such store, its last step and quad cut
+    (1300, 255, 64, 8, "filtered"),
+    (16000, 514, 32, 64, "filtered"),   # chunks of two steps and of two rows
+    (100, 1027, 8224, 64, "filtered"),  # the 128-query tile
+])
+def test_batches_past_the_dense_search(Q, N, d, k, path):
+    print(f"case Q={Q} N={N} d={d} k={k}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=64, seed=Q + N + k, clusters=4)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, 64), dtype=torch.uint8, device="cuda")
     check(w, k, "panels", ws)
-    assert sage.predict_stats(ws, Q, N, 64, k, 64)["path"] == path
+    assert sage.predict_stats(ws, Q, N, d, k, 64)["path"] == path
 
 
 @pytest.mark.parametrize("Q,k,path,cap", [
