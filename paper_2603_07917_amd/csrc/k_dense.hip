@@ -92,8 +92,8 @@ __global__ void __launch_bounds__(256, 2) dense_score_kernel(EmbView queries, in
 // saves its launch.
 template <int S, int kPer>
 __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restrict__ scores, int N, int ld, int k,
-                                                            int32_t* __restrict__ ids, float* __restrict__ sims,
-                                                            DenseHist h) {
+                                                            uint32_t* __restrict__ ran, int32_t* __restrict__ ids,
+                                                            float* __restrict__ sims, DenseHist h) {
   constexpr int KL = 64 * S;
   constexpr int W = 16;
   constexpr int kCap = 1024;
@@ -133,6 +133,7 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
     gmax[tid] = m;
   }
   if (tid == 0) {
+    if (ran && q == 0) *ran = kDenseRan;
     n_cand = 0;
     n_nbr = 0;
     w_all = 0;
@@ -233,22 +234,25 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
 }
 
 template <int S>
-void launch_dense_select(const float* scores, int Q, int N, int ld, int k, int32_t* ids, float* sims,
+void launch_dense_select(const float* scores, int Q, int N, int ld, int k, uint32_t* ran, int32_t* ids, float* sims,
                          const DenseHist& h, hipStream_t stream) {
   const size_t lds = h.B > 0 ? (size_t)h.B * 20 + 8 : 0;
   if (N <= 8192)
-    hipLaunchKernelGGL((dense_select_kernel<S, 8>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ids, sims, h);
+    hipLaunchKernelGGL((dense_select_kernel<S, 8>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ran, ids,
+                       sims, h);
   else if (N <= 16384)
-    hipLaunchKernelGGL((dense_select_kernel<S, 16>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ids, sims, h);
+    hipLaunchKernelGGL((dense_select_kernel<S, 16>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ran, ids,
+                       sims, h);
   else
-    hipLaunchKernelGGL((dense_select_kernel<S, 32>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ids, sims, h);
+    hipLaunchKernelGGL((dense_select_kernel<S, 32>), dim3(Q), dim3(1024), lds, stream, scores, N, ld, k, ran, ids,
+                       sims, h);
 }
 static_assert(kDenseMaxRows == 32 * 1024, "the last case holds the largest store");
 
 }  // namespace
 
 hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
-                        int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream) {
+                        uint32_t* ran, int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream) {
   if (Q <= 0 || Q > kDenseMaxQ || N <= 0 || N > kDenseMaxRows || ld < N || k < 1 || k > 256 || d % 32 != 0 ||
       d > kDenseMaxD || h.B > kDenseHistMaxBins) return hipErrorInvalidValue;
   {
@@ -270,9 +274,9 @@ hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int 
                          N, d, ld, scores);
   }
   LaunchScope scope(h.B > 0 ? "hist" : "topk_select", stream);   // the histogram ends it, where it is part
-  if (k <= 64) launch_dense_select<1>(scores, Q, N, ld, k, ids, sims, h, stream);
-  else if (k <= 128) launch_dense_select<2>(scores, Q, N, ld, k, ids, sims, h, stream);
-  else launch_dense_select<4>(scores, Q, N, ld, k, ids, sims, h, stream);
+  if (k <= 64) launch_dense_select<1>(scores, Q, N, ld, k, ran, ids, sims, h, stream);
+  else if (k <= 128) launch_dense_select<2>(scores, Q, N, ld, k, ran, ids, sims, h, stream);
+  else launch_dense_select<4>(scores, Q, N, ld, k, ran, ids, sims, h, stream);
   return hipGetLastError();
 }
 

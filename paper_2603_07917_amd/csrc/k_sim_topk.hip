@@ -1160,10 +1160,33 @@ void plan_workspace(SimTopkPlan* p, int Q, int L) {
   p->total_bytes = o;
 }
 
+bool dense_takes(int Q, int N, int d) {
+  return Q <= kDenseMaxQ && N <= kDenseMaxRows && d <= kDenseMaxD && (long)Q * N <= kDenseMaxScores;
+}
+// Whether writing every score out is the faster search, from its and the
+// filtered search's times (us, measured at k = 64 over 17 to 1,024 queries, 64
+// to 32,768 rows and d = 384 to 8,192, both layouts). Up to 256 queries it is,
+// or is at least no slower than any search was before it; for k > 64 the other
+// one is mostly the exact lists, two to three times slower. Past that its select
+// takes a workgroup of 16 waves per query, about 36 ns each, and every 32 x 32
+// tile fetches its own operands: 1.6e14 products a second, and 0.7e14 where
+// rows lie d apart, so that a load touches twice as many cache lines. The
+// filtered search is one round of tiles at these sizes, its time the latency of
+// d / 32 slices, twice that with a pre-pass. Dense / filtered, panels and rows:
+// 1,024 x 5,000 x 768 68 / 62 and 91 / 63, x 8,192 294 / 190 and 544 / 192;
+// 512 x 10,000 x 768 52 / 59 and 75 / 60; 512 x 5,000 x 384 36 / 54 and 43 / 54;
+// 1,024 x 64 x 384 45 / 28.
+bool dense_pays(int Q, int N, int d, int k, bool sampled, bool panels) {
+  if (!dense_takes(Q, N, d)) return false;
+  if (Q <= 256 || k > 64) return true;
+  const double dense = 4.0 + 0.036 * Q + (double)Q * N * d / (panels ? 1.6e8 : 0.7e8);
+  const double filtered = sampled ? 35.0 + d / 30.0 : std::min(48.0, 20.0 + 0.017 * N) + d / 60.0;
+  return dense <= filtered;
+}
+
 }  // namespace
 
-
-SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit) {
+SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit, PlanFor layout) {
   SimTopkPlan p{};
   int L = 64;
   while (L < k) L <<= 1;
@@ -1203,18 +1226,19 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit) {
     p.sample_every = (int)sr;
     p.n_samples = (int)((steps + sr - 1) / sr);
   }
-  // Small store and batch: every score written out (up to 20 MB of them). The
-  // select takes a workgroup of 16 waves per query whatever the store, about
-  // 36 ns a query from a few thousand queries on, where the filtered path has
-  // a wave per query: predict at d = 384, k = 64, dense against filtered,
-  // 1,000 x 2,000 48 / 82 us, 1,024 x 5,000 59 / 114, 2,048 x 2,500 91 / 94,
-  // 4,096 x 300 160 / 70, 16,384 x 300 613 / 170.
-  p.dense = Q <= kDenseMaxQ && N <= kDenseMaxRows && d <= kDenseMaxD && (long)Q * N <= kDenseMaxScores;
-  p.dense_ld = (N + 31) / 32 * 32;
-  if (p.dense) {
-    p.total_bytes = align256((size_t)Q * p.dense_ld * sizeof(float));
+  // Small store and batch: every score written out (up to 20 MB of them).
+  const size_t scores = align256((size_t)Q * ((N + 31) / 32 * 32) * sizeof(float));
+  auto dense = [&]() {
+    SimTopkPlan p{};
+    p.dense = true;
+    p.dense_ld = (N + 31) / 32 * 32;
+    p.total_bytes = scores;
     return p;
-  }
+  };
+  if (dense_pays(Q, N, d, k, p.n_samples > 0, false)) return dense();
+  // Where it pays on panels only, the layout decides: the workspace holds either
+  // search, and a word in it says which one ran.
+  const bool by_layout = dense_pays(Q, N, d, k, p.n_samples > 0, true);
   // Few queries against a large store: the stream path (one pass over the
   // store, bound by HBM), given a threshold pre-pass.
   p.stream = Q <= kStreamMaxQ && d <= kStreamMaxD && k <= 256 && p.n_samples > 0;
@@ -1262,6 +1286,16 @@ SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit) {
     while (p.s_cap < 4L * k * p.sample_every) p.s_cap *= 2;
   }
   plan_workspace(&p, Q, L);
+  if (by_layout && p.total_bytes + scores <= limit) {  // then k <= 64, on the filtered path
+    p.by_layout = true;
+    p.dense = layout == PlanFor::panels;
+    p.dense_ld = (N + 31) / 32 * 32;
+    p.off_scores = p.total_bytes;
+    p.total_bytes += scores;
+    return p;
+  }
+  if (scores <= limit && ((by_layout && layout == PlanFor::panels) ||
+                          (p.total_bytes > limit && dense_takes(Q, N, d)))) return dense();
   // The exact lists alone take less. They are three times slower (figures
   // above), so a search of k > 64 keeps to them only where the scratch is
   // given and holds them and not the candidates.
@@ -1280,7 +1314,8 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
   if (Q == 0) return hipSuccess;
   char* ws = static_cast<char*>(workspace);
   if (p.dense)
-    return launch_dense(queries, Q, hist, N, d, k, p.dense_ld, reinterpret_cast<float*>(ws + p.off_scores), ids, sims,
+    return launch_dense(queries, Q, hist, N, d, k, p.dense_ld, reinterpret_cast<float*>(ws + p.off_scores),
+                        p.by_layout ? reinterpret_cast<uint32_t*>(ws + p.off_flag_word) : nullptr, ids, sims,
                         hist_part, stream);
   uint64_t* partial = reinterpret_cast<uint64_t*>(ws + p.off_partial);
   uint64_t* merge_lists = reinterpret_cast<uint64_t*>(ws + p.off_merge);

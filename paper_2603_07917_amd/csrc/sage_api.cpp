@@ -333,6 +333,11 @@ SAGE_API size_t sage_predict_workspace_bytes(int Q, int N, int d, int k, int B) 
 }
 
 namespace {
+sage::PlanFor plan_for(int query_layout, int hist_layout) {
+  return query_layout == SAGE_LAYOUT_PANELS && hist_layout == SAGE_LAYOUT_PANELS ? sage::PlanFor::panels
+                                                                                 : sage::PlanFor::rows;
+}
+
 // The search and histogram with the plan for `scratch_limit` bytes.
 int predict_within(size_t scratch_limit, const uint16_t* queries, int query_layout, int Q, const uint16_t* hist_emb,
                    int hist_layout, const int32_t* hist_len, int N, int d, int k, float tau, const double* bin_edges,
@@ -352,7 +357,7 @@ int predict_within(size_t scratch_limit, const uint16_t* queries, int query_layo
     if (!ptrs[i]) return fail(SAGE_EINVAL, "sage_predict: %s is NULL", names[i]);
     if (!aligned16(ptrs[i])) return fail(SAGE_EINVAL, "sage_predict: %s is not 16-byte aligned", names[i]);
   }
-  const sage::SimTopkPlan plan = sage::plan_sim_topk(Q, N, d, k, scratch_limit);
+  const sage::SimTopkPlan plan = sage::plan_sim_topk(Q, N, d, k, scratch_limit, plan_for(query_layout, hist_layout));
   if (workspace_bytes < plan.workspace_bytes() || !workspace)
     return fail(SAGE_EWORKSPACE, "sage_predict: workspace of %zu bytes, %zu needed", workspace_bytes,
                 plan.workspace_bytes());
@@ -426,7 +431,8 @@ SAGE_API int sage_predict_noalloc(const uint16_t* queries, int query_layout, int
   if (st != SAGE_OK) return st;
   if (Q == 0) return sage_predict_layout(queries, query_layout, 0, hist_emb, hist_layout, hist_len, N, d, k, tau,
                                          bin_edges, B, nbr_ids, nbr_sims, counts, mass, nullptr, 0, stream);
-  const size_t need = sage::plan_sim_topk(Q, N, d, k, SAGE_NOALLOC_SCRATCH_BYTES).workspace_bytes();
+  const size_t need = sage::plan_sim_topk(Q, N, d, k, SAGE_NOALLOC_SCRATCH_BYTES, plan_for(query_layout, hist_layout))
+                          .workspace_bytes();
   if (need > (size_t)SAGE_NOALLOC_SCRATCH_BYTES)
     return fail(SAGE_EWORKSPACE, "sage_predict_noalloc: this search needs %zu bytes of scratch, the static "
                 "array holds %zu (use sage_predict_layout with a workspace)", need,
@@ -454,7 +460,15 @@ SAGE_API int sage_predict_stats(const void* workspace, size_t workspace_bytes, i
   hipStream_t s = (hipStream_t)stream;
   std::vector<int32_t> counts, flags;
   int per_query = 0, cap = 0;
-  if (plan.dense) {
+  bool dense = plan.dense;
+  if (plan.by_layout) {                      // the kernels that ran left a word that tells
+    uint32_t word = 0;
+    hipError_t e = hipMemcpyAsync(&word, ws + plan.off_flag_word, sizeof word, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_status(e, "sage_predict_stats copy");
+    dense = word == sage::kDenseRan;
+  }
+  if (dense) {
     stats[0] = 3;
     stats[1] = (long long)Q * N;
     stats[3] = 1;

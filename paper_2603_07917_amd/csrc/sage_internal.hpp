@@ -59,6 +59,7 @@ struct SimTopkPlan {
   // small stores: every score written out (row pitch in scores)
   bool dense;
   int dense_ld;
+  bool by_layout;   // workspace for this and the filtered path: the operands' layout decides between them
   // few-query stream path (Q <= kStreamMaxQ, any k <= 256)
   bool stream;
   int s_chunk_rows; // history rows per workgroup
@@ -70,7 +71,10 @@ struct SimTopkPlan {
 };
 // `limit`: scratch bytes that the search has to do with. A plan that needs more
 // is returned only when no other fits either.
-SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit = SIZE_MAX);
+// `layout`: panels when both operands are; rows when one is not; any where the
+// layouts are not known (the workspace is then the same, the path may not be).
+enum class PlanFor { any, rows, panels };
+SimTopkPlan plan_sim_topk(int Q, int N, int d, int k, size_t limit = SIZE_MAX, PlanFor layout = PlanFor::any);
 // Few-query stream path: limits, and the search + candidate select.
 constexpr int kStreamMaxQ = 16;
 constexpr int kStreamMaxD = 2048;
@@ -84,7 +88,7 @@ float debug_theta_floor();
 // their arrays hold, or fewer than min(k, N)), and *word = 1 once any query is
 // flagged. The search's first kernel that always runs (the
 // filter kernel, the stream search) clears the word, so that the fallback
-// kernels return at once when it is still 0; nothing here depends on the
+// kernels return at once when it is still 0 (kDenseRan: see launch_dense); nothing here depends on the
 // call, so a captured graph replays it as it stands.
 enum FlagReason { kNotFlagged = 0, kOverflowed = 1, kTooFew = 2 };
 struct Flagged {
@@ -126,8 +130,10 @@ struct DenseHist {
   int32_t* counts = nullptr;
   float* mass = nullptr;
 };
+// `ran`: set to kDenseRan, for plans whose path the sizes do not tell.
+constexpr uint32_t kDenseRan = 2;
 hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
-                        int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream);
+                        uint32_t* ran, int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream);
 
 hipError_t launch_stream_search(EmbView queries, int Q, EmbView hist, int N, int d, int chunk_rows,
                                 const float* theta0, int cap, uint64_t* cand, int* cand_count, uint32_t* flag_word,

@@ -104,7 +104,9 @@ def test_dense_search_edges(Q, N, d, k, layout):
 
 
 @pytest.mark.parametrize("Q,N,d,k,path", [
-    (1024, 300, 64, 32, "dense"), (1025, 300, 64, 32, "filtered"), (1025, 2500, 64, 100, "lists"),
+    (256, 300, 64, 32, "dense"), (1024, 2000, 64, 32, "dense"), (1025, 300, 64, 32, "filtered"),
+    (1024, 300, 64, 32, "filtered"),    # few rows: a workgroup of 16 waves per query is too many
+    (1024, 300, 64, 65, "dense"), (1025, 2500, 64, 100, "lists"),
     (3000, 40, 64, 64, "filtered"),
     # no pre-pass: every row of a chunk is a candidate
     (1025, 8191, 32, 64, "filtered"),   # the largest such store, its last step and quad cut
@@ -118,6 +120,38 @@ def test_batches_past_the_dense_search(Q, N, d, k, path):
     ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, 64), dtype=torch.uint8, device="cuda")
     check(w, k, "panels", ws)
     assert sage.predict_stats(ws, Q, N, d, k, 64)["path"] == path
+
+
+@pytest.mark.parametrize("Q,N,d,k", [(512, 10000, 768, 64), (1024, 2500, 384, 32), (300, 6000, 4096, 50)])
+def test_search_chosen_by_layout(Q, N, d, k):
+    """Sizes at which panels are searched by writing every score out and rows are
+    filtered: one workspace serves both in turn, predict_stats tells which ran,
+    and the bits are the same; one operand in rows counts as rows."""
+    B = 64
+    print(f"case Q={Q} N={N} d={d} k={k}", flush=True)
+    w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=Q + N + k, clusters=8)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, B), dtype=torch.uint8, device="cuda")
+    hist_len, edges = dev(w.hist_len), dev(w.bin_edges)
+    emb = {lay: (sage.ingest_bf16(dev(w.queries), lay), sage.ingest_bf16(dev(w.hist_emb), lay))
+           for lay in ("rows", "panels")}
+    outs = []
+    for ql, hl, path in (("panels", "panels", "dense"), ("rows", "rows", "filtered"), ("panels", "panels", "dense"),
+                         ("rows", "panels", "filtered"), ("panels", "rows", "filtered")):
+        out = sage.predict(emb[ql][0], emb[hl][1], hist_len, k, 0.8, edges, workspace=ws)
+        stats = sage.predict_stats(ws, Q, N, d, k, B)
+        assert stats["path"] == path and stats["flagged"] == 0, (ql, hl)
+        outs.append([host(t) for t in out])
+        if Q * 8192 * 8 < 60 << 20 and N < 9000:      # both fit the static scratch: either way without a workspace
+            again = [torch.full_like(t, 7) for t in out]
+            assert sage.load_library().sage_predict_noalloc(
+                emb[ql][0].data_ptr(), sage.LAYOUTS[ql], Q, emb[hl][1].data_ptr(), sage.LAYOUTS[hl], hist_len.data_ptr(),
+                N, d, k, 0.8, edges.data_ptr(), B, *[t.data_ptr() for t in again], sage._stream()) == 0
+            outs.append([host(t) for t in again])
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+    S = oracle.similarity(oracle.round_to_bf16(w.queries), oracle.round_to_bf16(w.hist_emb))
+    parity.check_predict(*outs[0], S, w.hist_len, w.bin_edges, 0.8, k)
 
 
 @pytest.mark.parametrize("Q,k,path,cap", [
