@@ -60,15 +60,34 @@ class Decision:
         return [t.cpu().numpy().copy() for t in self.out]
 
 
+class OneCall(Decision):
+    """The same by sage_decide."""
+
+    def __init__(self, w):
+        super().__init__(w)
+        need = sage.load_library().sage_decide_workspace_bytes(2, self.Q, self.N, self.d, self.k, self.B)
+        self.ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+
+    def step(self):
+        sage._check(sage.load_library().sage_decide(
+            self.queries.data_ptr(), 2, self.Q, self.hist.data_ptr(), PANELS, self.hist_len.data_ptr(), self.N, self.d,
+            self.k, self.tau, self.edges.data_ptr(), self.plen.data_ptr(), self.repr.data_ptr(), self.B,
+            *[t.data_ptr() for t in self.out], self.ws.data_ptr(), self.ws.numel(),
+            torch.cuda.current_stream().cuda_stream))
+
+
 @pytest.mark.parametrize("Q,N,d,k,B", [
     (300, 40000, 64, 32, 64),       # filtered path with its threshold pre-pass; counting rank
     (8, 70000, 96, 128, 128),       # stream path
-    (20000, 30000, 64, 16, 32),     # filtered path; the radix rank (more than 16,384 requests)
+    (16, 10000, 96, 64, 128),       # dense path, which bins its neighbours
+    (20000, 30000, 64, 16, 32),     # filtered path; the rank by merged tiles
+    (131100, 300, 64, 8, 16),       # filtered path without a threshold; the radix rank (more than 131,072 requests)
 ])
-def test_decision_replays_in_a_hip_graph(Q, N, d, k, B):
-    print(f"case Q={Q} N={N} d={d} k={k} B={B}", flush=True)
+@pytest.mark.parametrize("one_call", [False, True])
+def test_decision_replays_in_a_hip_graph(Q, N, d, k, B, one_call):
+    print(f"case Q={Q} N={N} d={d} k={k} B={B} one_call={one_call}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=Q + N + k, clusters=6)
-    dec = Decision(w)
+    dec = (OneCall if one_call else Decision)(w)
     dec.step()
     eager = dec.snapshot()
 

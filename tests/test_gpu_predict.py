@@ -46,40 +46,61 @@ def check_decision(w, rows, ids, sims, counts, mass, g, order, k, tau):
     return int(clean.sum())
 
 
-# (Q, N, d, k, B): several query tiles with a ragged tail, history chunks and
-# 256-row steps with ragged ends, d with a half 64-wide slice, every list length.
+# (Q, N, d, k, B, search path): several query tiles with a ragged tail, history
+# chunks and 256-row steps with ragged ends, d with a half 64-wide slice, every
+# list length.
 CASES = [
-    (70, 3000, 64, 8, 16),
-    (130, 5000, 96, 32, 128),
-    (64, 4096, 384, 64, 64),
-    (65, 7777, 128, 100, 256),
-    (40, 3001, 32, 200, 64),
-    (33, 2500, 64, 256, 1024),
-    (5, 300, 64, 1, 7),
-    (3, 10, 64, 32, 16),        # N < k: padded with -1 / -inf
-    (8, 300000, 64, 128, 512),  # few queries, hundreds of chunk lists: two-level merge
-    (8, 200000, 32, 200, 64),
-    # few queries (at most 16): the stream search over the store
-    (1, 50001, 768, 64, 256),
-    (16, 70000, 96, 256, 64),
-    (7, 33333, 2048, 100, 128),
-    (16, 20000, 64, 1, 16),
-    (9, 65536, 32, 64, 32),
-    (4, 40000, 2080, 32, 64),   # d above the stream path's limit: the list path
-    (17, 30000, 64, 100, 64),   # one query past the stream path: the list path
-    (17, 30000, 64, 64, 64),    # ... and the filtered path
-    (4, 16384, 64, 128, 32),    # the smallest store with a threshold sample at k = 128: stream path
-    (4, 16383, 64, 128, 32),    # one row less: no sample, the list path without a threshold
+    (70, 3000, 64, 8, 16, "dense"),
+    (130, 5000, 96, 32, 128, "dense"),
+    (64, 4096, 384, 64, 64, "dense"),
+    (65, 7777, 128, 100, 256, "dense"),
+    (40, 3001, 32, 200, 64, "dense"),
+    (33, 2500, 64, 256, 1024, "dense"),
+    (5, 300, 64, 1, 7, "dense"),
+    (3, 10, 64, 32, 16, "dense"),          # N < k: padded with -1 / -inf
+    (8, 300000, 64, 128, 512, "stream"),
+    (8, 200000, 32, 200, 64, "stream"),
+    # few queries (at most 16) against more rows than are all written out
+    (1, 50001, 768, 64, 256, "stream"),
+    (16, 70000, 96, 256, 64, "stream"),
+    (7, 33333, 2048, 100, 128, "stream"),
+    (9, 65536, 32, 64, 32, "stream"),
+    (1, 32769, 64, 1, 16, "stream"),       # the smallest store past those
+    (16, 20000, 64, 1, 16, "dense"),
+    (4, 40000, 2080, 32, 64, "filtered"),  # d above the stream path's limit
+    (4, 40000, 2080, 100, 64, "filtered"),
+    (17, 40000, 64, 100, 64, "filtered"),  # one query past the stream path
+    (17, 40000, 64, 64, 64, "filtered"),
+    (17, 30000, 64, 64, 64, "dense"),
+    (70, 9000, 8224, 65, 16, "filtered"),  # d above the dense path's limit, the smallest pre-pass at k = 65
+    (4, 16384, 64, 128, 32, "dense"),
+    (4, 16384, 8224, 128, 32, "filtered"),
+    # k > 64 and too few rows for a threshold sample: the exact lists, of both lengths
+    (4, 16383, 8224, 128, 32, "lists"),
+    (40, 16383, 8224, 200, 32, "lists"),
+    (1100, 7777, 64, 100, 64, "lists"),
+    (1100, 5000, 96, 256, 16, "lists"),
 ]
 
 
-@pytest.mark.parametrize("Q,N,d,k,B", CASES)
-def test_predict_small_vs_oracle(Q, N, d, k, B):
-    print(f"case Q={Q} N={N} d={d} k={k} B={B}", flush=True)
+def check_path(Q, N, d, k, B, path, layouts=("rows", "rows")):
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, B), dtype=torch.uint8, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    emb = [sage.ingest_bf16(torch.randn((n, d), generator=g, device="cuda") / d ** 0.5, lay)
+           for n, lay in zip((Q, N), layouts)]
+    edges = torch.arange(B + 1, dtype=torch.float64, device="cuda")
+    sage.predict(*emb, torch.ones(N, dtype=torch.int32, device="cuda"), k, 0.8, edges, workspace=ws)
+    assert sage.predict_stats(ws, Q, N, d, k, B)["path"] == path
+
+
+@pytest.mark.parametrize("Q,N,d,k,B,path", CASES)
+def test_predict_small_vs_oracle(Q, N, d, k, B, path):
+    print(f"case Q={Q} N={N} d={d} k={k} B={B} {path}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=Q + N + d + k, clusters=6)
     ids, sims, counts, mass = run_predict(w, k)
     S = oracle_scores(w)
     parity.check_predict(ids, sims, counts, mass, S, w.hist_len, w.bin_edges, 0.8, k)
+    check_path(Q, N, d, k, B, path)
 
 
 def test_panels_ingest_bit_exact():
@@ -95,18 +116,20 @@ def test_panels_ingest_bit_exact():
         assert torch.equal(sage.to_panels(rows).view(torch.int16), expect.view(torch.int16))
 
 
-LAYOUT_CASES = CASES + [(12, 12000, 64, 8, 16)]
+LAYOUT_CASES = CASES + [(12, 12000, 64, 8, 16, "dense"), (12, 60000, 64, 8, 16, "stream"),
+                        (40, 60000, 64, 8, 16, "filtered")]
 
 
-@pytest.mark.parametrize("Q,N,d,k,B", LAYOUT_CASES)
-def test_predict_panels_identical_to_rows(Q, N, d, k, B):
-    """Every search path (filtered, exact lists, two-level merge, fallback)
-    gives bit-identical outputs on panel-major and row-major operands."""
-    print(f"case Q={Q} N={N} d={d} k={k} B={B}", flush=True)
+@pytest.mark.parametrize("Q,N,d,k,B,path", LAYOUT_CASES)
+def test_predict_panels_identical_to_rows(Q, N, d, k, B, path):
+    """Every search path (dense, filtered, stream, exact lists, fallback) gives
+    bit-identical outputs on panel-major and row-major operands."""
+    print(f"case Q={Q} N={N} d={d} k={k} B={B} {path}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=Q + N + d + k, clusters=6)
-    if (Q, N) == (12, 12000):                      # overflowing candidates: the exact fallback
-        w.hist_emb[:6000] = w.hist_emb[6000]
-        w.queries[:6] = w.hist_emb[6000]
+    if N in (12000, 60000):                        # many equal scores; past the dense path the exact fallback
+        w.hist_emb[:N // 2] = w.hist_emb[N // 2]
+        w.queries[:6] = w.hist_emb[N // 2]
+    check_path(Q, N, d, k, B, path, ("panels", "panels"))
     qf, hf, hl, be = dev(w.queries), dev(w.hist_emb), dev(w.hist_len), dev(w.bin_edges)
     ref = [host(t) for t in sage.predict(sage.ingest_bf16(qf), sage.ingest_bf16(hf), hl, k, 0.8, be)]
     for ql, hlay in [("panels", "panels"), ("rows", "panels"), ("panels", "rows")]:
@@ -151,16 +174,23 @@ def test_predict_duplicate_rows_lower_id_first():
         assert ids[q, 0] == 100
 
 
-def test_predict_candidate_overflow_takes_exact_fallback():
+@pytest.mark.parametrize("Q,N,path", [(12, 12000, "dense"), (12, 60000, "stream"), (40, 60000, "filtered")])
+def test_predict_many_equal_rows(Q, N, path):
     # Half of the store repeats one vector: queries equal to it see thousands of
-    # tied scores (far more survivors than the filtered path keeps), which must
-    # be answered exactly by the fallback; the other queries take the fast path.
-    w = workloads.small_predict(Q=12, N=12000, d=64, k=8, B=16, seed=21, clusters=4)
+    # tied scores. The dense search answers them by folding them all; past it
+    # they are far more survivors than are kept and go to the exact fallback,
+    # while the other queries take the fast path.
+    w = workloads.small_predict(Q=Q, N=N, d=64, k=8, B=16, seed=21, clusters=4)
     h = w.hist_emb.copy()
-    h[:6000] = h[6000]
+    h[:N // 2] = h[N // 2]
     w.hist_emb = h
-    w.queries[:6] = h[6000]
-    ids, sims, counts, mass = run_predict(w, 8)
+    w.queries[:6] = h[N // 2]
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, 64, 8, 16), dtype=torch.uint8, device="cuda")
+    ids, sims, counts, mass = [host(t) for t in sage.predict(
+        sage.ingest_bf16(dev(w.queries)), sage.ingest_bf16(dev(w.hist_emb)), dev(w.hist_len), 8, 0.8,
+        dev(w.bin_edges), workspace=ws)]
+    stats = sage.predict_stats(ws, Q, N, 64, 8, 16)
+    assert stats["path"] == path and (stats["flagged"] >= 6) == (path != "dense")
     S = oracle_scores(w)
     assert list(ids[0]) == list(range(8))          # all tied: lowest indices first
     parity.check_predict(ids, sims, counts, mass, S, w.hist_len, w.bin_edges, 0.8, 8)

@@ -43,11 +43,15 @@ def check(w, k, layout, workspace=None):
     (300, 40000, 96, 65, "rows"),       # two list registers per lane, four waves per query
     (129, 65537, 32, 256, "panels"),    # four list registers, sixteen waves
     (2100, 33000, 32, 200, "rows"),     # ... and one wave per query
+    (2100, 33000, 32, 128, "panels"),   # two list registers and one wave per query
 ])
 def test_filtered_search_edges(Q, N, d, k, layout):
     print(f"case Q={Q} N={N} d={d} k={k} {layout}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=64, seed=Q + N + k, clusters=12)
-    check(w, k, layout)
+    ws = torch.empty(sage.predict_workspace_bytes(Q, N, d, k, 64), dtype=torch.uint8, device="cuda")
+    check(w, k, layout, ws)
+    stats = sage.predict_stats(ws, Q, N, d, k, 64)
+    assert stats["path"] == "filtered" and stats["flagged"] == 0
 
 
 @pytest.mark.parametrize("Q,k", [(300, 100), (40, 256)])
@@ -189,17 +193,20 @@ def test_overflowing_candidates_take_the_exact_path(Q, k, path, cap, layout):
 
 
 @pytest.mark.parametrize("Q,N,k", [(2047, 100000, 128), (2048, 100000, 128), (1001, 100003, 128), (481, 60001, 256),
-                                   (963, 50000, 100)])
+                                   (963, 50000, 100), (327, 500000, 256)])
 def test_long_lists_of_any_batch_are_filtered(Q, N, k):
     """k > 64 with a workspace of its own takes the filtered search, whether or
     not the exact lists would fit the scratch of sage_predict_noalloc; that call
-    takes them there, and gives the same bits."""
+    takes them where only they fit (all but the fourth: lists of 128 and, the
+    last, 256 keys, with the threshold of their own sample), and gives the same
+    bits."""
     d, B = 32, 16
     print(f"case Q={Q} N={N} k={k}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=B, seed=Q + N + k, clusters=12)
     qb, hb = sage.ingest_bf16(dev(w.queries), "panels"), sage.ingest_bf16(dev(w.hist_emb), "panels")
     hist_len, edges = dev(w.hist_len), dev(w.bin_edges)
     need = sage.predict_workspace_bytes(Q, N, d, k, B)
+    assert (need > 64 << 20) == (Q != 481)
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     out = sage.predict(qb, hb, hist_len, k, 0.8, edges, workspace=ws)
     stats = sage.predict_stats(ws, Q, N, d, k, B)

@@ -47,17 +47,22 @@ def oracle_scores(w):
 def sample_every(Q, N, d, k):
     """The pre-pass's step stride as the library plans it: every SR-th whole
     256-row step, SR chosen for >= 4k group maxima (16 per step), at most 128
-    on the stream path (at most 16 queries), else at most 16 for k <= 64 on a
-    store below 2^29 elements and 32 otherwise, and at most 512 sampled steps."""
+    on the stream path (at most 16 queries), else 16, and 32 for k <= 64 on a
+    store of 2^29 elements and more; at most 512 sampled steps; halved for more
+    than 128 queries while the samples of all 256-query tiles are at most 256,
+    and a query's at most 128 (64 from 512 queries on)."""
     steps = N // 256
-    L = max(64, 1 << (k - 1).bit_length())
     assert steps * 16 >= 8 * k, "store too small for a pre-pass"
     wide = Q > 16 and N * d >= (1 << 29)
     few = Q <= 16 and d <= STREAM_MAX_D and k <= 256
-    sr_max = 128 if few else (16 if (L == 64 and not wide) else 32)
+    sr_max = 128 if few else (32 if k <= 64 and wide else 16)
     sr = max(1, min(sr_max, steps * 16 // (4 * k)))
     while -(-steps // sr) > 512:
         sr += 1
+    if Q > 128:
+        most = min(256 // -(-Q // 256), 64 if Q >= 512 else 128)
+        while sr > 1 and -(-steps // (sr // 2)) <= most:
+            sr //= 2
     return sr
 
 
@@ -77,9 +82,11 @@ def plant_kth_equals_theta(w, q, k, sr):
     return rows
 
 
-@pytest.mark.parametrize("Q,k", [(1, 64), (8, 128), (16, 256), (5, 32), (64, 64), (300, 16)])
+@pytest.mark.parametrize("Q,k", [(1, 64), (8, 128), (16, 256), (5, 32), (64, 64), (300, 16), (64, 128), (200, 100),
+                                 (600, 200)])
 def test_theta_equals_kth_score(Q, k):
-    """Q <= 16: the stream path; larger Q with k <= 64: the filtered path."""
+    """Q <= 16: the stream path; larger Q: the filtered path, whose 128-query
+    tile takes up to 128."""
     N, d = 262144, 128
     print(f"case Q={Q} k={k}", flush=True)
     w = workloads.small_predict(Q=Q, N=N, d=d, k=k, B=64, seed=500 + Q + k, clusters=8)
@@ -90,8 +97,9 @@ def test_theta_equals_kth_score(Q, k):
     for q in planted:
         assert len(set(planted[q].tolist())) == k
     ids, sims, counts, mass = run_predict(w, k)
-    S = oracle_scores(w)
-    parity.check_predict(ids, sims, counts, mass, S, w.hist_len, w.bin_edges, 0.8, k)
+    some = np.unique(np.concatenate([np.arange(min(Q, 64)), [Q - 1]]))
+    S = oracle.similarity(oracle.round_to_bf16(w.queries[some]), oracle.round_to_bf16(w.hist_emb))
+    parity.check_predict(ids[some], sims[some], counts[some], mass[some], S, w.hist_len, w.bin_edges, 0.8, k)
     for q, rows in planted.items():
         assert np.all(w.hist_emb[rows] == w.queries[q])
         assert set(ids[q].tolist()) == set(rows.tolist()), f"query {q}: its {k} copies are its neighbours"

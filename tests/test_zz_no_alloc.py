@@ -43,6 +43,7 @@ def noalloc(lib, qb, ql, hb, hl, hist_len, N, d, k, tau, edges, B, out):
 # large store, then smaller inputs on the stream and filtered paths
 CALLS = [(8, 400000, 256, 128, 256, "panels", "panels"),
          (5, 100000, 128, 64, 64, "panels", "rows"),
+         (40, 50000, 64, 16, 32, "rows", "panels"),
          (40, 20000, 64, 16, 32, "rows", "panels")]
 
 
