@@ -799,17 +799,23 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) threshold_sample
 // query's spill[q][0..spill_cap): a chunk whose rows are alike fills its
 // segment without sending the query to the exact path.
 //
-// kAll: a store too small for a pre-pass, no threshold, every row of a chunk a
+// A kernel without spill array is an instance of its own: with the spill code
+// and the threshold that it changes in it, the largest batches, which have
+// none, took 1.3% more (28.36 against 28.74 ms at 16,384 x 1M x 1,024).
+//
+// kAllRows: a store too small for a pre-pass, no threshold, every row of a chunk a
 // candidate. Row h of the chunk goes to place h - h_begin of its segment, four
 // keys to two stores. Found and picked one by one, 16,000 queries against 2,000
 // rows (d = 384) took 565 us a predict, so 243; 60,000 against 1,000 1,194, 520.
-template <int WQ, bool kAll>
+enum FilterMode { kSegments, kSpill, kAllRows };
+template <int WQ, FilterMode kMode>
 __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kernel(
     EmbView queries, int Q, EmbView hist, int N, int d,
     int chunk_rows, int n_chunks, int q_tiles, int q_sub, const float* __restrict__ theta0,
     int seg_cap, uint64_t* __restrict__ seg, int* __restrict__ seg_count, int spill_cap,
     uint64_t* __restrict__ spill, int* __restrict__ spill_count, uint32_t* __restrict__ flag_word) {
   using S = ring::Shape<WQ>;
+  constexpr bool kAll = kMode == kAllRows;
   __shared__ __align__(16) char lds[S::kStages * S::kStageBytes];
   if (blockIdx.x == 0 && threadIdx.x == 0) *flag_word = 0u;     // set again by the select if it flags a query
   __shared__ int cnt[S::kBQ];
@@ -955,7 +961,7 @@ __global__ void __launch_bounds__(ring::Shape<WQ>::kThreads, 2) sim_filter_kerne
           rest |= (uint64_t)(bits & (bits - 1u)) << (16 * u);
         }
       }
-      if (spill_cap > 0 && __any(m != 0 && base + __popcll(m) > seg_cap)) spill_column(t, m, base);
+      if (kMode == kSpill && __any(m != 0 && base + __popcll(m) > seg_cap)) spill_column(t, m, base);
       if (!__any(rest != 0)) return;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -1335,14 +1341,16 @@ hipError_t launch_neighbours(EmbView queries, int Q, EmbView hist, int N, int d,
     {
       LaunchScope scope("sim_topk", stream);
       const dim3 grid((p.f_q_tiles * p.f_n_chunks + 7) / 8 * 8);
-#define SAGE_FILTER(WQ, ALL)                                                                                       \
-  hipLaunchKernelGGL((sim_filter_kernel<WQ, ALL>), grid, dim3(ring::Shape<WQ>::kThreads), 0, stream, queries, Q,    \
+#define SAGE_FILTER(WQ, MODE)                                                                                      \
+  hipLaunchKernelGGL((sim_filter_kernel<WQ, MODE>), grid, dim3(ring::Shape<WQ>::kThreads), 0, stream, queries, Q,   \
                      hist, N, d, p.f_chunk_rows, p.f_n_chunks, p.f_q_tiles, p.f_q_sub, theta0, p.seg_cap, seg, segcnt, \
                      p.spill_cap, spill, spillcnt, fl.word)
-      if (p.n_samples > 0) {
-        if (p.f_tile == 128) SAGE_FILTER(2, false); else SAGE_FILTER(4, false);
+      if (p.n_samples == 0) {
+        if (p.f_tile == 128) SAGE_FILTER(2, kAllRows); else SAGE_FILTER(4, kAllRows);
+      } else if (p.spill_cap > 0) {
+        if (p.f_tile == 128) SAGE_FILTER(2, kSpill); else SAGE_FILTER(4, kSpill);
       } else {
-        if (p.f_tile == 128) SAGE_FILTER(2, true); else SAGE_FILTER(4, true);
+        if (p.f_tile == 128) SAGE_FILTER(2, kSegments); else SAGE_FILTER(4, kSegments);
       }
 #undef SAGE_FILTER
     }
