@@ -520,8 +520,13 @@ class Store:
     def _library_predict(self) -> bool:
         """Whether predict, and every predict that it may call through super(),
         is the library's own."""
-        return "predict" not in self.__dict__ and all(
-            c.__dict__["predict"] in _LIBRARY_PREDICT for c in type(self).__mro__ if "predict" in c.__dict__)
+        if "predict" in self.__dict__:
+            return False
+        for c in type(self).__mro__:
+            p = c.__dict__.get("predict")
+            if p is not None and p not in _LIBRARY_PREDICT:
+                return False
+        return True
 
     def _decide_once(self, queries: torch.Tensor, f32: bool, prompt_len: torch.Tensor, out):
         """decide() as one library call, or None where a check of the separate
