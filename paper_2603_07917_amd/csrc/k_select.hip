@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) select_kernel(Candidate
   if (over || all + n_spill < need) {                 // the same for every wave of the query
     if (lane == 0 && w == 0) {
       fl.flags[q] = over ? kOverflowed : kTooFew;
-      *fl.word = 1u;
+      atomicAdd(fl.word, 1u);
     }
     return;
   }

@@ -57,8 +57,11 @@ struct Core {
   // Loads are unconditional (rows clamped into range) so that no branch sits
   // around them; only the zero-fill of columns past d is a select. Rows past
   // h_end and queries past Q carry real but unused data (masked later).
+  // The query whose columns this thread's c-th load of a slice fetches: slot
+  // (that load's row) of the tile.
+  static __device__ __forceinline__ int slot(int c) { return min(c * kThreads + (int)threadIdx.x, B_CHUNKS - 1) >> 3; }
   __device__ __forceinline__ void load(const EmbView& hist, int h0, int h_last, const EmbView& queries,
-                                       int q0, int q_last, int d, int kt) {
+                                       const int (&q_of)[B_LD], int d, int kt) {
     const int tid = threadIdx.x;
     const int k0 = kt * kKT;
 #pragma unroll
@@ -72,9 +75,8 @@ struct Core {
 #pragma unroll
     for (int c = 0; c < B_LD; ++c) {
       const int f = min(c * kThreads + tid, B_CHUNKS - 1);
-      const int row = f >> 3, col = k0 + (f & 7) * 8;
-      const int q = min(q0 + row, q_last);
-      const uint4 v = *reinterpret_cast<const uint4*>(emb_at(queries, q, min(col, d - 8)));
+      const int col = k0 + (f & 7) * 8;
+      const uint4 v = *reinterpret_cast<const uint4*>(emb_at(queries, q_of[c], min(col, d - 8)));
       rb[c] = col < d ? v : make_uint4(0, 0, 0, 0);
     }
   }
@@ -115,11 +117,12 @@ __device__ __forceinline__ void mfma_slice(floatx16 (&acc)[2][NQT], const uint16
 }
 
 // Scores of one step: acc[u][t][v] = S[h][q] with
-//   h = h0 + 64w + 32u + 8(v/4) + 4*half + (v%4),  q = q0 + 32t + l32.
+//   h = h0 + 64w + 32u + 8(v/4) + 4*half + (v%4),  q = the tile's query 32t + l32
+// (q_of: those whose columns this thread loads).
 template <int NQT>
 __device__ __forceinline__ void gemm_step(floatx16 (&acc)[2][NQT], const EmbView& hist, int h0, int h_end,
-                                          const EmbView& queries, int q0, int Q, int d, uint16_t* a_tile,
-                                          uint16_t* b_tile) {
+                                          const EmbView& queries, const int (&q_of)[Core<NQT>::B_LD], int d,
+                                          uint16_t* a_tile, uint16_t* b_tile) {
   const int lane = (int)lane_id();
   const int w = threadIdx.x / kWave;
   const int l32 = lane & 31, half = lane >> 5;
@@ -130,14 +133,14 @@ __device__ __forceinline__ void gemm_step(floatx16 (&acc)[2][NQT], const EmbView
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[u][t][v] = 0.0f;
   const int nk = (d + kKT - 1) / kKT;
-  const int h_last = h_end - 1, q_last = Q - 1;
+  const int h_last = h_end - 1;
   Core<NQT> core;
-  core.load(hist, h0, h_last, queries, q0, q_last, d, 0);
+  core.load(hist, h0, h_last, queries, q_of, d, 0);
   for (int kt = 0; kt + 1 < nk; ++kt) {
     __syncthreads();
     core.store(a_tile, b_tile);
     __syncthreads();
-    core.load(hist, h0, h_last, queries, q0, q_last, d, kt + 1);
+    core.load(hist, h0, h_last, queries, q_of, d, kt + 1);
     mfma_slice<NQT>(acc, a_tile, b_tile, w, l32, half);
   }
   __syncthreads();
@@ -200,8 +203,11 @@ __global__ void __launch_bounds__(kThreads, 1) threshold_sample_kernel(
   const int s = blockIdx.y;
   const int h0 = s * sample_every * kStepRows;
   const int h_end = min(N, h0 + kStepRows);
+  int q_of[Core<NQT>::B_LD];
+#pragma unroll
+  for (int c = 0; c < Core<NQT>::B_LD; ++c) q_of[c] = min(q0 + Core<NQT>::slot(c), Q - 1);
   floatx16 acc[2][NQT];
-  gemm_step<NQT>(acc, hist, h0, h_end, queries, q0, Q, d, a_tile, b_tile);
+  gemm_step<NQT>(acc, hist, h0, h_end, queries, q_of, d, a_tile, b_tile);
 
   const int lane = (int)lane_id();
   const int w = threadIdx.x / kWave;
@@ -239,14 +245,43 @@ struct TopkSmem {
   int tot[BQ];
   int cnt[BQ * 8];
   int rounds;
+  int query[BQ];                           // the tile's queries
+  int wave_n[kThreads / kWave];
 };
 
-// One (query tile, history chunk) of the list search.
+// The flagged queries of ranks q0 .. q0 + BQ - 1 among all flagged ones, in
+// order, to sm.query. Every thread of the workgroup calls it.
+template <int NQT, int KL>
+__device__ __forceinline__ void gather_flagged(TopkSmem<NQT, KL>& sm, const int* __restrict__ flags, int Q, int q0) {
+  constexpr int BQ = 32 * NQT;
+  const int tid = threadIdx.x;
+  const int w = tid / kWave;
+  const uint64_t below = (1ull << lane_id()) - 1ull;
+  int found = 0;
+  for (int base = 0; base < Q && found < q0 + BQ; base += kThreads) {
+    const bool on = base + tid < Q && flags[base + tid] != kNotFlagged;
+    const uint64_t mask = __ballot(on);
+    if (lane_id() == 0) sm.wave_n[w] = __popcll(mask);
+    __syncthreads();
+    int rank = found + __popcll(mask & below);
+#pragma unroll
+    for (int i = 0; i < kThreads / kWave; ++i) {
+      if (i < w) rank += sm.wave_n[i];
+      found += sm.wave_n[i];
+    }
+    if (on && rank >= q0 && rank < q0 + BQ) sm.query[rank - q0] = base + tid;
+    __syncthreads();                       // wave_n read; query complete
+  }
+}
+
+// One (query tile, history chunk) of the list search: of all Q queries, or as
+// the exact fallback of the n_flagged queries that are flagged, whose tiles
+// then hold no others.
 template <int NQT, int KL>
 __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries, int Q, EmbView hist, int N,
                                           int d, int k, int chunk_rows, int n_chunks, int q_tiles,
                                           const float* __restrict__ theta0, const int* __restrict__ only_flagged,
-                                          uint64_t* __restrict__ partial, const int b) {
+                                          int n_flagged, uint64_t* __restrict__ partial, const int b) {
   constexpr int BQ = 32 * NQT;
   constexpr int QPW = BQ / 4;              // queries merged by each wave
   constexpr int kCap = CapOf<NQT>::value;
@@ -271,36 +306,31 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
   const int h_begin = chunk * chunk_rows;
   const int h_end = min(N, h_begin + chunk_rows);
 
-  // As the exact fallback, only tiles holding a flagged query do any work.
-  if (only_flagged) {
-    if (tid == 0) sm.rounds = 0;
-    __syncthreads();
-    if (tid < BQ && q0 + tid < Q && only_flagged[q0 + tid]) sm.rounds = 1;
-    __syncthreads();
-    if (sm.rounds == 0) return;
-  }
+  const int n_q = only_flagged ? n_flagged : Q;        // queries in all tiles
+  for (int i = tid; i < BQ; i += kThreads) sm.query[i] = min(q0 + i, Q - 1);
+  __syncthreads();
+  if (only_flagged) gather_flagged(sm, only_flagged, Q, q0);
+  int q_of[Core<NQT>::B_LD];
+#pragma unroll
+  for (int c = 0; c < Core<NQT>::B_LD; ++c) q_of[c] = sm.query[Core<NQT>::slot(c)];
 
   for (int i = tid; i < BQ * KL; i += kThreads) sm.list[i] = kPadKey;
   for (int i = tid; i < BQ; i += kThreads) {
     sm.theta[i] = -__builtin_inff();
-    // As the fallback: no candidates for a query that is not flagged, and the
-    // threshold again for one that has more candidates than its arrays hold
-    // (50,000 equal rows of 100,000, 300 queries of which 100 are equal to them,
-    // k = 128, d = 384: 852 us without it). It is a bound that k of this
-    // query's scores reach; only where too few did, it is not.
-    float bound = (theta0 && q0 + i < Q) ? theta0[q0 + i] : -__builtin_inff();
-    if (only_flagged) {
-      const int f = q0 + i < Q ? only_flagged[q0 + i] : kNotFlagged;
-      bound = f == kNotFlagged ? __builtin_inff() : (f == kOverflowed ? bound : -__builtin_inff());
-    }
-    sm.theta0[i] = bound;
+    // As the fallback: the threshold again for a query that has more candidates
+    // than its arrays hold (50,000 equal rows of 100,000, 300 queries of which
+    // 100 are equal to them, k = 128, d = 384: 852 us without it). It is a bound
+    // that k of this query's scores reach; only where too few did, it is not.
+    const int q = sm.query[i];
+    const bool bound = theta0 && q0 + i < n_q && (!only_flagged || only_flagged[q] == kOverflowed);
+    sm.theta0[i] = bound ? theta0[q] : -__builtin_inff();
     sm.fill[i] = 0;
   }
 
   for (int h0 = h_begin; h0 < h_end; h0 += kStepRows) {
     floatx16 acc[2][NQT];
     const int step_end = min(h_end, h0 + kStepRows);
-    gemm_step<NQT>(acc, hist, h0, step_end, queries, q0, Q, d, sm.a_tile, sm.b_tile);
+    gemm_step<NQT>(acc, hist, h0, step_end, queries, q_of, d, sm.a_tile, sm.b_tile);
 
     // ---------------- filter, rank, append, merge ----------------
     // One compare per score: s >= theta0 and s > theta  <=>  s > max(below(theta0), theta),
@@ -329,7 +359,7 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
         const int n_in = 4 * (c >> 3) + min(c & 7, 4);
         m &= n_in >= 32 ? ~0u : (1u << n_in) - 1u;
       }
-      if (q0 + ql >= Q) m = 0;
+      if (q0 + ql >= n_q) m = 0;
       bits[t] = m;
       my_cnt[t] = __popc(m);
       sm.cnt[ql * 8 + 2 * w + half] = my_cnt[t];
@@ -407,8 +437,7 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
   __syncthreads();
   for (int i = tid; i < BQ * KL; i += kThreads) {
     const int ql = i / KL, e = i - ql * KL;
-    const int q = q0 + ql;
-    if (q < Q) partial[((size_t)q * n_chunks + chunk) * KL + e] = sm.list[i];
+    if (q0 + ql < n_q) partial[((size_t)sm.query[ql] * n_chunks + chunk) * KL + e] = sm.list[i];
   }
 }
 
@@ -420,13 +449,15 @@ __global__ void __launch_bounds__(kThreads, 1) sim_topk_kernel(
     uint64_t* __restrict__ partial) {
   __shared__ __align__(16) TopkSmem<NQT, KL> sm;
   // As the exact fallback: nothing to do unless a query of this call was
-  // flagged (the flagging kernel set the word).
-  if (only_flagged && *flag_word == 0u) return;
+  // flagged (the flagging kernel counts them in the word), and the tiles of
+  // those that were.
+  const int n_flagged = only_flagged ? (int)*flag_word : 0;
+  if (only_flagged) q_tiles = (n_flagged + 32 * NQT - 1) / (32 * NQT);
   // Tiles b = blockIdx.x, + gridDim.x, ... (one each for the full search).
   for (int b = blockIdx.x; b < q_tiles * n_chunks; b += gridDim.x) {
     __syncthreads();                         // the previous tile's LDS reads are done
     list_tile<NQT, KL>(sm, queries, Q, hist, N, d, k, chunk_rows, n_chunks, q_tiles, theta0, only_flagged,
-                       partial, b);
+                       n_flagged, partial, b);
   }
 }
 

@@ -85,11 +85,11 @@ hipError_t launch_stream_sample(EmbView queries, int Q, EmbView hist, int N, int
 // filtered and stream paths; -inf when unset.
 float debug_theta_floor();
 // Queries sent to the exact fallback: flags[q] says why (more candidates than
-// their arrays hold, or fewer than min(k, N)), and *word = 1 once any query is
-// flagged. The search's first kernel that always runs (the
-// filter kernel, the stream search) clears the word, so that the fallback
-// kernels return at once when it is still 0 (kDenseRan: see launch_dense); nothing here depends on the
-// call, so a captured graph replays it as it stands.
+// their arrays hold, or fewer than min(k, N)), and *word counts them. The
+// search's first kernel that always runs (the filter kernel, the stream search)
+// clears the word, so that the fallback kernels return at once when it is still
+// 0 (kDenseRan: see launch_dense); nothing here depends on the call, so a
+// captured graph replays it as it stands.
 enum FlagReason { kNotFlagged = 0, kOverflowed = 1, kTooFew = 2 };
 struct Flagged {
   int* flags;
@@ -131,7 +131,7 @@ struct DenseHist {
   float* mass = nullptr;
 };
 // `ran`: set to kDenseRan, for plans whose path the sizes do not tell.
-constexpr uint32_t kDenseRan = 2;
+constexpr uint32_t kDenseRan = 0xFFFFFFFFu;    // no count of flagged queries
 hipError_t launch_dense(EmbView queries, int Q, EmbView hist, int N, int d, int k, int ld, float* scores,
                         uint32_t* ran, int32_t* ids, float* sims, const DenseHist& h, hipStream_t stream);
 
