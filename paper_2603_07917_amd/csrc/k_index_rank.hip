@@ -37,6 +37,18 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mass, size_t 
       if (b0 + j < B) v = *reinterpret_cast<const float4*>(mass + row + b0 + j);
       p[j] = v.x; p[j + 1] = v.y; p[j + 2] = v.z; p[j + 3] = v.w;
     }
+  } else if (C % 4 == 0) {                           // four at a time from 4-byte aligned addresses
+#pragma unroll
+    for (int j = 0; j < C; j += 4) {
+      if (kFull || b0 + j + 3 < B) {
+        float v[4];
+        __builtin_memcpy(v, mass + row + b0 + j, sizeof v);
+        p[j] = v[0]; p[j + 1] = v[1]; p[j + 2] = v[2]; p[j + 3] = v[3];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[j + i] = b0 + j + i < B ? mass[row + b0 + j + i] : 0.0f;
+      }
+    }
   } else {
 #pragma unroll
     for (int j = 0; j < C; ++j) p[j] = (kFull || b0 + j < B) ? mass[row + b0 + j] : 0.0f;
@@ -92,11 +104,18 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
 
   float p[C], p_next[C];
   int I_next = 0;
+  // A given cost row that does not fill its lanes is loaded as the masses are
+  // (C <= 16): read one by one where used, the 16 consecutive costs of each of 64
+  // lanes took 65,536 rows of 200 bins 74 us, so 21; full rows are as fast so
+  // (the compiler joins the reads).
+  constexpr bool kKeepCost = kMode == kGivenCost && C <= 16 && !kFull;
+  float x_cost[kKeepCost ? C : 1], x_next[kKeepCost ? C : 1];
   // Next row's prompt length before its masses: loads return in order.
   auto load_next = [&](int base) {
     const int q = row_of(base);
     if (kFused) I_next = prompt_len[q];
     load_row<C, kFull>(mass, (size_t)q * (size_t)B, b0, B, p_next);
+    if constexpr (kKeepCost) load_row<C, kFull>(cost, (size_t)q * (size_t)B, b0, B, x_next);
   };
   if (q_first < Q) load_next(q_first);             // in flight while LDS is set up
   if (kFused) {
@@ -121,6 +140,10 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     const size_t row = (size_t)q * (size_t)B;
 #pragma unroll
     for (int j = 0; j < C; ++j) p[j] = p_next[j];
+    if constexpr (kKeepCost) {
+#pragma unroll
+      for (int j = 0; j < C; ++j) x_cost[j] = x_next[j];
+    }
     const double I = (double)I_next;
     store_result();
     res_base = base;
@@ -161,6 +184,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
         const double r = in ? repr_l[j] : 0.0;
         return r * fma(0.5, r, I);
       }
+      if (kKeepCost) return (double)x_cost[kKeepCost ? j : 0];
       return in ? (double)cost[row + b] : 0.0;
     };
     if (kMode == kVariant && var.noise > 0.0f) {     // p' = (1 - w) p / sum(p) + w / B
