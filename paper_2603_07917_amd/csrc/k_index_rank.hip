@@ -135,6 +135,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     }
   };
   const int n_lv = kMode == kTable ? var.levels : 1;
+  constexpr int kStep = kMode == kTable ? kR : 1;
   for (int base = q_first; base < Q; base += q_step) {
     const int q = row_of(base);
     const size_t row = (size_t)q * (size_t)B;
@@ -160,10 +161,12 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
       }
     }
     float lane_res = 0.0f;
-   for (int lv = 0; lv < n_lv; lv += kMode == kTable ? kR : 1) {
+   // Counted so that levels up to 2^31 - 1 do not run over.
+   for (int step = 0; step <= (n_lv - 1) / kStep; ++step) {
+    const int lv = step * kStep;
     double a = 0.0;                                 // service already received
     if (kAtt) {
-      const double o = kMode == kTable ? (double)(lv + group) * (double)bucket
+      const double o = kMode == kTable ? ((double)lv + (double)group) * (double)bucket
                                        : (double)((max(generated[q], 0) / bucket) * bucket);
       a = o * fma(0.5, o, I);
     }
@@ -222,7 +225,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     // level, so what it rules out stays ruled out). A row of 64 predicted
     // lengths passes its longest one after about 16 of 41 levels of 200.
     if (kMode == kTable && !__any(f_total != 0.0) && I >= 0.0) {
-      for (int t = (lv & ~(kWave - 1)) + lane; t < n_lv; t += kWave)
+      for (long long t = (lv & ~(kWave - 1)) + lane; t < n_lv; t += kWave)
         index[(size_t)t * (size_t)Q + (size_t)q] = t < lv ? lane_res : __builtin_inff();
       break;
     }
@@ -291,9 +294,9 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
             (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(res), g * G + G - 1));
         if (lane == t0 + g) lane_res = v;
       }
-      if (t0 + kR == kWave || lv + kR >= n_lv) {
+      if (t0 + kR == kWave || n_lv - lv <= kR) {
         const int t = (lv & ~(kWave - 1)) + lane;
-        if (t < lv + kR && t < n_lv) index[(size_t)t * (size_t)Q + (size_t)q] = lane_res;
+        if (t - lv < kR && t < n_lv) index[(size_t)t * (size_t)Q + (size_t)q] = lane_res;
       }
     }
    }
