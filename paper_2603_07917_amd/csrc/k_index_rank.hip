@@ -134,7 +134,10 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
       if (kArg) argmin[res_base + group] = res_arg;
     }
   };
-  const int n_lv = kMode == kTable ? var.levels : 1;
+  // Levels [lv_first, n_lv) of the table (blockIdx.y: their share).
+  const int lv_first = kMode == kTable ? (int)blockIdx.y * var.level_share : 0;
+  const int n_lv = kMode == kTable ? lv_first + min(var.level_share, var.levels - lv_first)
+                                   : 1;
   constexpr int kStep = kMode == kTable ? kR : 1;
   for (int base = q_first; base < Q; base += q_step) {
     const int q = row_of(base);
@@ -162,8 +165,8 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     }
     float lane_res = 0.0f;
    // Counted so that levels up to 2^31 - 1 do not run over.
-   for (int step = 0; step <= (n_lv - 1) / kStep; ++step) {
-    const int lv = step * kStep;
+   for (int step = 0; step <= (n_lv - lv_first - 1) / kStep; ++step) {
+    const int lv = lv_first + step * kStep;
     double a = 0.0;                                 // service already received
     if (kAtt) {
       const double o = kMode == kTable ? ((double)lv + (double)group) * (double)bucket
@@ -226,7 +229,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     // lengths passes its longest one after about 16 of 41 levels of 200.
     if (kMode == kTable && !__any(f_total != 0.0) && I >= 0.0) {
       for (long long t = (lv & ~(kWave - 1)) + lane; t < n_lv; t += kWave)
-        index[(size_t)t * (size_t)Q + (size_t)q] = t < lv ? lane_res : __builtin_inff();
+        if (t >= lv_first) index[(size_t)t * (size_t)Q + (size_t)q] = t < lv ? lane_res : __builtin_inff();
       break;
     }
     if (kMode == kVariant && var.kind == 1) {        // the mean: sum p x / sum p
@@ -296,7 +299,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
       }
       if (t0 + kR == kWave || n_lv - lv <= kR) {
         const int t = (lv & ~(kWave - 1)) + lane;
-        if (t - lv < kR && t < n_lv) index[(size_t)t * (size_t)Q + (size_t)q] = lane_res;
+        if (t >= lv_first && t - lv < kR && t < n_lv) index[(size_t)t * (size_t)Q + (size_t)q] = lane_res;
       }
     }
    }
@@ -314,19 +317,28 @@ hipError_t launch_index_v(const float* mass, const float* cost, const int32_t* p
   // representatives (65,536 rows x 1,024 bins: 2,048 workgroups 65.6 us, 4,096
   // 67.1, 16,384 81; table of 32,768 rows x 41 levels: 1,024 workgroups 126 us,
   // 2,048 118, 4,096 125, 8,192 138).
-  const long most = kMode == kTable || C * G >= 1024 ? 2048 : 4096;
+  const long most = kMode >= kTable || (C * G >= 1024 && kMode != kGivenCost) ? 2048 : 4096;
   const int rows = waves_per_block * (kMode == kTable ? 1 : kWave / G);
   const long blocks = std::min<long>(((long)Q + rows - 1) / rows, most);
+  // Table of few rows: their levels in shares (multiples of 64 / G), while the
+  // waves are fewer than four a CU. One row of 2,048 bins and 41 levels took
+  // one wave 79 us, shared 7.5.
+  unsigned shares = 1;
+  if (kMode == kTable) {
+    const long want = std::max(1L, 256 / blocks), steps = ((long)var.levels + kWave / G - 1) / (kWave / G);
+    const long share = (steps + std::min(want, steps) - 1) / std::min(want, steps) * (kWave / G);
+    var.level_share = (int)std::min<long>(share, var.levels);
+    shares = (unsigned)((var.levels - 1) / var.level_share + 1);
+  }
   // Representatives, a pitch of C + 2 per lane that has any (C as it is for C < 4).
   const size_t lds = kMode != kGivenCost ? (size_t)((B + C - 1) / C) * (C >= 4 ? C + 2 : C) * sizeof(double) : 0;
-  if (argmin)
-    hipLaunchKernelGGL((index_kernel<C, G, kFull, kMode, true>), dim3((unsigned)blocks),
-                       dim3(64 * waves_per_block), lds, stream, mass, cost, prompt_len, repr, generated,
-                       bucket, Q, B, index, argmin, var);
+  const dim3 grid((unsigned)blocks, shares);
+  if (argmin && kMode < kTable)                      // the tables have none
+    hipLaunchKernelGGL((index_kernel<C, G, kFull, kMode, kMode < kTable>), grid, dim3(64 * waves_per_block), lds,
+                       stream, mass, cost, prompt_len, repr, generated, bucket, Q, B, index, argmin, var);
   else
-    hipLaunchKernelGGL((index_kernel<C, G, kFull, kMode, false>), dim3((unsigned)blocks),
-                       dim3(64 * waves_per_block), lds, stream, mass, cost, prompt_len, repr, generated,
-                       bucket, Q, B, index, argmin, var);
+    hipLaunchKernelGGL((index_kernel<C, G, kFull, kMode, false>), grid, dim3(64 * waves_per_block), lds, stream, mass,
+                       cost, prompt_len, repr, generated, bucket, Q, B, index, argmin, var);
   return hipGetLastError();
 }
 

@@ -166,6 +166,7 @@ struct IndexVariant {
   int kind = 0;
   float noise = 0.0f;
   int levels = 0;     // > 0: the refreshed index at o = 0, bucket, ..., (levels - 1) * bucket
+  int level_share = 0;   // of them, per workgroup row (set by the launch)
 };
 hipError_t launch_index(const float* mass, const float* cost, const int32_t* prompt_len,
                         const double* bin_repr, const int32_t* generated, int bucket, int Q, int B,

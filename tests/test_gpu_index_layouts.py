@@ -61,3 +61,43 @@ def test_index_layouts(B):
         assert np.array_equal(table[lv].view(np.uint32), one.view(np.uint32)), lv
     mean = host(sage.index_variant(md, pd, rd, kind="mean", noise=0.2))
     assert np.array_equal(np.isinf(mean), mass.sum(axis=1) == 0)
+
+
+@pytest.mark.parametrize("B", [1, 40, 64, 200, 256, 301, 512, 513, 1024, 2048])
+@pytest.mark.parametrize("Q,levels", [(1, 1), (1, 70), (3, 131), (9, 5), (70, 6)])
+def test_table_levels_in_shares(B, Q, levels):
+    """The refresh table where a few rows' levels are shared between workgroups
+    (with a share that starts inside a block of 64 levels): the bits of the
+    per-level calls, past a row's last outcome too."""
+    rng = np.random.default_rng(B + Q + levels)
+    mass = rng.dirichlet(np.full(B, 0.3), size=Q).astype(np.float32)
+    mass[rng.random((Q, B)) < 0.5] = 0.0
+    mass[Q // 2, :] = 0.0                                     # no mass at all
+    if Q > 2:
+        mass[2, B // 3:] = 0.0                                # done after a few levels
+    plen = rng.integers(0, 4000, size=Q).astype(np.int32)
+    _, r = workloads.log_bins(16384, B)
+    md, pd, rd = dev(mass), dev(plen), dev(r)
+    bucket = max(1, 20000 // levels)
+    table = host(sage.index_attained_table(md, pd, rd, levels, bucket, out=torch.full((levels, Q), 7.0, device="cuda")))
+    for lv in range(levels):
+        one = host(sage.index_attained(md, pd, rd, dev(np.full(Q, lv * bucket, np.int32)), bucket))
+        assert np.array_equal(table[lv].view(np.uint32), one.view(np.uint32)), lv
+    Gt, _ = oracle.gittins_attained(mass.astype(np.float64), oracle.cost(plen, r),
+                                    oracle.attained_service(plen, np.full(Q, (levels // 2) * bucket), bucket))
+    close(table[levels // 2], Gt)
+
+
+@pytest.mark.parametrize("B", [3, 31, 67, 102, 127, 200, 255, 301, 511, 515, 700, 1023, 1100])
+def test_given_cost_rows_of_any_width(B):
+    """Rows whose bins do not fill their lanes, masses and costs loaded four at a
+    time from any 4-byte aligned place; the last row ends its buffer."""
+    rng = np.random.default_rng(B)
+    Q = 37
+    mass = rng.dirichlet(np.full(B, 0.3), size=Q).astype(np.float32)
+    cost = np.sort(rng.lognormal(8, 2, size=(Q, B)), axis=1).astype(np.float32)
+    G, arg = oracle.gittins(mass.astype(np.float64), cost)
+    g, a = sage.index(dev(mass), cost=dev(cost), with_argmin=True)
+    close(host(g), G)
+    assert np.all(host(a) >= 0)
+    assert np.array_equal(host(sage.index(dev(mass), cost=dev(cost))).view(np.uint32), host(g).view(np.uint32))
