@@ -64,12 +64,16 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mass, size_t 
 // the index of the remaining cost. kVariant takes the cost model, the kind
 // of index (Gittins or mean) and a uniform-mixing weight at run time.
 // kTable: kAttained for every row at each level o = lv * bucket (lv < levels),
-// one row per wave and 64 / G levels at a time.
-enum IndexMode { kGivenCost = 0, kFused = 1, kAttained = 2, kVariant = 3, kTable = 4 };
+// one row per wave and 64 / G levels at a time. kTableRows: the same with 64 / G
+// rows per wave and one level at a time, for tables of few levels, which would
+// leave some of a row's lane groups without one (and have no long run of levels
+// past all mass to skip). Both give kAttained's bits.
+enum IndexMode { kGivenCost = 0, kFused = 1, kAttained = 2, kVariant = 3, kTable = 4, kTableRows = 5 };
+constexpr int kTableRowsMax = 5;     // levels
 // Workgroups per CU the register budget is tuned for (4 waves each).
 // The table keeps its support in registers: 2 of them and no spills at C = 16.
 template <int C, int kMode> struct IndexOcc {
-  static constexpr int value = C <= 8 ? 4 : (C == 16 ? (kMode == 4 ? 2 : 3) : 1);
+  static constexpr int value = C <= 8 ? 4 : (C == 16 ? (kMode >= 4 ? 2 : 3) : 1);
 };
 
 constexpr int kNoBin = 0x7fffffff;   // a lane without a candidate bin
@@ -83,7 +87,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
                                                     int Q, int B, float* __restrict__ index,
                                                     int32_t* __restrict__ argmin, IndexVariant var) {
   constexpr bool kFused = kMode != kGivenCost;
-  constexpr bool kAtt = kMode == kAttained || kMode == kTable;
+  constexpr bool kAtt = kMode == kAttained || kMode == kTable || kMode == kTableRows;
   constexpr int kR = kWave / G;                    // rows, or levels of a row, at a time
   constexpr int kRows = kMode == kTable ? 1 : kR;  // rows per wave and turn
   // Representatives (fused cost only): lane l's C of them at l * kPitch. Without
@@ -129,7 +133,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
   float res = 0.0f;
   int res_arg = -1, res_base = -1;
   auto store_result = [&]() {
-    if (kMode != kTable && res_base >= 0 && l == G - 1 && res_base + group < Q) {
+    if (kMode != kTable && kMode != kTableRows && res_base >= 0 && l == G - 1 && res_base + group < Q) {
       index[res_base + group] = res;
       if (kArg) argmin[res_base + group] = res_arg;
     }
@@ -137,7 +141,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
   // Levels [lv_first, n_lv) of the table (blockIdx.y: their share).
   const int lv_first = kMode == kTable ? (int)blockIdx.y * var.level_share : 0;
   const int n_lv = kMode == kTable ? lv_first + min(var.level_share, var.levels - lv_first)
-                                   : 1;
+                                   : (kMode == kTableRows ? var.levels : 1);
   constexpr int kStep = kMode == kTable ? kR : 1;
   for (int base = q_first; base < Q; base += q_step) {
     const int q = row_of(base);
@@ -154,7 +158,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     if (base + q_step < Q) load_next(base + q_step);
     // Refresh table: the support stays in registers across the levels (C <= 16),
     // and lane t keeps the result of level t (mod 64), written 64 at a time.
-    constexpr bool kKeepX = kMode == kTable && C <= 16;
+    constexpr bool kKeepX = (kMode == kTable || kMode == kTableRows) && C <= 16;
     double x_row[kKeepX ? C : 1];
     if (kKeepX) {
 #pragma unroll
@@ -169,8 +173,9 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     const int lv = lv_first + step * kStep;
     double a = 0.0;                                 // service already received
     if (kAtt) {
-      const double o = kMode == kTable ? ((double)lv + (double)group) * (double)bucket
-                                       : (double)((max(generated[q], 0) / bucket) * bucket);
+      const double o = kMode == kTable       ? ((double)lv + (double)group) * (double)bucket
+                       : kMode == kTableRows ? (double)lv * (double)bucket
+                                             : (double)((max(generated[q], 0) / bucket) * bucket);
       a = o * fma(0.5, o, I);
     }
 
@@ -232,6 +237,11 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
         if (t >= lv_first) index[(size_t)t * (size_t)Q + (size_t)q] = t < lv ? lane_res : __builtin_inff();
       break;
     }
+    if (kMode == kTableRows && __all(f_total == 0.0 && I >= 0.0)) {
+      for (int t = lv + l; t < n_lv; t += G)
+        if (base + group < Q) index[(size_t)t * (size_t)Q + (size_t)q] = __builtin_inff();
+      break;
+    }
     if (kMode == kVariant && var.kind == 1) {        // the mean: sum p x / sum p
       const double s_incl = s_base + lane_s;
       res = f_total > 0.0 ? (float)(s_incl / f_total) : __builtin_inff();   // the last lane's
@@ -289,6 +299,7 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
       // where fp64 takes six instructions.
       res = f32_from_order_bits(group_min_u32<G>(f32_order_bits((float)r)));
     }
+    if (kMode == kTableRows && l == G - 1 && base + group < Q) index[(size_t)lv * (size_t)Q + (size_t)q] = res;
     if (kMode == kTable) {
       const int t0 = lv & (kWave - 1);                // lv is a multiple of kR, which divides 64
 #pragma unroll
@@ -356,6 +367,14 @@ hipError_t launch_index_c(const float* mass, const float* cost, const int32_t* p
   if (mode == kVariant) {
     if (full) SAGE_INDEX_LAUNCH(true, kVariant);
     SAGE_INDEX_LAUNCH(false, kVariant);
+  }
+  if constexpr (G < kWave) {
+    // 65,536 rows x 256 bins: one level 63 -> 19 us (64 lanes a row: 28), two
+    // 63 -> 28 (47); 512 bins: three 105 -> 73 (85), five 146 -> 113 (136).
+    if (mode == kTable && var.levels <= kTableRowsMax) {
+      if (full) SAGE_INDEX_LAUNCH(true, kTableRows);
+      SAGE_INDEX_LAUNCH(false, kTableRows);
+    }
   }
   if (mode == kTable) {
     if (full) SAGE_INDEX_LAUNCH(true, kTable);

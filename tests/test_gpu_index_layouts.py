@@ -64,11 +64,12 @@ def test_index_layouts(B):
 
 
 @pytest.mark.parametrize("B", [1, 40, 64, 200, 256, 301, 512, 513, 1024, 2048])
-@pytest.mark.parametrize("Q,levels", [(1, 1), (1, 70), (3, 131), (9, 5), (70, 6)])
-def test_table_levels_in_shares(B, Q, levels):
+@pytest.mark.parametrize("Q,levels", [(1, 1), (1, 70), (3, 131), (9, 5), (70, 6), (133, 2), (1030, 3)])
+def test_table_shares_and_few_levels(B, Q, levels):
     """The refresh table where a few rows' levels are shared between workgroups
-    (with a share that starts inside a block of 64 levels): the bits of the
-    per-level calls, past a row's last outcome too."""
+    (with a share that starts inside a block of 64 levels) and where it has so
+    few levels that rows take the lanes: the bits of the per-level calls, past a
+    row's last outcome too."""
     rng = np.random.default_rng(B + Q + levels)
     mass = rng.dirichlet(np.full(B, 0.3), size=Q).astype(np.float32)
     mass[rng.random((Q, B)) < 0.5] = 0.0
