@@ -102,3 +102,18 @@ def test_given_cost_rows_of_any_width(B):
     close(host(g), G)
     assert np.all(host(a) >= 0)
     assert np.array_equal(host(sage.index(dev(mass), cost=dev(cost))).view(np.uint32), host(g).view(np.uint32))
+
+
+@pytest.mark.parametrize("B", [16, 300])
+def test_table_of_the_most_levels(B):
+    """levels * bucket = 2^31 - 1: four (B = 16) or two levels at a time would
+    count past the 32-bit range in the last step. Done after 16,384 levels."""
+    levels = 2**31 - 1
+    _, r = workloads.log_bins(16384, B)
+    md, pd, rd = dev(np.full((1, B), 1.0 / B, np.float32)), dev(np.array([100], np.int32)), dev(r)
+    table = sage.index_attained_table(md, pd, rd, levels, 1).view(-1)
+    for lv in (0, 1, 63, 64, 8191, 16000):
+        one = host(sage.index_attained(md, pd, rd, dev(np.array([lv], np.int32)), 1))
+        assert np.array_equal(host(table[lv:lv + 1]).view(np.uint32), one.view(np.uint32)), lv
+    done = int(np.ceil(r[-1]))
+    assert bool(torch.isinf(table[done:]).all()) and bool(torch.isfinite(table[:int(r[-1])]).all())
