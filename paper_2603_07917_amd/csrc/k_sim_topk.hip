@@ -277,7 +277,7 @@ __device__ __forceinline__ void gather_flagged(TopkSmem<NQT, KL>& sm, const int*
 // One (query tile, history chunk) of the list search: of all Q queries, or as
 // the exact fallback of the n_flagged queries that are flagged, whose tiles
 // then hold no others.
-template <int NQT, int KL>
+template <int NQT, int KL, bool kFallback>
 __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries, int Q, EmbView hist, int N,
                                           int d, int k, int chunk_rows, int n_chunks, int q_tiles,
                                           const float* __restrict__ theta0, const int* __restrict__ only_flagged,
@@ -306,13 +306,16 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
   const int h_begin = chunk * chunk_rows;
   const int h_end = min(N, h_begin + chunk_rows);
 
-  const int n_q = only_flagged ? n_flagged : Q;        // queries in all tiles
-  for (int i = tid; i < BQ; i += kThreads) sm.query[i] = min(q0 + i, Q - 1);
-  __syncthreads();
-  if (only_flagged) gather_flagged(sm, only_flagged, Q, q0);
+  const int n_q = kFallback ? n_flagged : Q;           // queries in all tiles
+  if (kFallback) {
+    for (int i = tid; i < BQ; i += kThreads) sm.query[i] = 0;
+    __syncthreads();
+    gather_flagged(sm, only_flagged, Q, q0);
+  }
+  auto query = [&](int i) { return kFallback ? sm.query[i] : min(q0 + i, Q - 1); };   // of slot i
   int q_of[Core<NQT>::B_LD];
 #pragma unroll
-  for (int c = 0; c < Core<NQT>::B_LD; ++c) q_of[c] = sm.query[Core<NQT>::slot(c)];
+  for (int c = 0; c < Core<NQT>::B_LD; ++c) q_of[c] = query(Core<NQT>::slot(c));
 
   for (int i = tid; i < BQ * KL; i += kThreads) sm.list[i] = kPadKey;
   for (int i = tid; i < BQ; i += kThreads) {
@@ -321,8 +324,8 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
     // than its arrays hold (50,000 equal rows of 100,000, 300 queries of which
     // 100 are equal to them, k = 128, d = 384: 852 us without it). It is a bound
     // that k of this query's scores reach; only where too few did, it is not.
-    const int q = sm.query[i];
-    const bool bound = theta0 && q0 + i < n_q && (!only_flagged || only_flagged[q] == kOverflowed);
+    const int q = query(i);
+    const bool bound = theta0 && q0 + i < n_q && (!kFallback || only_flagged[q] == kOverflowed);
     sm.theta0[i] = bound ? theta0[q] : -__builtin_inff();
     sm.fill[i] = 0;
   }
@@ -437,11 +440,11 @@ __device__ __forceinline__ void list_tile(TopkSmem<NQT, KL>& sm, EmbView queries
   __syncthreads();
   for (int i = tid; i < BQ * KL; i += kThreads) {
     const int ql = i / KL, e = i - ql * KL;
-    if (q0 + ql < n_q) partial[((size_t)sm.query[ql] * n_chunks + chunk) * KL + e] = sm.list[i];
+    if (q0 + ql < n_q) partial[((size_t)query(ql) * n_chunks + chunk) * KL + e] = sm.list[i];
   }
 }
 
-template <int NQT, int KL>
+template <int NQT, int KL, bool kFallback>
 __global__ void __launch_bounds__(kThreads, 1) sim_topk_kernel(
     EmbView queries, int Q, EmbView hist, int N, int d,
     int k, int chunk_rows, int n_chunks, int q_tiles, const float* __restrict__ theta0,
@@ -451,12 +454,12 @@ __global__ void __launch_bounds__(kThreads, 1) sim_topk_kernel(
   // As the exact fallback: nothing to do unless a query of this call was
   // flagged (the flagging kernel counts them in the word), and the tiles of
   // those that were.
-  const int n_flagged = only_flagged ? (int)*flag_word : 0;
-  if (only_flagged) q_tiles = (n_flagged + 32 * NQT - 1) / (32 * NQT);
+  const int n_flagged = kFallback ? (int)*flag_word : 0;
+  if (kFallback) q_tiles = (n_flagged + 32 * NQT - 1) / (32 * NQT);
   // Tiles b = blockIdx.x, + gridDim.x, ... (one each for the full search).
   for (int b = blockIdx.x; b < q_tiles * n_chunks; b += gridDim.x) {
     __syncthreads();                         // the previous tile's LDS reads are done
-    list_tile<NQT, KL>(sm, queries, Q, hist, N, d, k, chunk_rows, n_chunks, q_tiles, theta0, only_flagged,
+    list_tile<NQT, KL, kFallback>(sm, queries, Q, hist, N, d, k, chunk_rows, n_chunks, q_tiles, theta0, only_flagged,
                        n_flagged, partial, b);
   }
 }
@@ -1064,10 +1067,13 @@ hipError_t launch_lists(EmbView queries, int Q, EmbView hist, int N, int d, int 
   // The fallback runs as one round of workgroups (one per CU) that loop over
   // the tiles, and return at once when no query of the call was flagged.
   const int tiles = p.q_tiles * p.n_chunks;
-  hipLaunchKernelGGL((sim_topk_kernel<NQT, KL>), dim3(only_flagged ? std::min(tiles, 256) : tiles), dim3(kThreads),
-                     0, stream, queries, Q, hist, N, d, k, p.chunk_rows, p.n_chunks, p.q_tiles, theta0,
-                     only_flagged ? only_flagged->flags : nullptr, only_flagged ? only_flagged->word : nullptr,
-                     partial);
+  if (only_flagged)
+    hipLaunchKernelGGL((sim_topk_kernel<NQT, KL, true>), dim3(std::min(tiles, 256)), dim3(kThreads), 0, stream, queries,
+                       Q, hist, N, d, k, p.chunk_rows, p.n_chunks, p.q_tiles, theta0, only_flagged->flags,
+                       only_flagged->word, partial);
+  else
+    hipLaunchKernelGGL((sim_topk_kernel<NQT, KL, false>), dim3(tiles), dim3(kThreads), 0, stream, queries, Q, hist, N, d,
+                       k, p.chunk_rows, p.n_chunks, p.q_tiles, theta0, nullptr, nullptr, partial);
   return hipGetLastError();
 }
 
