@@ -1210,7 +1210,10 @@ bool dense_takes(int Q, int N, int d) {
 // filtered search's times (us, measured at k = 64 over 17 to 1,024 queries, 64
 // to 32,768 rows and d = 384 to 8,192, both layouts). Up to 256 queries it is,
 // or is at least no slower than any search was before it; for k > 64 the other
-// one is mostly the exact lists, two to three times slower. Past that its select
+// one is mostly the exact lists, two to three times slower but for a single tile
+// of rows and k > 128, whose lists hold all of them (dense / lists, k = 256:
+// 1,024 x 50 x 128 67 / 38, x 2,048 72 / 62; 600 x 100 x 128 62 / 57; 600 x 10 x
+// 2,048 46 / 55). Past that its select
 // takes a workgroup of 16 waves per query, about 36 ns each, and every 32 x 32
 // tile fetches its own operands: 1.6e14 products a second, and 0.7e14 where
 // rows lie d apart, so that a load touches twice as many cache lines. The
@@ -1221,7 +1224,8 @@ bool dense_takes(int Q, int N, int d) {
 // 1,024 x 64 x 384 45 / 28.
 bool dense_pays(int Q, int N, int d, int k, bool sampled, bool panels) {
   if (!dense_takes(Q, N, d)) return false;
-  if (Q <= 256 || k > 64) return true;
+  if (Q <= 256) return true;
+  if (k > 64) return !(k > 128 && N <= 128 && 0.06 * Q > 20.0 + d / 64.0);
   const double dense = 4.0 + 0.036 * Q + (double)Q * N * d / (panels ? 1.6e8 : 0.7e8);
   const double filtered = sampled ? 35.0 + d / 30.0 : std::min(48.0, 20.0 + 0.017 * N) + d / 60.0;
   return dense <= filtered;

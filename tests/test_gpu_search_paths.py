@@ -111,6 +111,7 @@ def test_dense_search_edges(Q, N, d, k, layout):
     (256, 300, 64, 32, "dense"), (1024, 2000, 64, 32, "dense"), (1025, 300, 64, 32, "filtered"),
     (1024, 300, 64, 32, "filtered"),    # few rows: a workgroup of 16 waves per query is too many
     (1024, 300, 64, 65, "dense"), (1025, 2500, 64, 100, "lists"),
+    (1024, 100, 64, 256, "lists"), (600, 20, 64, 129, "lists"), (300, 100, 64, 256, "dense"), (1024, 100, 64, 128, "dense"),
     (3000, 40, 64, 64, "filtered"),
     # no pre-pass: every row of a chunk is a candidate
     (1025, 8191, 32, 64, "filtered"),   # the largest such store, its last step and quad cut
