@@ -133,7 +133,6 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
     gmax[tid] = m;
   }
   if (tid == 0) {
-    if (ran && q == 0) *ran = kDenseRan;
     n_cand = 0;
     n_nbr = 0;
     w_all = 0;
@@ -194,6 +193,7 @@ __global__ void __launch_bounds__(1024) dense_select_kernel(const float* __restr
   top.flush();
   merge_lists<S, W>(top.lv, &lists[0][0], w, n <= kCap ? (n + kWave - 1) / kWave : W);
   if (w == 0) top.write(k, ids + (size_t)q * k, sims + (size_t)q * k);
+  else if (q == 0 && tid == 1023 && ran) *ran = kDenseRan;       // here, where no other wave waits for it
   if (h.B < 1) return;
   if (w == 0) {
     int32_t len[S];
