@@ -703,9 +703,6 @@ __global__ void __launch_bounds__(1024) rank_merge_kernel(const uint32_t* __rest
   const int own = blockIdx.x * E / T;               // E divides T
   const uint32_t k = keys_in[at];
   int cnt = s == 0 ? at - own * T : 0;              // place in its own tile
-  // Of the tiles before, every key comes before one of kRankPad's bits (one NaN's);
-  // k + 1 wraps to 0 there, so that the searches below count none of them.
-  if (s == 0 && k == kRankPad) cnt += own * T;
   for (int t0 = 0; t0 < n_tiles; t0 += kGroupTiles) {
     const int n = min(kGroupTiles, n_tiles - t0);
     __syncthreads();                                // the previous group's searches are done
@@ -737,6 +734,9 @@ __global__ void __launch_bounds__(1024) rank_merge_kernel(const uint32_t* __rest
       }
     }
   }
+  // Of the tiles before, every key comes before one of kRankPad's bits (one NaN's);
+  // k + 1 wraps to 0 there, so that the searches above counted none of them.
+  if (s == 0 && k == kRankPad) cnt += own * T;
   part[s][e] = cnt;
   __syncthreads();
   if (s != 0) return;
