@@ -109,10 +109,10 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
   float p[C], p_next[C];
   int I_next = 0;
   // A given cost row that does not fill its lanes is loaded as the masses are
-  // (C <= 16): read one by one where used, the 16 consecutive costs of each of 64
-  // lanes took 65,536 rows of 200 bins 74 us, so 21; full rows are as fast so
-  // (the compiler joins the reads).
-  constexpr bool kKeepCost = kMode == kGivenCost && C <= 16 && !kFull;
+  // (C <= 32): read one by one where used, the 16 consecutive costs of each of 64
+  // lanes took 65,536 rows of 200 bins 74 us, so 18, and 1,500 bins 802, so 168;
+  // full rows are as fast so (the compiler joins the reads).
+  constexpr bool kKeepCost = kMode == kGivenCost && C <= 32 && !kFull;
   float x_cost[kKeepCost ? C : 1], x_next[kKeepCost ? C : 1];
   // Next row's prompt length before its masses: loads return in order.
   auto load_next = [&](int base) {
@@ -326,9 +326,13 @@ hipError_t launch_index_v(const float* mass, const float* cost, const int32_t* p
   // One turn per wave up to a number of workgroups, then several, the next row
   // loading behind the one being scanned: a new workgroup first stages the
   // representatives (65,536 rows x 1,024 bins: 2,048 workgroups 65.6 us, 4,096
-  // 67.1, 16,384 81; table of 32,768 rows x 41 levels: 1,024 workgroups 126 us,
-  // 2,048 118, 4,096 125, 8,192 138).
-  const long most = kMode >= kTable || (C * G >= 1024 && kMode != kGivenCost) ? 2048 : 4096;
+  // 67.1, 16,384 81; mean of 65,536 x 512: 2,048 27.6, 4,096 29.0; table of 32,768
+  // rows x 41 levels: 1,024 workgroups 126 us, 2,048 118, 4,096 125, 8,192 138).
+  // Where a wave takes much of the register file, one round of them: one a CU at
+  // C = 64 and two at C = 32 (16,384 x 4,096: 2,048 workgroups 101 us, 256 59;
+  // with attained service 246 and 169; 16,384 x 2,048 52 and 41).
+  const long most = C >= 64 ? 256 : C == 32 ? 512 : C * G == 512 ? 2048
+                    : kMode >= kTable || (C * G >= 1024 && kMode != kGivenCost) ? 2048 : 4096;
   const int rows = waves_per_block * (kMode == kTable ? 1 : kWave / G);
   const long blocks = std::min<long>(((long)Q + rows - 1) / rows, most);
   // Table of few rows: their levels in shares (multiples of 64 / G), while the
