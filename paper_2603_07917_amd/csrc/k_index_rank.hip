@@ -233,8 +233,9 @@ __global__ void __launch_bounds__(256, (IndexOcc<C, kMode>::value)) index_kernel
     // level, so what it rules out stays ruled out). A row of 64 predicted
     // lengths passes its longest one after about 16 of 41 levels of 200.
     if (kMode == kTable && !__any(f_total != 0.0) && I >= 0.0) {
-      for (long long t = (lv & ~(kWave - 1)) + lane; t < n_lv; t += kWave)
-        if (t >= lv_first) index[(size_t)t * (size_t)Q + (size_t)q] = t < lv ? lane_res : __builtin_inff();
+      for (uint32_t t = (uint32_t)((lv & ~(kWave - 1)) + lane); t < (uint32_t)n_lv; t += kWave)
+        if (t >= (uint32_t)lv_first)
+          index[(size_t)t * (size_t)Q + (size_t)q] = t < (uint32_t)lv ? lane_res : __builtin_inff();
       break;
     }
     if (kMode == kTableRows && __all(f_total == 0.0 && I >= 0.0)) {
@@ -328,11 +329,12 @@ hipError_t launch_index_v(const float* mass, const float* cost, const int32_t* p
   // representatives (65,536 rows x 1,024 bins: 2,048 workgroups 65.6 us, 4,096
   // 67.1, 16,384 81; mean of 65,536 x 512: 2,048 27.6, 4,096 29.0; table of 32,768
   // rows x 41 levels: 1,024 workgroups 126 us, 2,048 118, 4,096 125, 8,192 138).
-  // Where a wave takes much of the register file, one round of them: one a CU at
-  // C = 64 and two at C = 32 (16,384 x 4,096: 2,048 workgroups 101 us, 256 59;
-  // with attained service 246 and 169; 16,384 x 2,048 52 and 41).
-  const long most = C >= 64 ? 256 : C == 32 ? 512 : C * G == 512 ? 2048
-                    : kMode >= kTable || (C * G >= 1024 && kMode != kGivenCost) ? 2048 : 4096;
+  // Where a wave takes much of the register file, one round of them (but for the
+  // table, whose rows take unequal time): one a CU at C = 64 and two at C = 32
+  // (16,384 x 4,096: 2,048 workgroups 101 us, 256 59; with attained service 246
+  // and 169; 16,384 x 2,048 52 and 41).
+  const long most = kMode >= kTable ? 2048 : C >= 64 ? 256 : C == 32 ? 512
+                    : C * G == 512 || (C * G >= 1024 && kMode != kGivenCost) ? 2048 : 4096;
   const int rows = waves_per_block * (kMode == kTable ? 1 : kWave / G);
   const long blocks = std::min<long>(((long)Q + rows - 1) / rows, most);
   // Table of few rows: their levels in shares (multiples of 64 / G), while the
