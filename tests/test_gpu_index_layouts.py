@@ -28,7 +28,7 @@ def close(g, G):
     assert np.all(np.abs(g[f].astype(np.float64) - G[f]) <= parity.INDEX_RTOL * np.abs(G[f]))
 
 
-@pytest.mark.parametrize("B", [1, 16, 17, 32, 33, 64, 65, 128, 129, 256, 257, 260, 512, 513, 1024, 1025, 2049])
+@pytest.mark.parametrize("B", [1, 16, 17, 32, 33, 64, 65, 128, 129, 256, 257, 260, 512, 513, 1024, 1025, 1500, 2047, 2048, 2049, 4096])
 def test_index_layouts(B):
     rng = np.random.default_rng(B)
     Q = 133
