@@ -133,7 +133,8 @@ int sage_queue_dispatch(const int32_t* order, int batch, const int64_t* request,
 /*
  * sage_predict_workspace_bytes - bytes of device workspace sage_predict needs
  * for these sizes (it holds scores, candidate keys or partial neighbour
- * lists). Returns 0 for invalid sizes.
+ * lists; up to about 64 KiB per query in large batches, 96 KiB for k > 64).
+ * Returns 0 for invalid sizes.
  */
 size_t sage_predict_workspace_bytes(int Q, int N, int d, int k, int B);
 
